@@ -417,7 +417,11 @@ typedef struct {
   int32_t graph_segment;   /* steps per captured graph (0 = direct launches) */
   int32_t kernel;          /* step kernel used: 0 column-chunk, 1 row, 2 block,
                               3 block-table, 4 spin-s, 5 slice (block-table
-                              tiles, each wave on rows of one block) */
+                              tiles, each wave on rows of one block),
+                              6 resident (every step of a column in one launch,
+                              its vectors on one compute unit: float64 calls
+                              whose sectors all have at most 19456 states and
+                              32 bonds; step_launches still counts the steps) */
   double recursion_ms;     /* hipEvent time on the call's stream from the first
                               to the last recursion-step launch, inclusive */
   int32_t relabelled;      /* problems whose sites the block kernels relabel (fewer

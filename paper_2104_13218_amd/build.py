@@ -24,7 +24,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libkpm.so")
 LIB_ASAN = os.path.join(HERE, "libkpm_asan.so")
-SOURCES = ["kpm_kernels.hip", "kpm_slice.hip", "kpm_thermo.hip", "kpm_adjoint.hip", "kpm_ftlm.hip", "kpm_ed.hip",
+SOURCES = ["kpm_kernels.hip", "kpm_slice.hip", "kpm_resident.hip", "kpm_thermo.hip", "kpm_adjoint.hip", "kpm_ftlm.hip", "kpm_ed.hip",
            "kpm_api.hip"]
 ARCH = os.environ.get("KPM_OFFLOAD_ARCH", "gfx950")
 

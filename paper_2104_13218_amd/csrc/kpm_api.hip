@@ -1182,7 +1182,7 @@ RunShape lanczos_shape(const kpm_problem* p, int n) {
   return s;
 }
 
-size_t lanczos_bytes(const kpm_problem* p, int n, int steps) {
+size_t stepped_lanczos_bytes(const kpm_problem* p, int n, int steps) {
   Planned P;
   if (make_plan(p, n, lanczos_shape(p, n), nullptr, nullptr, P) != KPM_OK) return 0;
   return lanczos_layout(P, steps).total;
@@ -1259,8 +1259,8 @@ int lanczos_turns(const DevicePlan& D, double* vec, double* part, double* dots, 
 
 // Batched Lanczos over every problem (one float64 column each), the recursion
 // of lanczos_turns on H' = H/2.
-int run_lanczos(const kpm_problem* p, int n, int steps, double margin, uint64_t seed,
-                double* e_lo_hi, unsigned char* work, hipStream_t st) {
+int stepped_lanczos(const kpm_problem* p, int n, int steps, double margin, uint64_t seed,
+                    double* e_lo_hi, unsigned char* work, hipStream_t st) {
   Planned P;
   const std::vector<double> two(n, 2.0), zero_b(n, 0.0);
   int r = make_plan(p, n, lanczos_shape(p, n), two.data(), zero_b.data(), P);
@@ -1321,6 +1321,263 @@ int run_lanczos(const kpm_problem* p, int n, int steps, double margin, uint64_t 
     }
   }
   return KPM_OK;
+}
+
+// ------------------------------------------------------ resident recursions
+//
+// Float64 calls whose sectors all fit one compute unit run their whole
+// recursion in one launch, one workgroup per real column (kpm_resident.hip):
+// the bounds and the moments of a 12-site ring took 50 x 5 + 128 launches.
+// The line lies where v_n still fits the 160 KB of LDS (19456 states) and a
+// row's bonds four 16-byte index entries (32).  A larger sector in the call
+// keeps every sector on the step kernels: beside its launches the small
+// sectors' rows are nearly free.  Overrides of the step kernels keep them too.
+
+bool resident_allowed() {
+  return env_int("KPM_RESIDENT", 1) && !std::getenv("KPM_BLOCK") && !std::getenv("KPM_ROW_KERNEL") &&
+         !std::getenv("KPM_CPL");
+}
+
+bool resident_problems(const kpm_problem* p, int n) {
+  if (n > 65535 || !resident_allowed()) return false;   // one grid row per problem
+  for (int i = 0; i < n; ++i)
+    if (two_s_of(p[i]) != 1 || prob_dim(p[i]) > (uint64_t)kResMaxDim || p[i].n_bonds > kResMaxBonds) return false;
+  return true;
+}
+
+struct ResLayout {
+  size_t probs, info, jobs, lz, binom, mask, coef, units, pu0, scale, flag, unstable, up, idx, diag, lohi, alpha, beta, total;
+};
+
+// `cols` columns per problem and K steps of the moments (0: bounds only), the
+// bounds of n_lz problems.
+ResLayout res_layout(const kpm_problem* p, int n, int64_t cols, int64_t K, int n_lz) {
+  ResLayout L{};
+  size_t o = 0;
+  auto put = [&](size_t bytes) {
+    const size_t r = o;
+    o = align_up(o + bytes);
+    return r;
+  };
+  size_t entries = 0, rows = 0;
+  for (int i = 0; i < n; ++i) {
+    const size_t d = (size_t)prob_dim(p[i]);
+    rows += d;
+    entries += d * (size_t)std::max(1, (p[i].n_bonds + 7) / 8);
+  }
+  L.probs = put((size_t)n * sizeof(ProbDev));
+  L.info = put((size_t)n * sizeof(ResInfo));
+  L.jobs = put((size_t)cols * sizeof(ResJob));
+  L.lz = put((size_t)n_lz * sizeof(ResJob));
+  L.binom = put((size_t)kBinomN * kBinomN * 4);
+  L.mask = put((size_t)n * kResMaxBonds * 4);
+  L.coef = put((size_t)n * kResMaxBonds * 8);
+  L.units = put((size_t)n * sizeof(UnitDev));
+  L.pu0 = put((size_t)(n + 1) * 4);
+  L.scale = put((size_t)n * 16);
+  L.flag = put(256);
+  L.unstable = put((size_t)n * 4);
+  L.up = o;
+  L.idx = put(entries * 16);
+  L.diag = put(rows * 8);
+  L.lohi = put((size_t)n * 16);
+  L.alpha = put((size_t)(cols ? K + 1 : 0) * cols * 8);
+  L.beta = put((size_t)K * cols * 8);
+  // never less than the two vectors per column that the step kernels keep: a
+  // stepped estimate of some windows (settle_bounds) finds room there
+  L.total = std::max(o, align_up(16 * rows * (size_t)(cols / n)));
+  return L;
+}
+
+// Columns of all problems of a moments call.
+int64_t res_columns(const kpm_problem* p, int n, const kpm_params& q) {
+  RunShape s;
+  s.vec_kind = q.vec_kind;
+  s.R = q.R;
+  int64_t c = 0;
+  for (int i = 0; i < n; ++i) c += total_columns(p[i], s);
+  return c;
+}
+
+int count_nan(const kpm_problem* p, int n) {
+  int k = 0;
+  for (int i = 0; i < n; ++i) k += std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi);
+  return k;
+}
+
+struct ResRun {
+  ResArgs a{};
+  std::vector<unsigned char> staging;   // alive until the stream is synchronised
+  uint32_t max_dim = 1;
+  int nch = 1, n_jobs = 0, n_lz = 0;
+};
+
+// Uploads the tables of the call and runs the index tables' kernel and the
+// bounds of the problems without given ones.  q: eps, seed, lanczos_steps,
+// bound_margin; with cols > 0 also vec_kind, R, M.
+int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, int64_t K, const ResLayout& L,
+              unsigned char* work, ResRun& R, hipStream_t st) {
+  R.staging.assign(L.up, 0);
+  unsigned char* h = R.staging.data();
+  ProbDev* probs = reinterpret_cast<ProbDev*>(h + L.probs);
+  ResInfo* info = reinterpret_cast<ResInfo*>(h + L.info);
+  ResJob* jobs = reinterpret_cast<ResJob*>(h + L.jobs);
+  ResJob* lz = reinterpret_cast<ResJob*>(h + L.lz);
+  uint32_t* mask = reinterpret_cast<uint32_t*>(h + L.mask);
+  double* coef = reinterpret_cast<double*>(h + L.coef);
+  UnitDev* units = reinterpret_cast<UnitDev*>(h + L.units);
+  int32_t* pu0 = reinterpret_cast<int32_t*>(h + L.pu0);
+  double* scale = reinterpret_cast<double*>(h + L.scale);
+  const std::vector<uint32_t> bn = binom_table();
+  std::memcpy(h + L.binom, bn.data(), bn.size() * 4);
+  RunShape s;
+  s.vec_kind = q.vec_kind;
+  s.R = q.R;
+  int64_t entries = 0, rows = 0, col = 0;
+  std::vector<int> order(n);
+  for (int i = 0; i < n; ++i) {
+    order[i] = i;
+    ProbDev& d = probs[i];
+    d.dim = (int64_t)prob_dim(p[i]);
+    d.n_sites = p[i].n_sites;
+    d.n_up = p[i].n_up;
+    d.n_bonds = p[i].n_bonds;
+    d.cluster = p[i].cluster;
+    d.two_s = 1;
+    ResInfo& f = info[i];
+    f.nch = std::max(1, (p[i].n_bonds + 7) / 8);
+    f.coef_off = i * kResMaxBonds;
+    f.idx_off = entries;
+    f.diag_off = rows;
+    entries += (int64_t)f.nch * d.dim;
+    rows += d.dim;
+    for (int b = 0; b < p[i].n_bonds; ++b) {
+      mask[f.coef_off + b] = (1u << p[i].bond_i[b]) | (1u << p[i].bond_j[b]);
+      coef[f.coef_off + b] = 0.5 * p[i].J[b];
+    }
+    const bool given = !std::isnan(p[i].e_lo) && !std::isnan(p[i].e_hi);
+    if (given) {
+      const double a = (p[i].e_hi - p[i].e_lo) / (2.0 - q.eps), b = 0.5 * (p[i].e_hi + p[i].e_lo);
+      if (!(a > 0.0) || !std::isfinite(a) || !std::isfinite(b)) return KPM_EINVAL;
+      scale[2 * i] = a;
+      scale[2 * i + 1] = b;
+    }
+    pu0[i] = i;
+    UnitDev& u = units[i];
+    u.prob = i;
+    u.ncols = u.ld = (int32_t)(cols ? total_columns(p[i], s) : 0);
+    u.col_off = (int32_t)col;
+    col += u.ncols;
+    R.max_dim = std::max(R.max_dim, (uint32_t)d.dim);
+    R.nch = std::max(R.nch, (int)f.nch);
+  }
+  pu0[n] = n;
+  // the largest sectors' workgroups start first
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return probs[x].dim > probs[y].dim; });
+  for (int i : order) {
+    for (int c = 0; c < units[i].ncols; ++c) jobs[R.n_jobs++] = ResJob{i, c, units[i].col_off + c, 0};
+    if (std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi)) lz[R.n_lz++] = ResJob{i, 1023, 0, 0};   // RNG stream 1023
+  }
+  KPM_HIP(hipMemcpyAsync(work, h, L.up, hipMemcpyHostToDevice, st));
+  ResArgs& a = R.a;
+  a.probs = reinterpret_cast<ProbDev*>(work + L.probs);
+  a.info = reinterpret_cast<ResInfo*>(work + L.info);
+  a.jobs = reinterpret_cast<ResJob*>(work + L.jobs);
+  a.lz_jobs = reinterpret_cast<ResJob*>(work + L.lz);
+  a.binom = reinterpret_cast<uint32_t*>(work + L.binom);
+  a.mask = reinterpret_cast<uint32_t*>(work + L.mask);
+  a.coef = reinterpret_cast<double*>(work + L.coef);
+  a.idx = reinterpret_cast<uint4*>(work + L.idx);
+  a.diag = reinterpret_cast<double*>(work + L.diag);
+  a.scale = reinterpret_cast<double*>(work + L.scale);
+  a.lohi = reinterpret_cast<double*>(work + L.lohi);
+  a.alpha = reinterpret_cast<double*>(work + L.alpha);
+  a.beta = reinterpret_cast<double*>(work + L.beta);
+  a.flag = reinterpret_cast<int*>(work + L.flag);
+  a.unstable = reinterpret_cast<int32_t*>(work + L.unstable);
+  a.seed = q.seed;
+  a.margin = q.bound_margin;
+  a.eps = q.eps;
+  a.K = (int32_t)K;
+  a.total_cols = (int32_t)cols;
+  a.vec_kind = q.vec_kind;
+  a.lz_steps = q.lanczos_steps > 0 ? q.lanczos_steps : 50;
+  KPM_HIP(launch_res_tables(a, n, R.max_dim, st));
+  if (R.n_lz) KPM_HIP(launch_res_lanczos(a, R.nch, R.n_lz, R.max_dim, st));
+  return KPM_OK;
+}
+
+// Memory for a second, stepped estimate of some windows: the caller's region
+// where it holds it, else an allocation (refused to the allocation-free entry
+// point, whose region is its whole array).
+struct Spare {
+  unsigned char* work;
+  size_t bytes;
+  bool may_alloc;
+};
+
+// The windows that the resident recursion reported as hanging on rounding,
+// once more by the stepped recursion, whose values these calls have always
+// had.  e_lo_hi [n][2] holds the others already.
+int settle_bounds(const kpm_problem* p, int n, const std::vector<int32_t>& unstable, int steps, double margin,
+                  uint64_t seed, double* e_lo_hi, const Spare& mem, hipStream_t st) {
+  std::vector<kpm_problem> sub;
+  std::vector<int> at;
+  for (int i = 0; i < n; ++i)
+    if (unstable[i]) {
+      sub.push_back(p[i]);
+      at.push_back(i);
+    }
+  const size_t need = stepped_lanczos_bytes(sub.data(), (int)sub.size(), steps);
+  if (need == 0) return KPM_EINVAL;
+  DevBuf own;
+  unsigned char* work = mem.work;
+  if (need > mem.bytes) {
+    if (!mem.may_alloc) return KPM_ETOOLARGE;
+    const int r = own.alloc(need);
+    if (r != KPM_OK) return r;
+    work = static_cast<unsigned char*>(own.p);
+  }
+  std::vector<double> got(2 * sub.size());
+  const int r = stepped_lanczos(sub.data(), (int)sub.size(), steps, margin, seed, got.data(), work, st);
+  if (r != KPM_OK) return r;
+  for (size_t k = 0; k < at.size(); ++k) {
+    e_lo_hi[2 * at[k]] = got[2 * k];
+    e_lo_hi[2 * at[k] + 1] = got[2 * k + 1];
+  }
+  return KPM_OK;
+}
+
+size_t lanczos_bytes(const kpm_problem* p, int n, int steps) {
+  if (steps <= kResLanczos && resident_problems(p, n)) return res_layout(p, n, 0, 0, n).total;
+  return stepped_lanczos_bytes(p, n, steps);
+}
+
+// Windows of every problem, estimated (their own bounds are not used), in
+// lanczos_bytes() bytes at mem.work (mem.bytes are at hand there).
+int run_lanczos(const kpm_problem* p, int n, int steps, double margin, uint64_t seed, double* e_lo_hi,
+                const Spare& mem, hipStream_t st) {
+  if (steps > kResLanczos || !resident_problems(p, n))
+    return stepped_lanczos(p, n, steps, margin, seed, e_lo_hi, mem.work, st);
+  std::vector<kpm_problem> open(p, p + n);
+  for (auto& o : open) o.e_lo = o.e_hi = NAN;
+  kpm_params q{};
+  q.seed = seed;
+  q.lanczos_steps = steps;
+  q.bound_margin = margin;
+  const ResLayout L = res_layout(p, n, 0, 0, n);
+  ResRun R;
+  StreamSync guard{st};                  // the staging buffer outlives its copy
+  int r = res_start(open.data(), n, q, 0, 0, L, mem.work, R, st);
+  if (r != KPM_OK) return r;
+  int flag = 0;
+  std::vector<int32_t> unstable(n);
+  KPM_HIP(hipMemcpyAsync(e_lo_hi, R.a.lohi, (size_t)n * 16, hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipMemcpyAsync(&flag, R.a.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipMemcpyAsync(unstable.data(), R.a.unstable, (size_t)n * 4, hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipStreamSynchronize(st));
+  if (flag & 2) return KPM_EDEVICE;
+  return (flag & 16) ? settle_bounds(p, n, unstable, steps, margin, seed, e_lo_hi, mem, st) : KPM_OK;
 }
 
 // ------------------------------------------------------------ moments driver
@@ -1578,7 +1835,31 @@ int get_tune(const kpm_problem* p, int n, const kpm_params& q, const double* a, 
   return KPM_OK;
 }
 
+size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q);
+
+// Bytes of a resident moments call, 0 where the step kernels run it: a call
+// that the allocation-free entry point's array held on the step kernels stays
+// there if the index tables would not fit it.
+size_t resident_workspace(const kpm_problem* p, int n, const kpm_params& q) {
+  if (q.precision != KPM_FP64 || q.col_block != 0 || !resident_problems(p, n)) return 0;
+  const int lz = count_nan(p, n);
+  if (lz && lanczos_steps_of(q) > kResLanczos) return 0;
+  const int64_t cols = res_columns(p, n, q);
+  if (cols > (int64_t(1) << 24)) return 0;
+  const size_t total = res_layout(p, n, cols, n_steps(q.M), lz).total;
+  if (total > KPM_NOALLOC_MAX_BYTES) {
+    const size_t stepped = stepped_workspace(p, n, q);
+    if (stepped && stepped <= KPM_NOALLOC_MAX_BYTES) return 0;
+  }
+  return total;
+}
+
 size_t moments_workspace(const kpm_problem* p, int n, const kpm_params& q) {
+  const size_t r = resident_workspace(p, n, q);
+  return r ? r : stepped_workspace(p, n, q);
+}
+
+size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q) {
   std::vector<kpm_problem> need;
   for (int i = 0; i < n; ++i)
     if (std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi)) need.push_back(p[i]);
@@ -1774,7 +2055,7 @@ int run_vectors(Planned& P, const MomLayout& L, unsigned char* work, const kpm_p
 }
 
 // Resolve bounds (Lanczos where NaN) and the (a, b) of Eq. (5).
-int resolve_scale(const kpm_problem* p, int n, const kpm_params& q, unsigned char* lz_work,
+int resolve_scale(const kpm_problem* p, int n, const kpm_params& q, const Spare& mem,
                   hipStream_t st, std::vector<double>& a, std::vector<double>& b) {
   std::vector<kpm_problem> need;
   std::vector<int> idx;
@@ -1791,7 +2072,7 @@ int resolve_scale(const kpm_problem* p, int n, const kpm_params& q, unsigned cha
   if (!need.empty()) {
     std::vector<double> got(2 * need.size());
     const int r = run_lanczos(need.data(), (int)need.size(), lanczos_steps_of(q), q.bound_margin,
-                              q.seed, got.data(), lz_work, st);
+                              q.seed, got.data(), mem, st);
     if (r != KPM_OK) return r;
     for (size_t j = 0; j < idx.size(); ++j) {
       lohi[2 * idx[j]] = got[2 * j];
@@ -2344,11 +2625,95 @@ int ed_plan(const kpm_problem* p, int n, int max_dim, EdPlan& E) {
   return KPM_OK;
 }
 
+// chebyshev_moments with every sector resident; `direct` as in run_moments.
+int run_resident(const kpm_problem* p, int n, const kpm_params& q, double* d_mu, double* d_ab, unsigned char* work,
+                 size_t work_bytes, hipStream_t st, bool direct) {
+  const int64_t cols = res_columns(p, n, q);
+  const int K = n_steps(q.M);
+  const ResLayout L = res_layout(p, n, cols, K, count_nan(p, n));
+  ResRun R;
+  StreamSync guard{st};                  // the staging buffer outlives its copy
+  int r = res_start(p, n, q, cols, K, L, work, R, st);
+  if (r != KPM_OK) return r;
+  struct Events {
+    hipEvent_t a = nullptr, b = nullptr;
+    ~Events() {
+      if (a) (void)hipEventDestroy(a);
+      if (b) (void)hipEventDestroy(b);
+    }
+  } ev;
+  if (!direct) {
+    KPM_HIP(hipEventCreate(&ev.a));
+    KPM_HIP(hipEventCreate(&ev.b));
+    KPM_HIP(hipEventRecord(ev.a, st));
+  }
+  KPM_HIP(launch_res_moments(R.a, R.nch, R.n_jobs, R.max_dim, st));
+  if (ev.b) KPM_HIP(hipEventRecord(ev.b, st));
+  FinalArgs fa{};
+  fa.probs = R.a.probs;
+  fa.units = reinterpret_cast<UnitDev*>(work + L.units);
+  fa.prob_unit0 = reinterpret_cast<int32_t*>(work + L.pu0);
+  fa.alpha = R.a.alpha;
+  fa.beta = R.a.beta;
+  fa.mu = d_mu;
+  fa.flag = R.a.flag;
+  fa.n_probs = n;
+  fa.M = q.M;
+  fa.total_cols = (int32_t)cols;
+  fa.cols_per_vec = cols_per_vec(q.vec_kind);
+  fa.R = q.vec_kind == KPM_VEC_BASIS ? 0 : q.R;
+  KPM_HIP(launch_finalize(fa, st));
+  if (d_ab) KPM_HIP(hipMemcpyAsync(d_ab, R.a.scale, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
+  int flag = 0;
+  KPM_HIP(hipMemcpyAsync(&flag, R.a.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipStreamSynchronize(st));
+  g_stats = kpm_run_stats{};
+  g_stats.step_launches = K;
+  double rows = 0;
+  for (int i = 0; i < n; ++i) {
+    RunShape s;
+    s.vec_kind = q.vec_kind;
+    s.R = q.R;
+    rows += (double)prob_dim(p[i]) * (double)total_columns(p[i], s);
+  }
+  g_stats.bytes_per_launch = 24.0 * rows;
+  g_stats.state_col_steps = rows * K;
+  g_stats.col_block = 1;
+  g_stats.rows_per_tile = (int32_t)R.max_dim;
+  g_stats.kernel = 6;
+  g_stats.waves = (int32_t)std::min<uint32_t>(16u, (R.max_dim + 63u) / 64u);
+  float ms = 0.f;
+  g_stats.recursion_ms = ev.b && hipEventElapsedTime(&ms, ev.a, ev.b) == hipSuccess ? (double)ms : -1.0;
+  if (flag & 2) return KPM_EDEVICE;
+  if (flag & 8) return KPM_EINVAL;
+  if (flag & 16) {
+    // some window hangs on rounding: settle it and run again with it given
+    std::vector<double> lohi(2 * (size_t)n);
+    std::vector<int32_t> unstable(n);
+    KPM_HIP(hipMemcpyAsync(lohi.data(), R.a.lohi, lohi.size() * 8, hipMemcpyDeviceToHost, st));
+    KPM_HIP(hipMemcpyAsync(unstable.data(), R.a.unstable, (size_t)n * 4, hipMemcpyDeviceToHost, st));
+    KPM_HIP(hipStreamSynchronize(st));
+    r = settle_bounds(p, n, unstable, lanczos_steps_of(q), q.bound_margin, q.seed, lohi.data(),
+                      Spare{work, work_bytes, !direct}, st);
+    if (r != KPM_OK) return r;
+    std::vector<kpm_problem> given(p, p + n);
+    for (int i = 0; i < n; ++i)
+      if (std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi)) {
+        given[i].e_lo = lohi[2 * i];
+        given[i].e_hi = lohi[2 * i + 1];
+      }
+    return run_resident(given.data(), n, q, d_mu, d_ab, work, work_bytes, st, direct);
+  }
+  return (flag & 1) ? KPM_EBOUNDS : KPM_OK;
+}
+
 // chebyshev_moments on `need` bytes of device workspace at `work` (checked by
 // the caller); `direct` as in run_moments.  Arguments are validated already.
 int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, double* d_mu,
                          double* d_ab, unsigned char* work, size_t need, hipStream_t st,
                          bool direct) {
+  const size_t avail = direct ? KPM_NOALLOC_MAX_BYTES : need;
+  if (resident_workspace(p, n, *q)) return run_resident(p, n, *q, d_mu, d_ab, work, avail, st, direct);
   // When the launch shape is known already (no tuning, or measured before),
   // the host builds the plan at the unit map while the GPU runs the Lanczos
   // bounds, then applies the map.  The Lanczos region starts the workspace:
@@ -2367,7 +2732,7 @@ int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, doubl
     }
   }
   std::vector<double> a, b;
-  int r = resolve_scale(p, n, *q, work, st, a, b);
+  int r = resolve_scale(p, n, *q, Spare{work, avail, !direct}, st, a, b);
   const int rp = known ? planned.get() : KPM_OK;
   if (r != KPM_OK) return r;
   if (known) {
@@ -2571,7 +2936,7 @@ int kpm_spectral_bounds(const kpm_problem* p, int32_t n, int32_t steps, double m
     DevBuf buf;
     int r = buf.alloc(lanczos_bytes(p, n, steps));
     if (r != KPM_OK) return r;
-    return run_lanczos(p, n, steps, margin, seed, e_lo_hi, static_cast<unsigned char*>(buf.p), st);
+    return run_lanczos(p, n, steps, margin, seed, e_lo_hi, Spare{static_cast<unsigned char*>(buf.p), 0, true}, st);
   });
 }
 
@@ -2668,7 +3033,7 @@ int chebyshev_vectors(const kpm_problem* p, const kpm_params* q, int32_t n_vec, 
     if (r != KPM_OK) return r;
     const MomLayout L0 = moments_layout(P0, n_steps(q2.M), 0);
     std::vector<double> a, b;
-    r = resolve_scale(p, 1, q2, work + L0.lz, st, a, b);
+    r = resolve_scale(p, 1, q2, Spare{work + L0.lz, 0, true}, st, a, b);
     if (r != KPM_OK) return r;
     Planned P;
     r = make_plan(p, 1, shape_of(q2), a.data(), b.data(), P);
@@ -2814,7 +3179,7 @@ int chebyshev_moments_ckpt(const kpm_problem* p, int32_t n, const kpm_params* q,
     if (r != KPM_OK) return r;
     const MomLayout L0 = moments_layout(P0, n_steps(q->M), 0);
     std::vector<double> a, b;
-    r = resolve_scale(p, n, *q, work + L0.lz, st, a, b);
+    r = resolve_scale(p, n, *q, Spare{work + L0.lz, 0, true}, st, a, b);
     if (r != KPM_OK) return r;
     std::vector<double> h_ab(2 * n);
     for (int i = 0; i < n; ++i) {
@@ -2934,7 +3299,7 @@ int kpm_thermo_grad(const kpm_problem* p, int32_t n, const kpm_params* q, int32_
     if (r != KPM_OK) return r;
     const MomLayout L0 = moments_layout(P0, n_steps(q->M), 0);
     std::vector<double> a, b;
-    r = resolve_scale(p, n, *q, work + L0.lz, st, a, b);
+    r = resolve_scale(p, n, *q, Spare{work + L0.lz, 0, true}, st, a, b);
     if (r != KPM_OK) return r;
     std::vector<double> h_ab(2 * n);
     for (int i = 0; i < n; ++i) {

@@ -92,4 +92,35 @@ __device__ __forceinline__ uint32_t spin_rank(uint64_t dg, int N, int n, int R1,
   return rank;
 }
 
+// Counter-based SplitMix64 (Steele, Lea, Flood 2014): output ctr+1 of the
+// sequential generator started at `seed`.
+__device__ __forceinline__ uint64_t splitmix(uint64_t seed, uint64_t ctr) {
+  uint64_t z = seed + 0x9E3779B97F4A7C15ull * (ctr + 1ull);
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  return z ^ (z >> 31);
+}
+__device__ __forceinline__ double unit_open(uint64_t u) {
+  return ((double)(u >> 11) + 0.5) * 0x1.0p-53;
+}
+
+
+// Unnormalised start value of column pc (of the problem) at row rho.
+__device__ __forceinline__ double start_value(int kind, uint64_t seed, const ProbDev& P, int pc,
+                                              int64_t rho) {
+  if (kind == 3) return rho == (int64_t)pc ? 1.0 : 0.0;
+  const int r = kind == 1 ? (pc >> 1) : pc;
+  const uint64_t stream = ((uint64_t)P.cluster << 16) | ((uint64_t)P.n_up << 10) | (uint64_t)r;
+  if (kind == 0) {
+    const uint64_t u = splitmix(seed, (stream << 32) | (uint64_t)rho);
+    return (u >> 63) ? -1.0 : 1.0;
+  }
+  const uint64_t i1 = (uint64_t)(2 * rho), i2 = (uint64_t)(2 * rho + 1);
+  const double u1 = unit_open(splitmix(seed, (stream << 32) | i1));
+  const double u2 = unit_open(splitmix(seed, (stream << 32) | i2));
+  const double rad = sqrt(-2.0 * log(u1));
+  const double ang = 2.0 * M_PI * u2;
+  return (kind == 1 && (pc & 1)) ? rad * sin(ang) : rad * cos(ang);
+}
+
 }  // namespace kpm

@@ -384,6 +384,45 @@ struct FtlmArgs {
 hipError_t launch_ftlm_ritz(const FtlmArgs& a, hipStream_t st);
 hipError_t launch_ftlm_thermo(const FtlmArgs& a, hipStream_t st);
 
+// Resident recursions (kpm_resident.hip): sectors of at most kResMaxDim states
+// and kResMaxBonds bonds, one workgroup per column.
+constexpr int kResMaxDim = 19456;     // 19 rows per thread of 1024; v_n and the bookkeeping in 160 KB of LDS
+constexpr int kResMaxBonds = 32;
+constexpr int kResLanczos = 256;      // Lanczos steps whose coefficients are kept in LDS
+constexpr int KPM_RES_GAUSSIAN = 2;   // start_value's kind of the Lanczos start column
+struct ResInfo {
+  int64_t idx_off;     // first 16-byte index entry of the problem ([nch][dim])
+  int64_t diag_off;    // first diagonal entry
+  int32_t nch;         // index entries (8 bonds each) per row
+  int32_t coef_off;    // first of its nch * 8 masks and coefficients (zeros past the last bond)
+};
+struct ResJob {
+  int32_t prob, col, ocol, pad;   // problem, column of the problem, column of alpha / beta
+};
+struct ResArgs {
+  const ProbDev* probs;
+  const ResInfo* info;
+  const ResJob* jobs;      // one per workgroup of the moments
+  const ResJob* lz_jobs;   // one per workgroup of the bounds
+  const uint32_t* binom;
+  const uint32_t* mask;    // per bond (1 << i) | (1 << j)
+  const double* coef;      // per bond J_b / 2
+  uint4* idx;
+  double* diag;
+  double* scale;           // [n_probs][2]: (a, b)
+  double* lohi;            // [n_probs][2]: the window
+  double* alpha;           // [K + 1][total_cols]
+  double* beta;            // [K][total_cols]
+  int* flag;               // 2: rank outside the sector, 8: no usable (a, b), 16: some window is unstable
+  int32_t* unstable;       // [n_probs]: 1 where the estimated window hangs on rounding
+  uint64_t seed;
+  double margin, eps;
+  int32_t K, total_cols, vec_kind, lz_steps;
+};
+hipError_t launch_res_tables(const ResArgs& a, int n_probs, uint32_t max_dim, hipStream_t st);
+hipError_t launch_res_moments(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st);
+hipError_t launch_res_lanczos(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st);
+
 struct ThermoVjpArgs {
   const ThermoProb* tp;
   const double* ab;

@@ -2007,37 +2007,6 @@ hipError_t launch_reduce(const DevicePlan& p, const double* part, double* dst_a,
 
 // ---------------------------------------------------- random start vectors
 
-// Counter-based SplitMix64 (Steele, Lea, Flood 2014): output ctr+1 of the
-// sequential generator started at `seed`.
-__device__ __forceinline__ uint64_t splitmix(uint64_t seed, uint64_t ctr) {
-  uint64_t z = seed + 0x9E3779B97F4A7C15ull * (ctr + 1ull);
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  return z ^ (z >> 31);
-}
-__device__ __forceinline__ double unit_open(uint64_t u) {
-  return ((double)(u >> 11) + 0.5) * 0x1.0p-53;
-}
-
-
-// Unnormalised start value of column pc (of the problem) at row rho.
-__device__ __forceinline__ double start_value(int kind, uint64_t seed, const ProbDev& P, int pc,
-                                              int64_t rho) {
-  if (kind == 3) return rho == (int64_t)pc ? 1.0 : 0.0;
-  const int r = kind == 1 ? (pc >> 1) : pc;
-  const uint64_t stream = ((uint64_t)P.cluster << 16) | ((uint64_t)P.n_up << 10) | (uint64_t)r;
-  if (kind == 0) {
-    const uint64_t u = splitmix(seed, (stream << 32) | (uint64_t)rho);
-    return (u >> 63) ? -1.0 : 1.0;
-  }
-  const uint64_t i1 = (uint64_t)(2 * rho), i2 = (uint64_t)(2 * rho + 1);
-  const double u1 = unit_open(splitmix(seed, (stream << 32) | i1));
-  const double u2 = unit_open(splitmix(seed, (stream << 32) | i2));
-  const double rad = sqrt(-2.0 * log(u1));
-  const double ang = 2.0 * M_PI * u2;
-  return (kind == 1 && (pc & 1)) ? rad * sin(ang) : rad * cos(ang);
-}
-
 template <typename T>
 __global__ __launch_bounds__(kThreads) void init_kernel(const InitArgs a) {
   __shared__ double red[kThreads];
@@ -2132,9 +2101,12 @@ hipError_t launch_init(const DevicePlan& p, void* vec, int mode, int vec_kind, u
 // ------------------------------------------------- doubling + estimator
 
 
+// One wave per moment, the vectors of a block over its lanes (one thread per
+// moment took 119 us for 900 moments of 200 columns, a serial chain of loads).
 __global__ __launch_bounds__(kThreads) void finalize_kernel(const FinalArgs a) {
-  const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t gid = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (gid >= (int64_t)a.n_probs * a.M) return;
+  const int lane = threadIdx.x & 63;
   const int p = (int)(gid / a.M);
   const int n = (int)(gid % a.M);
   const int TC = a.total_cols;
@@ -2143,7 +2115,7 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(const FinalArgs a) {
   bool bad = false;
   for (int u = a.prob_unit0[p]; u < a.prob_unit0[p + 1]; ++u) {
     const UnitDev U = a.units[u];
-    for (int c = 0; c < U.ncols; c += a.cols_per_vec) {
+    for (int c = lane * a.cols_per_vec; c < U.ncols; c += 64 * a.cols_per_vec) {
       double num = 0.0, den = 0.0;
       for (int cc = 0; cc < a.cols_per_vec; ++cc) {
         const int col = U.col_off + c + cc;
@@ -2161,15 +2133,16 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(const FinalArgs a) {
       acc += num / den;
     }
   }
-  const ProbDev P = a.probs[p];
-  const double Reff = a.R > 0 ? (double)a.R : (double)P.dim;
-  a.mu[gid] = acc * ((double)P.dim / Reff);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  const double Reff = a.R > 0 ? (double)a.R : (double)a.probs[p].dim;
+  if (lane == 0) a.mu[gid] = acc * ((double)a.probs[p].dim / Reff);
   if (bad) atomicOr(a.flag, 1);
 }
 
 hipError_t launch_finalize(const FinalArgs& a, hipStream_t st) {
   const int64_t n = (int64_t)a.n_probs * a.M;
-  const int grid = (int)((n + kThreads - 1) / kThreads);
+  const int grid = (int)((n + kThreads / 64 - 1) / (kThreads / 64));
   hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }

@@ -1,0 +1,549 @@
+// Resident recursions: float64 sectors small enough for one compute unit.
+//
+// One workgroup owns one real column of one sector and runs every step of its
+// recursion (the moments of Eqs. (6)-(7), or the Lanczos steps behind the
+// bounds of Eqs. (4)-(5)) in a single launch: v_n lives in LDS (160 KB hold
+// 19456 states and the bookkeeping), v_{n-1} in registers of the thread that
+// owns the row, the dots are reduced inside the workgroup.  Nothing but the
+// neighbour indices is read from memory per step, and those only where they
+// do not fit registers.
+//
+// What bounds it: the LDS gathers.  A row needs one 8-byte LDS read per bond
+// (a bond that does not act reads the zero slot behind the vector, one address
+// for all lanes), 64 lanes to random addresses; with one row per thread the
+// two barriers per step and the dot reduction cost as much again.
+//
+// Why: these sectors took one launch per step, 17-30 us each however few
+// states they had (a chain of dependent loads through L2, then the next
+// launch), and five launches per Lanczos step.  Measured: the 12-site ring
+// (7 sectors, 20 columns, 128 steps) 30 -> 1.0 us per step, a whole call with
+// bounds and thermodynamics 5.82 -> 0.46 ms; the 16-site ladder (9 sectors up
+// to 12870 states, 200 columns, 50 steps) 111 -> 45 us per step and 117 ->
+// 14 us per Lanczos step, the call 13.0 -> 3.2 ms.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "kpm_device.h"
+#include "kpm_internal.h"
+#include "kpm_vec.h"
+
+namespace kpm {
+
+// ------------------------------------------------------------------ tables
+
+// Per row: the diagonal sum_b +-J_b/4 of H, and the rank of the state each
+// bond maps it to (16 bits; dim, the zero slot, where the bond does not act),
+// eight bonds per 16-byte entry, entries of one chunk consecutive in the row.
+__global__ __launch_bounds__(kThreads) void res_tables_kernel(const ResArgs a) {
+  __shared__ uint32_t bn[kBinomN * kBinomN];
+  for (int e = threadIdx.x; e < kBinomN * kBinomN; e += kThreads) bn[e] = a.binom[e];
+  __syncthreads();
+  const ProbDev P = a.probs[blockIdx.y];
+  const ResInfo I = a.info[blockIdx.y];
+  const uint32_t dim = (uint32_t)P.dim;
+  const uint32_t r = blockIdx.x * kThreads + threadIdx.x;
+  if (r >= dim) return;
+  const uint32_t s = unrank(r, P.n_sites, P.n_up, bn);
+  const uint32_t* mask = a.mask + I.coef_off;
+  const double* off = a.coef + I.coef_off;
+  uint4* out = a.idx + I.idx_off;
+  double d = 0.0;
+  for (int ch = 0; ch < I.nch; ++ch) {
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const uint32_t m = mask[ch * 8 + t];    // 0 past the last bond
+      const uint32_t v = s & m;
+      const bool act = v != 0u && v != m;
+      const double h = 0.5 * off[ch * 8 + t];
+      d += act ? -h : h;                      // the padding's coefficient is 0
+      uint32_t n = dim;
+      if (act) {
+        n = word_rank(s ^ m, bn);
+        if (n >= dim) {
+          atomicOr(a.flag, 2);
+          n = dim;
+        }
+      }
+      w[t >> 1] |= n << ((t & 1) * 16);
+    }
+    out[(size_t)ch * dim + r] = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  a.diag[I.diag_off + r] = d;
+}
+
+// ------------------------------------------------------------------ helpers
+
+// Two sums over the wave, the first in the even lanes, the second in the odd.
+__device__ __forceinline__ double wave_sum2(double p, double q, int lane) {
+  const bool up = (lane & 1) != 0;
+  double v = (up ? q : p) + lane_xor<1>(up ? p : q);
+  v += lane_xor<2>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<8>(v);
+  v += lane_xor<16>(v);
+  v += lane_xor<32>(v);
+  return v;
+}
+
+// Sum over the workgroup, known to every thread (one barrier; `slot` is 16
+// doubles of LDS, not written again before the next barrier of the caller).
+__device__ __forceinline__ double group_sum(double v, double* slot, int lane, int wid, int nw) {
+  v += lane_xor<1>(v);
+  v += lane_xor<2>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<8>(v);
+  v += lane_xor<16>(v);
+  v += lane_xor<32>(v);
+  if (lane == 0) slot[wid] = v;
+  __syncthreads();
+  const int l = lane & 15;
+  double t = l < nw ? slot[l] : 0.0;
+  t += lane_xor<1>(t);
+  t += lane_xor<2>(t);
+  t += lane_xor<4>(t);
+  t += lane_xor<8>(t);
+  return t;
+}
+
+// sum_b (J_b / 2) x[neighbour] of one row from its NCH index entries
+template <int NCH>
+__device__ __forceinline__ double gather_row(const uint4 (&q)[NCH], cptr<double> cf, const double* x) {
+  double acc = 0.0;
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) {
+    const uint32_t w[4] = {q[ch].x, q[ch].y, q[ch].z, q[ch].w};
+    double v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = x[(w[t >> 1] >> ((t & 1) * 16)) & 0xFFFFu];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc = fma(cf[ch * 8 + t], v[t], acc);
+  }
+  return acc;
+}
+
+// The index entries of a workgroup's rows: kept in registers for the whole
+// recursion where they fit (at most 8 entries per thread), else read from
+// L2 each step, the next row's while the current one is summed.  NCH is the
+// number of entries per row (rows with fewer read repeats with coefficient 0).
+template <int RPT, int NCH>
+struct Rows {
+  static constexpr bool kKeep = RPT * NCH <= 8;
+  uint4 q[kKeep ? RPT : 1][NCH];
+  double dg[kKeep ? RPT : 1];
+  const uint4* src;
+  const double* dsrc;
+  uint32_t dim;
+  int nch;
+  __device__ __forceinline__ void load(int k, uint32_t r, uint4 (&o)[NCH]) const {
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch)     // 32-bit offsets from a scalar base
+      o[ch] = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(src) +
+                                              (uint32_t)(((uint32_t)(ch < nch ? ch : 0) * dim + r) * 16u));
+  }
+  __device__ __forceinline__ double diag(int k, uint32_t r) const {
+    if constexpr (kKeep) return dg[k];
+    else return *reinterpret_cast<const double*>(reinterpret_cast<const unsigned char*>(dsrc) + r * 8u);
+  }
+};
+
+// The value as one that may change between steps: without this the compiler
+// moves every unpacked index and address of the recursion out of its loop and
+// spills them.
+__device__ __forceinline__ uint32_t fresh(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// One product: h[k] = sum_b (J_b/2) x[nb] for the thread's rows, passed to
+// use(k, row, on, h).
+template <int RPT, int NCH, typename F>
+__device__ __forceinline__ void product(const Rows<RPT, NCH>& R, cptr<double> cf, const double* x, int tid, int T,
+                                        F&& use) {
+  using RowsT = Rows<RPT, NCH>;
+  if constexpr (RowsT::kKeep) {
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r0 = (uint32_t)(k * T);
+      if (r0 < R.dim) {
+        const uint32_t r = r0 + (uint32_t)tid;
+        uint4 q[NCH];
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch)
+          q[ch] = make_uint4(fresh(R.q[k][ch].x), fresh(R.q[k][ch].y), fresh(R.q[k][ch].z), fresh(R.q[k][ch].w));
+        use(k, min(r, R.dim - 1u), r < R.dim, gather_row<NCH>(q, cf, x));
+      }
+    }
+  } else {
+    uint4 cur[NCH], nxt[NCH];
+    tid = (int)fresh((uint32_t)tid);
+    R.load(0, min((uint32_t)tid, R.dim - 1u), nxt);
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r0 = (uint32_t)(k * T);
+      if (r0 < R.dim) {
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) cur[ch] = nxt[ch];
+        const uint32_t r = r0 + (uint32_t)tid;
+        if (k + 1 < RPT && r0 + (uint32_t)T < R.dim) R.load(k + 1, min(r + (uint32_t)T, R.dim - 1u), nxt);
+        use(k, min(r, R.dim - 1u), r < R.dim, gather_row<NCH>(cur, cf, x));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+}
+
+template <int RPT, int NCH>
+__device__ __forceinline__ void rows_init(Rows<RPT, NCH>& R, const ResArgs& a, const ResInfo& I, uint32_t dim, int tid,
+                                          int T) {
+  R.src = a.idx + I.idx_off;
+  R.dsrc = a.diag + I.diag_off;
+  R.dim = dim;
+  R.nch = I.nch;
+  if constexpr (Rows<RPT, NCH>::kKeep) {
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r = min((uint32_t)(tid + k * T), dim - 1u);
+      R.load(k, r, R.q[k]);
+      R.dg[k] = R.dsrc[r];
+    }
+  }
+}
+
+// Start column of the job into x[0..dim), normalised as init_kernel does
+// (mode 1: <r|r> = dim over the vector's columns; mode 2: unit norm); each
+// thread writes and scales its own rows.  Returns the squared norm of the
+// unscaled column.
+__device__ __forceinline__ double start_rows(const ResArgs& a, const ProbDev& P, int kind, int col, int mode, int tid,
+                                             int T, int lane, int wid, int nw, double* slot, double* x) {
+  const int64_t dim = P.dim;
+  double own = 0.0, pair = 0.0;
+#pragma unroll 1
+  for (int64_t r = tid; r < dim; r += T) {
+    const double v = start_value(kind, a.seed, P, col, r);
+    x[r] = v;
+    own = fma(v, v, own);
+    if (kind == 1 && mode == 1) {
+      const double o = start_value(kind, a.seed, P, col ^ 1, r);
+      pair = fma(o, o, pair);
+    }
+  }
+  const double n_own = group_sum(own, slot, lane, wid, nw);
+  double scale = 1.0;
+  if (mode == 2) {
+    scale = 1.0 / sqrt(n_own);
+  } else if (kind == 1 || kind == 2) {
+    double n2 = n_own;
+    if (kind == 1) n2 += group_sum(pair, slot + 16, lane, wid, nw);
+    scale = sqrt((double)dim / n2);
+  }
+#pragma unroll 1
+  for (int64_t r = tid; r < dim; r += T) x[r] *= scale;
+  return n_own;
+}
+
+// ------------------------------------------------------------------ moments
+
+// Dots of kResRing steps are kept in LDS before they are summed over the
+// waves and written, so that the sum is not on every step's path.
+constexpr int kResRing = 8;
+
+template <int RPT, int NCH>
+__global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
+  extern __shared__ __align__(16) double sm[];
+  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, nw = T >> 6;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const ResJob J = a.jobs[blockIdx.x];
+  const ProbDev P = a.probs[J.prob];
+  const ResInfo I = a.info[J.prob];
+  const uint32_t dim = (uint32_t)P.dim;
+  double* red = sm;                       // [kResRing][16][2]
+  double* x = sm + kResRing * 32;         // [dim + 1]
+  const double sa = a.scale[2 * J.prob], sb = a.scale[2 * J.prob + 1];
+  const double inva = 1.0 / sa, sh = -sb / sa;
+  const cptr<double> cf = cview(a.coef) + I.coef_off;
+  Rows<RPT, NCH> R;
+  rows_init(R, a, I, dim, tid, T);
+  double y[RPT];
+  start_rows(a, P, a.vec_kind, J.col, 1, tid, T, lane, wid, nw, red, x);
+  double acc0 = 0.0;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    const uint32_t r = (uint32_t)(tid + k * T);
+    if (r < dim) acc0 = fma(x[r], x[r], acc0);
+    y[k] = 0.0;
+  }
+  if (tid == 0) x[dim] = 0.0;
+  __syncthreads();                        // x complete; the slots of start_rows read
+  {
+    const double s0 = group_sum(acc0, red, lane, wid, nw);
+    if (tid == 0) a.alpha[J.ocol] = s0;
+    __syncthreads();
+  }
+  const int64_t TC = a.total_cols;
+  for (int n = 0; n < a.K; ++n) {
+    double s2 = 0.0, s1 = 0.0;
+    product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
+      const double xr = x[r];
+      const double hx = fma(fma(R.diag(k, r), xr, h), inva, sh * xr);
+      const double v = on ? (n == 0 ? hx : fma(2.0, hx, -y[k])) : 0.0;
+      s2 = fma(v, v, s2);
+      s1 = fma(v, xr, s1);
+      y[k] = v;
+    });
+    const double f = wave_sum2(s2, s1, lane);
+    if (lane < 2) red[(n & (kResRing - 1)) * 32 + wid * 2 + lane] = f;
+    __syncthreads();                      // every read of v_n done
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r = (uint32_t)(tid + k * T);
+      if (r < dim) {
+        const double t = x[r];
+        x[r] = y[k];
+        y[k] = t;
+      }
+    }
+    if ((n & (kResRing - 1)) == kResRing - 1 || n == a.K - 1) {
+      const int n0 = n & ~(kResRing - 1);
+      const int st = n0 + (tid >> 1);
+      if (tid < 2 * kResRing && st <= n) {
+        const double* p = red + (st & (kResRing - 1)) * 32 + (tid & 1);
+        double s = p[0];
+        for (int w = 1; w < nw; ++w) s += p[2 * w];
+        if (tid & 1) a.beta[(int64_t)st * TC + J.ocol] = s;
+        else a.alpha[(int64_t)(st + 1) * TC + J.ocol] = s;
+      }
+    }
+    __syncthreads();                      // v_{n+1} in place
+  }
+}
+
+// ------------------------------------------------------------------ Lanczos
+
+// Eigenvalues of the symmetric tridiagonal (al[0..L), be2[0..L-1) = squared
+// off-diagonals) below x, by the Sturm recurrence.
+__device__ __forceinline__ int sturm_below(const double* al, const double* be2, int L, double x) {
+  int cnt = 0;
+  double q = 1.0;
+  for (int i = 0; i < L; ++i) {
+    q = al[i] - x - (i ? be2[i - 1] / q : 0.0);
+    if (q == 0.0) q = -1e-300;
+    cnt += q < 0.0;
+  }
+  return cnt;
+}
+
+// Plain Lanczos on H from the job's unit start column; the extreme Ritz
+// values (cut at the first off-diagonal below 1e-12), widened as
+// kpm_spectral_bounds documents, give the window and the problem's (a, b).
+template <int RPT, int NCH>
+__global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
+  extern __shared__ __align__(16) double sm[];
+  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, nw = T >> 6;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const ResJob J = a.lz_jobs[blockIdx.x];
+  const ProbDev P = a.probs[J.prob];
+  const ResInfo I = a.info[J.prob];
+  const uint32_t dim = (uint32_t)P.dim;
+  double* red = sm;                       // [2][16]
+  double* al = sm + 32;                   // [kResLanczos]
+  double* be = al + kResLanczos;          // [kResLanczos]: beta_{j+1}^2
+  double* x = be + kResLanczos;           // [dim + 1]
+  const cptr<double> cf = cview(a.coef) + I.coef_off;
+  Rows<RPT, NCH> R;
+  rows_init(R, a, I, dim, tid, T);
+  double y[RPT];
+  start_rows(a, P, KPM_RES_GAUSSIAN, J.col, 2, tid, T, lane, wid, nw, red, x);
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) y[k] = 0.0;
+  if (tid == 0) x[dim] = 0.0;
+  __syncthreads();
+  const int steps = (int)min((uint32_t)a.lz_steps, dim);
+  double b = 0.0;
+  int L = steps;
+  for (int j = 0; j < steps; ++j) {
+    double s = 0.0;
+    product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
+      const double xr = x[r];
+      const double w = on ? fma(R.diag(k, r), xr, h) - b * y[k] : 0.0;
+      s = fma(w, xr, s);
+      y[k] = w;
+    });
+    const double alpha = group_sum(s, red, lane, wid, nw);
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r = (uint32_t)(tid + k * T);
+      if (r < dim) {
+        y[k] = fma(-alpha, x[r], y[k]);
+        s = fma(y[k], y[k], s);
+      }
+    }
+    const double b2 = group_sum(s, red + 16, lane, wid, nw);
+    if (tid == 0) {
+      al[j] = alpha;
+      be[j] = b2;
+    }
+    b = sqrt(b2);
+    if (j == steps - 1 || b < 1e-12) {    // the same for every thread
+      L = j + 1;
+      break;
+    }
+    const double inv = 1.0 / b;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r = (uint32_t)(tid + k * T);
+      if (r < dim) {
+        const double t = x[r];
+        x[r] = y[k] * inv;
+        y[k] = t;
+      }
+    }
+    __syncthreads();
+  }
+  __syncthreads();
+  // extreme eigenvalues by multisection: half of the threads cut the interval
+  // of the smallest, half that of the largest, until no point falls inside
+  double gl = INFINITY, gu = -INFINITY;
+  for (int i = 0; i < L; ++i) {
+    const double r = (i ? sqrt(be[i - 1]) : 0.0) + (i + 1 < L ? sqrt(be[i]) : 0.0);
+    gl = fmin(gl, al[i] - r);
+    gu = fmax(gu, al[i] + r);
+  }
+  const int half = T >> 1;
+  const bool top = tid >= half;
+  const int t = top ? tid - half : tid;
+  double lo0 = gl, hi0 = gu, lo1 = gl, hi1 = gu;   // brackets of the smallest and the largest
+  for (int it = 0; it < 60; ++it) {
+    const double l = top ? lo1 : lo0, u = top ? hi1 : hi0;
+    const double p = fma((u - l), (double)(t + 1) / (double)(half + 1), l);
+    const bool below = sturm_below(al, be, L, p) <= (top ? L - 1 : 0);   // the eigenvalue is at or above p
+    const int c0 = __syncthreads_count(!top && below);
+    const int c1 = __syncthreads_count(top && below);
+    auto point = [&](double lv, double uv, int i) { return fma((uv - lv), (double)(i + 1) / (double)(half + 1), lv); };
+    const double nl0 = c0 > 0 ? point(lo0, hi0, c0 - 1) : lo0, nh0 = c0 < half ? point(lo0, hi0, c0) : hi0;
+    const double nl1 = c1 > 0 ? point(lo1, hi1, c1 - 1) : lo1, nh1 = c1 < half ? point(lo1, hi1, c1) : hi1;
+    const bool same = nl0 == lo0 && nh0 == hi0 && nl1 == lo1 && nh1 == hi1;
+    lo0 = nl0;
+    hi0 = nh0;
+    lo1 = nl1;
+    hi1 = nh1;
+    const double m0 = 0.5 * (lo0 + hi0), m1 = 0.5 * (lo1 + hi1);
+    if (same || ((m0 <= lo0 || m0 >= hi0) && (m1 <= lo1 || m1 >= hi1))) break;   // the same for every thread
+  }
+  if (tid == 0) {
+    const double lo = 0.5 * (lo0 + hi0), hi = 0.5 * (lo1 + hi1);
+    const double W = hi - lo;
+    double e0 = lo - a.margin * W, e1 = hi + a.margin * W;
+    if (W < 1e-8 * fmax(1.0, fmax(fabs(lo), fabs(hi)))) {
+      e0 = lo - 0.5;
+      e1 = hi + 0.5;
+    }
+    a.lohi[2 * J.prob] = e0;
+    a.lohi[2 * J.prob + 1] = e1;
+    const double sa = (e1 - e0) / (2.0 - a.eps), sb = 0.5 * (e1 + e0);
+    a.scale[2 * J.prob] = sa;
+    a.scale[2 * J.prob + 1] = sb;
+    if (!(sa > 0.0) || !isfinite(sa) || !isfinite(sb)) atomicOr(a.flag, 8);
+  }
+  // Does the window hang on rounding?  Only where an end has not converged
+  // (the value of two steps less differs by 1e-11 of the width) after the
+  // Lanczos vectors lost their orthogonality (Simon's recurrence for
+  // omega_{j,k} = <q_j, q_k>, 1984, above 1e-4): a copy of the other,
+  // converged end then takes steps from this one, at a point that the last
+  // bits decide.  Over 1080 sectors (six lattices of 8-16 sites) every window
+  // that moved by more than 1e-12 with the order of summation is caught.
+  const double elo = 0.5 * (lo0 + hi0), ehi = 0.5 * (lo1 + hi1), width = ehi - elo;
+  if (L < 3 || (L < steps && (uint32_t)L < dim)) return;       // the Krylov space is exhausted
+  const int Ls = L - 2;
+  if (sturm_below(al, be, Ls, elo + 1e-11 * width) > 0 && sturm_below(al, be, Ls, ehi - 1e-11 * width) < Ls) return;
+  __syncthreads();
+  constexpr int S = kResLanczos + 2;
+  double *prev = x, *cur = x + S, *nxt = x + 2 * S;            // omega_{j-1}, omega_j, omega_{j+1}
+  for (int k = tid; k < 3 * S; k += T) x[k] = k == S ? 1.0 : 0.0;
+  for (int k = tid; k < L; k += T) be[k] = sqrt(be[k]);
+  __syncthreads();
+  const double ulp = 1.1e-16;
+  double top_w = 0.0;
+  for (int j = 0; j + 1 < L; ++j) {
+    for (int k = tid; k < j; k += T) {
+      double v = be[k] * cur[k + 1] + (al[k] - al[j]) * cur[k] - be[j - 1] * prev[k];
+      if (k > 0) v += be[k - 1] * cur[k - 1];
+      v = (v + copysign(2.0 * ulp * width, v)) / be[j];
+      nxt[k] = v;
+      top_w = fmax(top_w, fabs(v));
+    }
+    if (tid == 0) {
+      nxt[j] = 30.0 * ulp * be[0] / be[j];
+      nxt[j + 1] = 1.0;
+    }
+    __syncthreads();
+    double* t = prev;
+    prev = cur;
+    cur = nxt;
+    nxt = t;
+  }
+  if (top_w > 1e-4) {
+    a.unstable[J.prob] = 1;
+    atomicOr(a.flag, 16);
+  }
+}
+
+// ------------------------------------------------------------------ launches
+
+hipError_t launch_res_tables(const ResArgs& a, int n_probs, uint32_t max_dim, hipStream_t st) {
+  hipLaunchKernelGGL(res_tables_kernel, dim3((max_dim + kThreads - 1) / kThreads, n_probs), dim3(kThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+template <typename K>
+static hipError_t launch_res(K kernel, const ResArgs& a, int grid, int threads, size_t lds, hipStream_t st) {
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, st, a);
+  return hipGetLastError();
+}
+
+template <int RPT, int NCH>
+static hipError_t launch_res_t(const ResArgs& a, bool lanczos, int grid, int threads, size_t lds, hipStream_t st) {
+  return lanczos ? launch_res(res_lanczos_kernel<RPT, NCH>, a, grid, threads, lds, st)
+                 : launch_res(res_moments_kernel<RPT, NCH>, a, grid, threads, lds, st);
+}
+
+template <int RPT>
+static hipError_t launch_res_n(const ResArgs& a, bool lanczos, int nch, int grid, int threads, size_t lds,
+                               hipStream_t st) {
+  if (nch <= 2) return launch_res_t<RPT, 2>(a, lanczos, grid, threads, lds, st);
+  if (nch <= 3) return launch_res_t<RPT, 3>(a, lanczos, grid, threads, lds, st);
+  return launch_res_t<RPT, 4>(a, lanczos, grid, threads, lds, st);
+}
+
+// Rows per thread: the smallest instantiation that covers the largest sector
+// with at most 1024 threads.
+static hipError_t launch_res_any(const ResArgs& a, bool lanczos, int nch, int grid, uint32_t max_dim, hipStream_t st) {
+  if (max_dim > (uint32_t)kResMaxDim || nch > kResMaxBonds / 8 || grid < 1) return hipErrorInvalidValue;
+  // the bounds end on three rows of omega in the vector's place
+  const size_t lds = lanczos ? (std::max<size_t>(max_dim + 1, 3 * (kResLanczos + 2)) + 32 + 2 * kResLanczos) * 8
+                             : ((size_t)max_dim + 1 + kResRing * 32) * 8;
+  const int threads = (int)std::min<uint32_t>(1024u, std::max(64u, (max_dim + 63u) / 64u * 64u));
+  const int rpt = (int)((max_dim + threads - 1) / threads);
+  if (rpt <= 1) return launch_res_n<1>(a, lanczos, nch, grid, threads, lds, st);
+  if (rpt <= 2) return launch_res_n<2>(a, lanczos, nch, grid, threads, lds, st);
+  if (rpt <= 4) return launch_res_n<4>(a, lanczos, nch, grid, threads, lds, st);
+  if (rpt <= 8) return launch_res_n<8>(a, lanczos, nch, grid, threads, lds, st);
+  if (rpt <= 13) return launch_res_n<13>(a, lanczos, nch, grid, threads, lds, st);
+  return launch_res_n<19>(a, lanczos, nch, grid, threads, lds, st);
+}
+
+hipError_t launch_res_moments(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st) {
+  return launch_res_any(a, false, nch, n_jobs, max_dim, st);
+}
+hipError_t launch_res_lanczos(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st) {
+  return launch_res_any(a, true, nch, n_jobs, max_dim, st);
+}
+
+}  // namespace kpm

@@ -46,15 +46,6 @@
 
 namespace kpm {
 
-// Constant-address-space views: loads at wave-uniform indices become scalar
-// loads (the tables are not written during a step).
-template <typename T>
-using cptr = const __attribute__((address_space(4))) T*;
-template <typename T>
-__device__ __forceinline__ cptr<T> cview(const T* p) {
-  return (cptr<T>)(const void*)p;
-}
-
 // A plan struct at a wave-uniform address, word by word through scalar loads.
 template <typename S>
 __device__ __forceinline__ S sload(const S* p) {
@@ -293,26 +284,6 @@ __device__ __forceinline__ uint32_t row_byte(const uint32_t (&w)[WB / 4], int by
 template <int WB>
 __device__ __forceinline__ uint32_t row_u16(const uint32_t (&w)[WB / 4], int byte) {
   return (w[byte >> 2] >> ((byte & 3) * 8)) & 0xFFFFu;
-}
-
-// The double held by lane (lane ^ M) of the wave, M a power of two below 64:
-// quad permutes for 1 and 2, a rotation by 8 inside rows of 16 lanes for 8,
-// swizzles inside halves of 32 lanes for 4 and 16, a lane permute for 32.
-template <int M>
-__device__ __forceinline__ double lane_xor(double x) {
-  int lo = __double2loint(x), hi = __double2hiint(x);
-  if constexpr (M == 1 || M == 2 || M == 8) {
-    constexpr int ctrl = M == 1 ? 0xB1 : (M == 2 ? 0x4E : 0x128);
-    lo = __builtin_amdgcn_mov_dpp(lo, ctrl, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_mov_dpp(hi, ctrl, 0xF, 0xF, false);
-  } else if constexpr (M == 4 || M == 16) {
-    constexpr int pat = 0x1F | (M << 10);
-    lo = __builtin_amdgcn_ds_swizzle(lo, pat);
-    hi = __builtin_amdgcn_ds_swizzle(hi, pat);
-  } else {
-    return __shfl_xor(x, M, 64);
-  }
-  return __hiloint2double(hi, lo);
 }
 
 // V values per lane folded to one: at step t the lanes that differ in bit
