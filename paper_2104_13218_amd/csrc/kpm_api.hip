@@ -1346,12 +1346,16 @@ bool resident_problems(const kpm_problem* p, int n) {
 }
 
 struct ResLayout {
-  size_t probs, info, jobs, lz, binom, mask, coef, units, pu0, scale, flag, unstable, up, idx, diag, lohi, alpha, beta, total;
+  size_t probs, info, jobs, lz, binom, mask, coef, units, pu0, scale, flag, unstable, rows, up, idx, lohi, alpha, beta,
+      seg, ckpt, wsave, bonds, total;
+  int n_ckpt;   // checkpoints of a gradient call, 0: the whole trajectory
 };
 
-// `cols` columns per problem and K steps of the moments (0: bounds only), the
-// bounds of n_lz problems.
-ResLayout res_layout(const kpm_problem* p, int n, int64_t cols, int64_t K, int n_lz) {
+// `cols` columns of all problems and K steps of the moments (0: bounds only),
+// the bounds of n_lz problems; basis: the complete basis (a problem has as
+// many columns as states, not its share); ckpt_every > 0: a gradient call, with the
+// vectors of the forward pass (every one where the interval is at least K).
+ResLayout res_layout(const kpm_problem* p, int n, int64_t cols, int64_t K, int n_lz, bool basis = false, int ckpt_every = 0) {
   ResLayout L{};
   size_t o = 0;
   auto put = [&](size_t bytes) {
@@ -1359,10 +1363,10 @@ ResLayout res_layout(const kpm_problem* p, int n, int64_t cols, int64_t K, int n
     o = align_up(o + bytes);
     return r;
   };
-  size_t entries = 0, rows = 0;
+  size_t entries = 0, elems = 0;
   for (int i = 0; i < n; ++i) {
     const size_t d = (size_t)prob_dim(p[i]);
-    rows += d;
+    elems += d * (basis ? d : (size_t)(cols / n));
     entries += d * (size_t)std::max(1, (p[i].n_bonds + 7) / 8);
   }
   L.probs = put((size_t)n * sizeof(ProbDev));
@@ -1377,15 +1381,24 @@ ResLayout res_layout(const kpm_problem* p, int n, int64_t cols, int64_t K, int n
   L.scale = put((size_t)n * 16);
   L.flag = put(256);
   L.unstable = put((size_t)n * 4);
+  L.rows = put(ckpt_every ? (size_t)cols * 8 : 0);
   L.up = o;
   L.idx = put(entries * 16);
-  L.diag = put(rows * 8);
   L.lohi = put((size_t)n * 16);
   L.alpha = put((size_t)(cols ? K + 1 : 0) * cols * 8);
   L.beta = put((size_t)K * cols * 8);
   // never less than the two vectors per column that the step kernels keep: a
   // stepped estimate of some windows (settle_bounds) finds room there
-  L.total = std::max(o, align_up(16 * rows * (size_t)(cols / n)));
+  L.total = std::max(o, align_up(16 * elems));
+  if (ckpt_every) {
+    const int64_t C = std::max(2, ckpt_every & ~1);
+    L.n_ckpt = C >= K ? 0 : (int)((K - 1) / C + 1);
+    L.seg = put((size_t)(L.n_ckpt ? std::min(C, K) + 2 : K + 1) * elems * 8);
+    L.ckpt = put((size_t)L.n_ckpt * 2 * elems * 8);
+    L.wsave = put(L.n_ckpt ? 2 * elems * 8 : 0);
+    L.bonds = put((size_t)cols * kResMaxBonds * 8);
+    L.total = std::max(L.total, o);
+  }
   return L;
 }
 
@@ -1414,9 +1427,10 @@ struct ResRun {
 
 // Uploads the tables of the call and runs the index tables' kernel and the
 // bounds of the problems without given ones.  q: eps, seed, lanczos_steps,
-// bound_margin; with cols > 0 also vec_kind, R, M.
+// bound_margin; with cols > 0 also vec_kind, R, M.  `again`: the tables are
+// there from an earlier call with the same arguments, nothing is launched.
 int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, int64_t K, const ResLayout& L,
-              unsigned char* work, ResRun& R, hipStream_t st) {
+              unsigned char* work, ResRun& R, hipStream_t st, int ckpt_every = 0, bool again = false) {
   R.staging.assign(L.up, 0);
   unsigned char* h = R.staging.data();
   ProbDev* probs = reinterpret_cast<ProbDev*>(h + L.probs);
@@ -1434,6 +1448,8 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
   s.vec_kind = q.vec_kind;
   s.R = q.R;
   int64_t entries = 0, rows = 0, col = 0;
+  int32_t bonds = 0;
+  int64_t* row0 = reinterpret_cast<int64_t*>(h + L.rows);   // gradient: rows of the columns before each
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) {
     order[i] = i;
@@ -1442,15 +1458,15 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
     d.n_sites = p[i].n_sites;
     d.n_up = p[i].n_up;
     d.n_bonds = p[i].n_bonds;
+    d.bond_off = bonds;
+    bonds += p[i].n_bonds;
     d.cluster = p[i].cluster;
     d.two_s = 1;
     ResInfo& f = info[i];
     f.nch = std::max(1, (p[i].n_bonds + 7) / 8);
     f.coef_off = i * kResMaxBonds;
     f.idx_off = entries;
-    f.diag_off = rows;
     entries += (int64_t)f.nch * d.dim;
-    rows += d.dim;
     for (int b = 0; b < p[i].n_bonds; ++b) {
       mask[f.coef_off + b] = (1u << p[i].bond_i[b]) | (1u << p[i].bond_j[b]);
       coef[f.coef_off + b] = 0.5 * p[i].J[b];
@@ -1467,6 +1483,7 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
     u.prob = i;
     u.ncols = u.ld = (int32_t)(cols ? total_columns(p[i], s) : 0);
     u.col_off = (int32_t)col;
+    for (int c = 0; ckpt_every && c < u.ncols; ++c, rows += d.dim) row0[col + c] = rows;
     col += u.ncols;
     R.max_dim = std::max(R.max_dim, (uint32_t)d.dim);
     R.nch = std::max(R.nch, (int)f.nch);
@@ -1478,7 +1495,6 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
     for (int c = 0; c < units[i].ncols; ++c) jobs[R.n_jobs++] = ResJob{i, c, units[i].col_off + c, 0};
     if (std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi)) lz[R.n_lz++] = ResJob{i, 1023, 0, 0};   // RNG stream 1023
   }
-  KPM_HIP(hipMemcpyAsync(work, h, L.up, hipMemcpyHostToDevice, st));
   ResArgs& a = R.a;
   a.probs = reinterpret_cast<ProbDev*>(work + L.probs);
   a.info = reinterpret_cast<ResInfo*>(work + L.info);
@@ -1488,7 +1504,6 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
   a.mask = reinterpret_cast<uint32_t*>(work + L.mask);
   a.coef = reinterpret_cast<double*>(work + L.coef);
   a.idx = reinterpret_cast<uint4*>(work + L.idx);
-  a.diag = reinterpret_cast<double*>(work + L.diag);
   a.scale = reinterpret_cast<double*>(work + L.scale);
   a.lohi = reinterpret_cast<double*>(work + L.lohi);
   a.alpha = reinterpret_cast<double*>(work + L.alpha);
@@ -1502,8 +1517,21 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
   a.total_cols = (int32_t)cols;
   a.vec_kind = q.vec_kind;
   a.lz_steps = q.lanczos_steps > 0 ? q.lanczos_steps : 50;
+  if (ckpt_every) {
+    a.col_elems = reinterpret_cast<int64_t*>(work + L.rows);
+    a.seg = reinterpret_cast<double*>(work + L.seg);
+    a.ckpt = L.n_ckpt ? reinterpret_cast<double*>(work + L.ckpt) : nullptr;
+    a.wsave = L.n_ckpt ? reinterpret_cast<double*>(work + L.wsave) : nullptr;
+    a.bond_part = reinterpret_cast<double*>(work + L.bonds);
+    a.ckpt_every = std::max(2, ckpt_every & ~1);
+    a.n_ckpt = L.n_ckpt;
+    a.M = q.M;
+    a.R = q.vec_kind == KPM_VEC_BASIS ? 0 : q.R;
+  }
+  if (again) return KPM_OK;
+  KPM_HIP(hipMemcpyAsync(work, h, L.up, hipMemcpyHostToDevice, st));
   KPM_HIP(launch_res_tables(a, n, R.max_dim, st));
-  if (R.n_lz) KPM_HIP(launch_res_lanczos(a, R.nch, R.n_lz, R.max_dim, st));
+  if (R.n_lz) KPM_HIP(launch_resident(a, kResLz, R.nch, R.n_lz, R.max_dim, st));
   return KPM_OK;
 }
 
@@ -1846,7 +1874,7 @@ size_t resident_workspace(const kpm_problem* p, int n, const kpm_params& q) {
   if (lz && lanczos_steps_of(q) > kResLanczos) return 0;
   const int64_t cols = res_columns(p, n, q);
   if (cols > (int64_t(1) << 24)) return 0;
-  const size_t total = res_layout(p, n, cols, n_steps(q.M), lz).total;
+  const size_t total = res_layout(p, n, cols, n_steps(q.M), lz, q.vec_kind == KPM_VEC_BASIS).total;
   if (total > KPM_NOALLOC_MAX_BYTES) {
     const size_t stepped = stepped_workspace(p, n, q);
     if (stepped && stepped <= KPM_NOALLOC_MAX_BYTES) return 0;
@@ -2089,6 +2117,119 @@ int resolve_scale(const kpm_problem* p, int n, const kpm_params& q, const Spare&
   return KPM_OK;
 }
 
+// The problems with every window given, those that hang on rounding settled.
+int settled_problems(const kpm_problem* p, int n, const kpm_params& q, const ResRun& R, const Spare& mem, hipStream_t st,
+                     std::vector<kpm_problem>& given) {
+  std::vector<double> lohi(2 * (size_t)n);
+  std::vector<int32_t> unstable(n);
+  KPM_HIP(hipMemcpyAsync(lohi.data(), R.a.lohi, lohi.size() * 8, hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipMemcpyAsync(unstable.data(), R.a.unstable, (size_t)n * 4, hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipStreamSynchronize(st));
+  const int r = settle_bounds(p, n, unstable, lanczos_steps_of(q), q.bound_margin, q.seed, lohi.data(), mem, st);
+  if (r != KPM_OK) return r;
+  given.assign(p, p + n);
+  for (int i = 0; i < n; ++i)
+    if (std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi)) {
+      given[i].e_lo = lohi[2 * i];
+      given[i].e_hi = lohi[2 * i + 1];
+    }
+  return KPM_OK;
+}
+
+FinalArgs res_final(const ResRun& R, const ResLayout& L, unsigned char* work, int n, const kpm_params& q, int64_t cols,
+                    double* d_mu) {
+  FinalArgs fa{};
+  fa.probs = R.a.probs;
+  fa.units = reinterpret_cast<UnitDev*>(work + L.units);
+  fa.prob_unit0 = reinterpret_cast<int32_t*>(work + L.pu0);
+  fa.alpha = R.a.alpha;
+  fa.beta = R.a.beta;
+  fa.mu = d_mu;
+  fa.flag = R.a.flag;
+  fa.n_probs = n;
+  fa.M = q.M;
+  fa.total_cols = (int32_t)cols;
+  fa.cols_per_vec = cols_per_vec(q.vec_kind);
+  fa.R = q.vec_kind == KPM_VEC_BASIS ? 0 : q.R;
+  return fa;
+}
+
+// ------------------------------------------------ gradient, resident sectors
+
+// Whether the gradient calls run resident (kpm_resident.hip); the checkpoints
+// keep as many vectors as on the step kernels.
+bool resident_gradient(const kpm_problem* p, int n, const kpm_params& q) {
+  if (q.precision != KPM_FP64 || q.col_block != 0 || std::getenv("KPM_ADJ_FWD") || !resident_problems(p, n)) return false;
+  if (count_nan(p, n) && lanczos_steps_of(q) > kResLanczos) return false;
+  return res_columns(p, n, q) <= (int64_t(1) << 24);
+}
+
+// The layout depends on the problems as the caller gave them (`n_lz` of their
+// windows open), so that the reverse sweep of a later call finds it.
+ResLayout grad_layout(const kpm_problem* p, int n, const kpm_params& q, int n_lz, int ckpt_every) {
+  return res_layout(p, n, res_columns(p, n, q), n_steps(q.M), n_lz, q.vec_kind == KPM_VEC_BASIS, ckpt_every);
+}
+
+// Bounds and moments with the forward vectors kept in `work`; d_ab0 (device):
+// the (a, b) to use instead of the problems' windows, d_mu may then be NULL.
+int res_grad_forward(const kpm_problem* p, int n, const kpm_params& q, const double* d_ab0, int ckpt_every,
+                     double* d_mu, double* d_ab, unsigned char* work, const ResLayout& L, hipStream_t st) {
+  const int64_t cols = res_columns(p, n, q);
+  std::vector<kpm_problem> unit;
+  const kpm_problem* pp = p;
+  if (d_ab0) {
+    unit.assign(p, p + n);
+    for (auto& u : unit) {
+      u.e_lo = -1.0;
+      u.e_hi = 1.0;
+    }
+    pp = unit.data();
+  }
+  ResRun R;
+  StreamSync guard{st};                  // the staging buffer outlives its copy
+  int r = res_start(pp, n, q, cols, n_steps(q.M), L, work, R, st, ckpt_every);
+  if (r != KPM_OK) return r;
+  if (d_ab0) KPM_HIP(hipMemcpyAsync(R.a.scale, d_ab0, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
+  KPM_HIP(launch_resident(R.a, kResMom, R.nch, R.n_jobs, R.max_dim, st));
+  if (d_mu) KPM_HIP(launch_finalize(res_final(R, L, work, n, q, cols, d_mu), st));
+  if (d_ab) KPM_HIP(hipMemcpyAsync(d_ab, R.a.scale, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
+  if (d_ab0) return KPM_OK;
+  int flag = 0;
+  KPM_HIP(hipMemcpyAsync(&flag, R.a.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipStreamSynchronize(st));
+  if (flag & 2) return KPM_EDEVICE;
+  if (flag & 8) return KPM_EINVAL;
+  if (flag & 16) {
+    std::vector<kpm_problem> given;
+    r = settled_problems(p, n, q, R, Spare{work, L.total, true}, st, given);
+    if (r != KPM_OK) return r;
+    return res_grad_forward(given.data(), n, q, nullptr, ckpt_every, d_mu, d_ab, work, L, st);
+  }
+  return (flag & 1) ? KPM_EBOUNDS : KPM_OK;
+}
+
+// dL/dJ from dL/dmu and what res_grad_forward left in `work`.
+int res_grad_reverse(const kpm_problem* p, int n, const kpm_params& q, const double* d_ab, const double* d_dmu,
+                     int ckpt_every, double* d_dJ, unsigned char* work, const ResLayout& L, hipStream_t st) {
+  std::vector<kpm_problem> unit(p, p + n);   // windows play no part here
+  for (auto& u : unit) {
+    u.e_lo = -1.0;
+    u.e_hi = 1.0;
+  }
+  ResRun R;
+  int r = res_start(unit.data(), n, q, res_columns(p, n, q), n_steps(q.M), L, work, R, st, ckpt_every, true);
+  if (r != KPM_OK) return r;
+  if (d_ab) KPM_HIP(hipMemcpyAsync(R.a.scale, d_ab, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
+  R.a.lambda = d_dmu;
+  KPM_HIP(launch_resident(R.a, kResAdj, R.nch, R.n_jobs, R.max_dim, st));
+  KPM_HIP(launch_res_bond_sum(R.a, reinterpret_cast<UnitDev*>(work + L.units), n, d_dJ, st));
+  int flag = 0;
+  KPM_HIP(hipMemcpyAsync(&flag, R.a.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  KPM_HIP(hipStreamSynchronize(st));
+  if (flag & 8) return KPM_EINVAL;
+  return flag ? KPM_EDEVICE : KPM_OK;
+}
+
 // ------------------------------------------------------------- adjoint driver
 
 struct VjpLayout {
@@ -2166,6 +2307,7 @@ RunShape adj_shape(const kpm_params& q) {
 }
 
 size_t vjp_workspace(const kpm_problem* p, int n, const kpm_params& q, int ckpt_every) {
+  if (resident_gradient(p, n, q)) return grad_layout(p, n, q, count_nan(p, n), ckpt_every).total;
   Planned P, F;
   if (make_plan(p, n, adj_shape(q), nullptr, nullptr, P) != KPM_OK) return 0;
   const bool fwd = forward_plan_for(p, n, q, P, nullptr, nullptr, F);
@@ -2630,7 +2772,7 @@ int run_resident(const kpm_problem* p, int n, const kpm_params& q, double* d_mu,
                  size_t work_bytes, hipStream_t st, bool direct) {
   const int64_t cols = res_columns(p, n, q);
   const int K = n_steps(q.M);
-  const ResLayout L = res_layout(p, n, cols, K, count_nan(p, n));
+  const ResLayout L = res_layout(p, n, cols, K, count_nan(p, n), q.vec_kind == KPM_VEC_BASIS);
   ResRun R;
   StreamSync guard{st};                  // the staging buffer outlives its copy
   int r = res_start(p, n, q, cols, K, L, work, R, st);
@@ -2647,22 +2789,9 @@ int run_resident(const kpm_problem* p, int n, const kpm_params& q, double* d_mu,
     KPM_HIP(hipEventCreate(&ev.b));
     KPM_HIP(hipEventRecord(ev.a, st));
   }
-  KPM_HIP(launch_res_moments(R.a, R.nch, R.n_jobs, R.max_dim, st));
+  KPM_HIP(launch_resident(R.a, kResMom, R.nch, R.n_jobs, R.max_dim, st));
   if (ev.b) KPM_HIP(hipEventRecord(ev.b, st));
-  FinalArgs fa{};
-  fa.probs = R.a.probs;
-  fa.units = reinterpret_cast<UnitDev*>(work + L.units);
-  fa.prob_unit0 = reinterpret_cast<int32_t*>(work + L.pu0);
-  fa.alpha = R.a.alpha;
-  fa.beta = R.a.beta;
-  fa.mu = d_mu;
-  fa.flag = R.a.flag;
-  fa.n_probs = n;
-  fa.M = q.M;
-  fa.total_cols = (int32_t)cols;
-  fa.cols_per_vec = cols_per_vec(q.vec_kind);
-  fa.R = q.vec_kind == KPM_VEC_BASIS ? 0 : q.R;
-  KPM_HIP(launch_finalize(fa, st));
+  KPM_HIP(launch_finalize(res_final(R, L, work, n, q, cols, d_mu), st));
   if (d_ab) KPM_HIP(hipMemcpyAsync(d_ab, R.a.scale, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
   int flag = 0;
   KPM_HIP(hipMemcpyAsync(&flag, R.a.flag, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -2688,20 +2817,9 @@ int run_resident(const kpm_problem* p, int n, const kpm_params& q, double* d_mu,
   if (flag & 8) return KPM_EINVAL;
   if (flag & 16) {
     // some window hangs on rounding: settle it and run again with it given
-    std::vector<double> lohi(2 * (size_t)n);
-    std::vector<int32_t> unstable(n);
-    KPM_HIP(hipMemcpyAsync(lohi.data(), R.a.lohi, lohi.size() * 8, hipMemcpyDeviceToHost, st));
-    KPM_HIP(hipMemcpyAsync(unstable.data(), R.a.unstable, (size_t)n * 4, hipMemcpyDeviceToHost, st));
-    KPM_HIP(hipStreamSynchronize(st));
-    r = settle_bounds(p, n, unstable, lanczos_steps_of(q), q.bound_margin, q.seed, lohi.data(),
-                      Spare{work, work_bytes, !direct}, st);
+    std::vector<kpm_problem> given;
+    r = settled_problems(p, n, q, R, Spare{work, work_bytes, !direct}, st, given);
     if (r != KPM_OK) return r;
-    std::vector<kpm_problem> given(p, p + n);
-    for (int i = 0; i < n; ++i)
-      if (std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi)) {
-        given[i].e_lo = lohi[2 * i];
-        given[i].e_hi = lohi[2 * i + 1];
-      }
     return run_resident(given.data(), n, q, d_mu, d_ab, work, work_bytes, st, direct);
   }
   return (flag & 1) ? KPM_EBOUNDS : KPM_OK;
@@ -3145,6 +3263,11 @@ int chebyshev_moments_vjp(const kpm_problem* p, int32_t n, const kpm_params* q,
     } else if (work_bytes < need) {
       return KPM_EWORKSPACE;
     }
+    if (resident_gradient(p, n, *q)) {
+      const ResLayout L = grad_layout(p, n, *q, count_nan(p, n), ckpt_every);
+      r = res_grad_forward(p, n, *q, d_ab, ckpt_every, nullptr, nullptr, work, L, st);
+      return r != KPM_OK ? r : res_grad_reverse(p, n, *q, nullptr, d_dmu, ckpt_every, d_dJ, work, L, st);
+    }
     std::vector<double> h_ab(2 * n);
     KPM_HIP(hipMemcpyAsync(h_ab.data(), d_ab, h_ab.size() * 8, hipMemcpyDeviceToHost, st));
     KPM_HIP(hipStreamSynchronize(st));
@@ -3174,6 +3297,9 @@ int chebyshev_moments_ckpt(const kpm_problem* p, int32_t n, const kpm_params* q,
     if (need == 0) return KPM_EINVAL;
     if (work_bytes < need) return KPM_EWORKSPACE;
     unsigned char* work = static_cast<unsigned char*>(d_work);
+    if (resident_gradient(p, n, *q))
+      return res_grad_forward(p, n, *q, nullptr, ckpt_every, d_mu, d_ab, work,
+                              grad_layout(p, n, *q, count_nan(p, n), ckpt_every), st);
     Planned P0;
     r = make_plan(p, n, shape_of(*q), nullptr, nullptr, P0);
     if (r != KPM_OK) return r;
@@ -3204,6 +3330,9 @@ int chebyshev_moments_vjp_resume(const kpm_problem* p, int32_t n, const kpm_para
     const size_t need = chebyshev_moments_ckpt_workspace_size(p, n, q, ckpt_every);
     if (need == 0) return KPM_EINVAL;
     if (work_bytes < need) return KPM_EWORKSPACE;
+    if (resident_gradient(p, n, *q))
+      return res_grad_reverse(p, n, *q, d_ab, d_dmu, ckpt_every, d_dJ, static_cast<unsigned char*>(d_work),
+                              grad_layout(p, n, *q, count_nan(p, n), ckpt_every), st);
     std::vector<double> h_ab(2 * n);
     KPM_HIP(hipMemcpyAsync(h_ab.data(), d_ab, h_ab.size() * 8, hipMemcpyDeviceToHost, st));
     KPM_HIP(hipStreamSynchronize(st));
@@ -3293,6 +3422,25 @@ int kpm_thermo_grad(const kpm_problem* p, int32_t n, const kpm_params* q, int32_
     double* ab = reinterpret_cast<double*>(t8 + 2 * align_up((size_t)n * q->M * 8));
     double* outs = reinterpret_cast<double*>(t8 + 2 * align_up((size_t)n * q->M * 8) + align_up((size_t)n * 16));
     const size_t ms = align_up(m * 8) / 8;
+    // the adjoint's checkpointed forward pass gives the moments; between it and
+    // the reverse sweep: dL/dmu, and L from the thermodynamics
+    auto between = [&]() -> int {
+      int rr = kpm_thermo_vjp(mu, ab, p, n, q->M, kernel, n_nodes, d_T, n_T, d_wC, d_wchi, lam, stream);
+      if (rr != KPM_OK) return rr;
+      rr = kpm_thermo(mu, ab, p, n, q->M, kernel, n_nodes, d_T, n_T, outs, outs + ms, outs + 2 * ms,
+                      outs + 3 * ms, nullptr, stream);
+      if (rr != KPM_OK) return rr;
+      KPM_HIP(launch_loss(outs + 2 * ms, outs + 3 * ms, d_wC, d_wchi, (int)m, d_L, st));
+      return KPM_OK;
+    };
+    if (resident_gradient(p, n, *q)) {
+      const ResLayout L = grad_layout(p, n, *q, count_nan(p, n), ckpt_every);
+      r = res_grad_forward(p, n, *q, nullptr, ckpt_every, mu, ab, work, L, st);
+      if (r != KPM_OK) return r;
+      if (d_ab) KPM_HIP(hipMemcpyAsync(d_ab, ab, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
+      r = between();
+      return r != KPM_OK ? r : res_grad_reverse(p, n, *q, nullptr, lam, ckpt_every, d_dJ, work, L, st);
+    }
     // bounds and (a, b) as chebyshev_moments resolves them
     Planned P0;
     r = make_plan(p, n, shape_of(*q), nullptr, nullptr, P0);
@@ -3308,17 +3456,6 @@ int kpm_thermo_grad(const kpm_problem* p, int32_t n, const kpm_params* q, int32_
     }
     KPM_HIP(hipMemcpyAsync(ab, h_ab.data(), h_ab.size() * 8, hipMemcpyHostToDevice, st));
     if (d_ab) KPM_HIP(hipMemcpyAsync(d_ab, ab, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
-    // the adjoint's checkpointed forward pass gives the moments; between it and
-    // the reverse sweep: dL/dmu, and L from the thermodynamics
-    auto between = [&]() -> int {
-      int rr = kpm_thermo_vjp(mu, ab, p, n, q->M, kernel, n_nodes, d_T, n_T, d_wC, d_wchi, lam, stream);
-      if (rr != KPM_OK) return rr;
-      rr = kpm_thermo(mu, ab, p, n, q->M, kernel, n_nodes, d_T, n_T, outs, outs + ms, outs + 2 * ms,
-                      outs + 3 * ms, nullptr, stream);
-      if (rr != KPM_OK) return rr;
-      KPM_HIP(launch_loss(outs + 2 * ms, outs + 3 * ms, d_wC, d_wchi, (int)m, d_L, st));
-      return KPM_OK;
-    };
     return run_vjp(p, n, *q, h_ab.data(), lam, ckpt_every, d_dJ, work, st, mu, between);
   });
 }

@@ -390,9 +390,10 @@ constexpr int kResMaxDim = 19456;     // 19 rows per thread of 1024; v_n and the
 constexpr int kResMaxBonds = 32;
 constexpr int kResLanczos = 256;      // Lanczos steps whose coefficients are kept in LDS
 constexpr int KPM_RES_GAUSSIAN = 2;   // start_value's kind of the Lanczos start column
+constexpr int kResAdjThreads = 512;   // threads of the gradient's workgroups
+constexpr int kResMom = 0, kResLz = 1, kResAdj = 2;   // launch_resident: moments, bounds, reverse sweep
 struct ResInfo {
   int64_t idx_off;     // first 16-byte index entry of the problem ([nch][dim])
-  int64_t diag_off;    // first diagonal entry
   int32_t nch;         // index entries (8 bonds each) per row
   int32_t coef_off;    // first of its nch * 8 masks and coefficients (zeros past the last bond)
 };
@@ -408,7 +409,6 @@ struct ResArgs {
   const uint32_t* mask;    // per bond (1 << i) | (1 << j)
   const double* coef;      // per bond J_b / 2
   uint4* idx;
-  double* diag;
   double* scale;           // [n_probs][2]: (a, b)
   double* lohi;            // [n_probs][2]: the window
   double* alpha;           // [K + 1][total_cols]
@@ -418,10 +418,19 @@ struct ResArgs {
   uint64_t seed;
   double margin, eps;
   int32_t K, total_cols, vec_kind, lz_steps;
+  // gradient (NULL otherwise): per column the rows of the columns before it;
+  // the vectors kept by the forward pass and made again by the reverse sweep
+  const int64_t* col_elems;
+  double* seg;             // per column [K + 1][dim] (whole trajectory) or [min(C, K) + 2][dim]
+  double* ckpt;            // per column [n_ckpt][2][dim]; NULL: whole trajectory in seg
+  double* wsave;           // per column [2][dim] (with checkpoints)
+  const double* lambda;    // [n_probs][M] = dL/dmu
+  double* bond_part;       // [total_cols][kResMaxBonds]
+  int32_t ckpt_every, n_ckpt, M, R;   // R = 0: complete basis
 };
 hipError_t launch_res_tables(const ResArgs& a, int n_probs, uint32_t max_dim, hipStream_t st);
-hipError_t launch_res_moments(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st);
-hipError_t launch_res_lanczos(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st);
+hipError_t launch_resident(const ResArgs& a, int what, int nch, int n_jobs, uint32_t max_dim, hipStream_t st);
+hipError_t launch_res_bond_sum(const ResArgs& a, const UnitDev* units, int n_probs, double* dJ, hipStream_t st);
 
 struct ThermoVjpArgs {
   const ThermoProb* tp;

@@ -8,10 +8,13 @@
 // neighbour indices is read from memory per step, and those only where they
 // do not fit registers.
 //
-// What bounds it: the LDS gathers.  A row needs one 8-byte LDS read per bond
-// (a bond that does not act reads the zero slot behind the vector, one address
-// for all lanes), 64 lanes to random addresses; with one row per thread the
-// two barriers per step and the dot reduction cost as much again.
+// H = sum_b J_b (P_b / 2 - 1/4), P_b the exchange of the bond's two sites, so
+// a row is sum_b (J_b / 2) v[P_b r] - (sum_b J_b / 4) v[r]: one index per bond
+// and no diagonal of its own.
+//
+// What bounds it: the LDS gathers.  A row needs one 8-byte LDS read per bond,
+// 64 lanes to scattered addresses; with one row per thread the two barriers
+// per step and the dot reduction cost as much again.
 //
 // Why: these sectors took one launch per step, 17-30 us each however few
 // states they had (a chain of dependent loads through L2, then the next
@@ -32,9 +35,9 @@ namespace kpm {
 
 // ------------------------------------------------------------------ tables
 
-// Per row: the diagonal sum_b +-J_b/4 of H, and the rank of the state each
-// bond maps it to (16 bits; dim, the zero slot, where the bond does not act),
-// eight bonds per 16-byte entry, entries of one chunk consecutive in the row.
+// Per row: the rank of the state each bond's exchange maps it to (16 bits; the
+// row itself where the two sites agree), eight bonds per 16-byte entry,
+// entries of one chunk consecutive in the row.
 __global__ __launch_bounds__(kThreads) void res_tables_kernel(const ResArgs a) {
   __shared__ uint32_t bn[kBinomN * kBinomN];
   for (int e = threadIdx.x; e < kBinomN * kBinomN; e += kThreads) bn[e] = a.binom[e];
@@ -46,9 +49,7 @@ __global__ __launch_bounds__(kThreads) void res_tables_kernel(const ResArgs a) {
   if (r >= dim) return;
   const uint32_t s = unrank(r, P.n_sites, P.n_up, bn);
   const uint32_t* mask = a.mask + I.coef_off;
-  const double* off = a.coef + I.coef_off;
   uint4* out = a.idx + I.idx_off;
-  double d = 0.0;
   for (int ch = 0; ch < I.nch; ++ch) {
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -56,21 +57,18 @@ __global__ __launch_bounds__(kThreads) void res_tables_kernel(const ResArgs a) {
       const uint32_t m = mask[ch * 8 + t];    // 0 past the last bond
       const uint32_t v = s & m;
       const bool act = v != 0u && v != m;
-      const double h = 0.5 * off[ch * 8 + t];
-      d += act ? -h : h;                      // the padding's coefficient is 0
-      uint32_t n = dim;
+      uint32_t n = r;
       if (act) {
         n = word_rank(s ^ m, bn);
         if (n >= dim) {
           atomicOr(a.flag, 2);
-          n = dim;
+          n = r;
         }
       }
       w[t >> 1] |= n << ((t & 1) * 16);
     }
     out[(size_t)ch * dim + r] = make_uint4(w[0], w[1], w[2], w[3]);
   }
-  a.diag[I.diag_off + r] = d;
 }
 
 // ------------------------------------------------------------------ helpers
@@ -107,7 +105,29 @@ __device__ __forceinline__ double group_sum(double v, double* slot, int lane, in
   return t;
 }
 
-// sum_b (J_b / 2) x[neighbour] of one row from its NCH index entries
+// Threads of the workgroup: a constant where a thread has more than one row
+// (the launch then uses the most), so that row offsets are too.
+template <int RPT>
+__device__ __forceinline__ int group_threads(int most) {
+  return RPT > 1 ? most : (int)blockDim.x;
+}
+
+// Element r of a row of doubles: 32-bit offset from a scalar base.
+__device__ __forceinline__ double& at(double* base, uint32_t r) {
+  return *reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(base) + r * 8u);
+}
+__device__ __forceinline__ double at(const double* base, uint32_t r) {
+  return *reinterpret_cast<const double*>(reinterpret_cast<const unsigned char*>(base) + r * 8u);
+}
+
+// sum_b J_b / 4 (coefficients past the last bond are 0)
+__device__ __forceinline__ double half_sum(cptr<double> cf) {
+  double s = 0.0;
+  for (int b = 0; b < kResMaxBonds; ++b) s += cf[b];
+  return 0.5 * s;
+}
+
+// sum_b (J_b / 2) x[exchanged row] of one row from its NCH index entries
 template <int NCH>
 __device__ __forceinline__ double gather_row(const uint4 (&q)[NCH], cptr<double> cf, const double* x) {
   double acc = 0.0;
@@ -131,9 +151,7 @@ template <int RPT, int NCH>
 struct Rows {
   static constexpr bool kKeep = RPT * NCH <= 8;
   uint4 q[kKeep ? RPT : 1][NCH];
-  double dg[kKeep ? RPT : 1];
   const uint4* src;
-  const double* dsrc;
   uint32_t dim;
   int nch;
   __device__ __forceinline__ void load(int k, uint32_t r, uint4 (&o)[NCH]) const {
@@ -141,10 +159,6 @@ struct Rows {
     for (int ch = 0; ch < NCH; ++ch)     // 32-bit offsets from a scalar base
       o[ch] = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(src) +
                                               (uint32_t)(((uint32_t)(ch < nch ? ch : 0) * dim + r) * 16u));
-  }
-  __device__ __forceinline__ double diag(int k, uint32_t r) const {
-    if constexpr (kKeep) return dg[k];
-    else return *reinterpret_cast<const double*>(reinterpret_cast<const unsigned char*>(dsrc) + r * 8u);
   }
 };
 
@@ -194,11 +208,60 @@ __device__ __forceinline__ void product(const Rows<RPT, NCH>& R, cptr<double> cf
   }
 }
 
+// The product with its bond dots: D[b] += v x[P_b r] over the thread's rows,
+// v = of(row, on).
+template <int NCH>
+__device__ __forceinline__ double gather_dots(const uint4 (&q)[NCH], cptr<double> cf, const double* x, double v,
+                                              double (&D)[NCH * 8]) {
+  double acc = 0.0;
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) {
+    const uint32_t w[4] = {q[ch].x, q[ch].y, q[ch].z, q[ch].w};
+    double g[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) g[t] = x[(w[t >> 1] >> ((t & 1) * 16)) & 0xFFFFu];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      acc = fma(cf[ch * 8 + t], g[t], acc);
+      D[ch * 8 + t] = fma(v, g[t], D[ch * 8 + t]);
+    }
+  }
+  return acc;
+}
+template <int RPT, int NCH, typename V, typename F>
+__device__ __forceinline__ void product_dots(const Rows<RPT, NCH>& R, cptr<double> cf, const double* x, int tid, int T,
+                                             double (&D)[NCH * 8], V&& of, F&& use) {
+  uint4 nxt[NCH];
+  tid = (int)fresh((uint32_t)tid);
+  if constexpr (!Rows<RPT, NCH>::kKeep) R.load(0, min((uint32_t)tid, R.dim - 1u), nxt);
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    const uint32_t r0 = (uint32_t)(k * T);
+    if (r0 < R.dim) {
+      uint4 cur[NCH];
+      const uint32_t r = r0 + (uint32_t)tid;
+      const uint32_t rc = min(r, R.dim - 1u);
+      const double v = of(rc, r < R.dim);
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        if constexpr (Rows<RPT, NCH>::kKeep)
+          cur[ch] = make_uint4(fresh(R.q[k][ch].x), fresh(R.q[k][ch].y), fresh(R.q[k][ch].z), fresh(R.q[k][ch].w));
+        else
+          cur[ch] = nxt[ch];
+      }
+      if constexpr (!Rows<RPT, NCH>::kKeep)
+        if (k + 1 < RPT && r0 + (uint32_t)T < R.dim) R.load(k + 1, min(r + (uint32_t)T, R.dim - 1u), nxt);
+      const double h = gather_dots<NCH>(cur, cf, x, v, D);
+      use(k, rc, r < R.dim, h, v);
+      if constexpr (!Rows<RPT, NCH>::kKeep) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
 template <int RPT, int NCH>
 __device__ __forceinline__ void rows_init(Rows<RPT, NCH>& R, const ResArgs& a, const ResInfo& I, uint32_t dim, int tid,
                                           int T) {
   R.src = a.idx + I.idx_off;
-  R.dsrc = a.diag + I.diag_off;
   R.dim = dim;
   R.nch = I.nch;
   if constexpr (Rows<RPT, NCH>::kKeep) {
@@ -206,7 +269,6 @@ __device__ __forceinline__ void rows_init(Rows<RPT, NCH>& R, const ResArgs& a, c
     for (int k = 0; k < RPT; ++k) {
       const uint32_t r = min((uint32_t)(tid + k * T), dim - 1u);
       R.load(k, r, R.q[k]);
-      R.dg[k] = R.dsrc[r];
     }
   }
 }
@@ -249,20 +311,21 @@ __device__ __forceinline__ double start_rows(const ResArgs& a, const ProbDev& P,
 // waves and written, so that the sum is not on every step's path.
 constexpr int kResRing = 8;
 
-template <int RPT, int NCH>
+template <int RPT, int NCH, bool KEEP>
 __global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
   extern __shared__ __align__(16) double sm[];
-  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, nw = T >> 6;
+  const int tid = threadIdx.x, T = group_threads<RPT>(1024), lane = tid & 63, nw = T >> 6;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ResJob J = a.jobs[blockIdx.x];
   const ProbDev P = a.probs[J.prob];
   const ResInfo I = a.info[J.prob];
   const uint32_t dim = (uint32_t)P.dim;
   double* red = sm;                       // [kResRing][16][2]
-  double* x = sm + kResRing * 32;         // [dim + 1]
+  double* x = sm + kResRing * 32;         // [dim]
   const double sa = a.scale[2 * J.prob], sb = a.scale[2 * J.prob + 1];
-  const double inva = 1.0 / sa, sh = -sb / sa;
+  const double inva = 1.0 / sa;
   const cptr<double> cf = cview(a.coef) + I.coef_off;
+  const double dg = -(half_sum(cf) + sb) * inva;
   Rows<RPT, NCH> R;
   rows_init(R, a, I, dim, tid, T);
   double y[RPT];
@@ -274,7 +337,6 @@ __global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
     if (r < dim) acc0 = fma(x[r], x[r], acc0);
     y[k] = 0.0;
   }
-  if (tid == 0) x[dim] = 0.0;
   __syncthreads();                        // x complete; the slots of start_rows read
   {
     const double s0 = group_sum(acc0, red, lane, wid, nw);
@@ -282,11 +344,20 @@ __global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
     __syncthreads();
   }
   const int64_t TC = a.total_cols;
+  // gradient calls: the whole trajectory (slot n holds v_n), or v_n and
+  // v_{n+1} at every ckpt_every-th step
+  const bool full = KEEP && a.ckpt == nullptr;
+  double* kept = nullptr;
+  if constexpr (KEEP) {
+    kept = full ? a.seg + (a.K + 1) * a.col_elems[J.ocol] : a.ckpt + 2 * (int64_t)a.n_ckpt * a.col_elems[J.ocol];
+    if (full)
+      for (uint32_t r = tid; r < dim; r += T) kept[r] = x[r];
+  }
   for (int n = 0; n < a.K; ++n) {
     double s2 = 0.0, s1 = 0.0;
     product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
       const double xr = x[r];
-      const double hx = fma(fma(R.diag(k, r), xr, h), inva, sh * xr);
+      const double hx = fma(h, inva, dg * xr);
       const double v = on ? (n == 0 ? hx : fma(2.0, hx, -y[k])) : 0.0;
       s2 = fma(v, v, s2);
       s1 = fma(v, xr, s1);
@@ -295,12 +366,24 @@ __global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
     const double f = wave_sum2(s2, s1, lane);
     if (lane < 2) red[(n & (kResRing - 1)) * 32 + wid * 2 + lane] = f;
     __syncthreads();                      // every read of v_n done
+    const bool mark = KEEP && !full && n % a.ckpt_every == 0;
+    double* k0 = nullptr;                 // where v_n goes (checkpoints) and v_{n+1}
+    double* k1 = nullptr;
+    if constexpr (KEEP) {
+      k0 = kept + 2 * (int64_t)(n / a.ckpt_every) * dim;
+      k1 = full ? kept + (int64_t)(n + 1) * dim : k0 + dim;
+    }
+    const uint32_t t0 = fresh((uint32_t)tid);
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
-      const uint32_t r = (uint32_t)(tid + k * T);
+      const uint32_t r = t0 + (uint32_t)(k * T);
       if (r < dim) {
         const double t = x[r];
         x[r] = y[k];
+        if constexpr (KEEP) {
+          if (mark) at(k0, r) = t;
+          if (mark || full) at(k1, r) = y[k];
+        }
         y[k] = t;
       }
     }
@@ -319,6 +402,168 @@ __global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
   }
 }
 
+// ------------------------------------------------------------------ gradient
+
+// Reverse sweep of one column (the recursion of kpm_adjoint.hip): with the
+// adjoint vectors w_{n+1} in LDS and w_{n+2} in registers,
+//   w_n = 2 abar_n v_n + bbar_n v_{n+1} + bbar_{n-1} v_{n-1} + 2 H' w_{n+1} - w_{n+2},
+// and the gathers of w_{n+1} give the bond dots too: h_b = P_b / 2 - 1/4, so
+//   <w_{n+1}, h_b v_n> = sum_r v_n[r] (w_{n+1}[P_b r] / 2 - w_{n+1}[r] / 4).
+// A thread carries one sum per bond over all rows and steps; they are added
+// over the workgroup once, at the end.  Vectors of v between checkpoints are
+// made again, in the workgroup, by the forward step.
+//
+// 512 threads: a wave then has 256 registers, which hold w_{n+2} and the bond
+// sums of up to 19456 rows without spills (1024 threads: 128).
+template <int RPT, int NCH>
+__global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResArgs a) {
+  extern __shared__ __align__(16) double sm[];
+  const int tid = threadIdx.x, T = group_threads<RPT>(kResAdjThreads), lane = tid & 63, nw = T >> 6;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const ResJob J = a.jobs[blockIdx.x];
+  const ProbDev P = a.probs[J.prob];
+  const ResInfo I = a.info[J.prob];
+  const uint32_t dim = (uint32_t)P.dim;
+  double* red = sm;                       // [2][16]
+  double* x = sm + 32;                    // [dim]
+  const double sa = a.scale[2 * J.prob], sb = a.scale[2 * J.prob + 1];
+  if (tid == 0 && (!(sa > 0.0) || !isfinite(sa) || !isfinite(sb))) atomicOr(a.flag, 8);
+  const double inva = 1.0 / sa;
+  const cptr<double> cf = cview(a.coef) + I.coef_off;
+  const double dg = -(half_sum(cf) + sb) * inva;
+  // dL/d<v_n, v_n> and dL/d<v_{n+1}, v_n> from dL/dmu through the estimator
+  // and the doubling identities
+  const double* lam = a.lambda + (int64_t)J.prob * a.M;
+  double norm = a.alpha[J.ocol];
+  if (a.vec_kind == 1) norm = a.alpha[J.ocol & ~1] + a.alpha[J.ocol | 1];
+  const double est = (double)dim / ((a.R > 0 ? (double)a.R : (double)dim) * norm);
+  double odd = 0.0;
+  for (int n = 3 + 2 * tid; n < a.M; n += 2 * T) odd += lam[n];
+  odd = group_sum(odd, red, lane, wid, nw);
+  auto abar = [&](int n) { return 2 * n < a.M ? 2.0 * est * lam[2 * n] : 0.0; };            // n >= 1
+  auto bbar = [&](int n) {
+    if (n == 0) return est * (lam[1] - odd);
+    return 2 * n + 1 < a.M ? 2.0 * est * lam[2 * n + 1] : 0.0;
+  };
+  Rows<RPT, NCH> R;
+  rows_init(R, a, I, dim, tid, T);
+  double y[RPT], D[NCH * 8], s0 = 0.0;
+#pragma unroll
+  for (int b = 0; b < NCH * 8; ++b) D[b] = 0.0;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    const uint32_t r = (uint32_t)(tid + k * T);
+    y[k] = 0.0;
+    if (r < dim) x[r] = 0.0;
+  }
+  const int64_t ce = a.col_elems[J.ocol];                    // rows of the columns before this one
+  const bool full = a.ckpt == nullptr;
+  const int C = a.ckpt_every, K = a.K;
+  double* seg = a.seg + (int64_t)(full ? K + 1 : min(C, K) + 2) * ce;
+  const double* ckpt = full ? nullptr : a.ckpt + 2 * (int64_t)a.n_ckpt * ce;
+  double* wsave = full ? nullptr : a.wsave + 2 * ce;
+  __syncthreads();
+  auto swap_in = [&]() {                                     // x <-> y, own rows
+    __syncthreads();
+    const uint32_t t0 = fresh((uint32_t)tid);
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r = t0 + (uint32_t)(k * T);
+      if (r < dim) {
+        const double t = x[r];
+        x[r] = y[k];
+        y[k] = t;
+      }
+    }
+    __syncthreads();
+  };
+  for (int m = full ? 0 : a.n_ckpt - 1; m >= 0; --m) {
+    const int j0 = full ? 0 : m * C;
+    const int j1 = full ? K : min(j0 + C, K);
+    if (!full) {
+      const double* c = ckpt + 2 * (int64_t)m * dim;
+      uint32_t t0 = fresh((uint32_t)tid);
+#pragma unroll
+      for (int k = 0; k < RPT; ++k) {
+        const uint32_t r = t0 + (uint32_t)(k * T);
+        if (r < dim) {
+          at(wsave, r) = x[r];
+          at(wsave + dim, r) = y[k];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < RPT; ++k) {
+        const uint32_t r = t0 + (uint32_t)(k * T);
+        if (r < dim) {
+          y[k] = at(c, r);
+          x[r] = at(c + dim, r);
+          at(seg, r) = y[k];
+          at(seg + dim, r) = x[r];
+        }
+      }
+      __syncthreads();
+      const int top = min(j1 + 1, K);                        // highest v index needed
+      for (int t = 1; j0 + t + 1 <= top; ++t) {
+        double* vt = seg + (int64_t)(t + 1) * dim;
+        product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
+          const double v = on ? fma(2.0, fma(h, inva, dg * x[r]), -y[k]) : 0.0;
+          if (on) at(vt, r) = v;
+          y[k] = v;
+        });
+        swap_in();
+      }
+      __syncthreads();
+      t0 = fresh((uint32_t)tid);
+#pragma unroll
+      for (int k = 0; k < RPT; ++k) {
+        const uint32_t r = t0 + (uint32_t)(k * T);
+        if (r < dim) {
+          x[r] = at(wsave, r);
+          y[k] = at(wsave + dim, r);
+        }
+      }
+      __syncthreads();
+    }
+    for (int n = j1; n >= j0 + 1; --n) {
+      const double ga = abar(n), gb = bbar(n), gbm = bbar(n - 1);
+      const double* v0 = seg + (int64_t)(n - j0) * dim;
+      const double* vm = v0 - dim;
+      const double* vp = n + 1 <= K ? v0 + dim : v0;         // bbar_K = 0
+      product_dots<RPT, NCH>(R, cf, x, tid, T, D, [&](uint32_t r, bool on) { return on ? 2.0 * at(v0, r) : 0.0; },
+                             [&](int k, uint32_t r, bool on, double h, double v2) {
+                               const double wr = x[r];
+                               s0 = fma(v2, wr, s0);
+                               const double g = fma(gbm, at(vm, r), fma(gb, at(vp, r), ga * v2));
+                               y[k] = on ? g + fma(2.0, fma(h, inva, dg * wr), -y[k]) : 0.0;
+                             });
+      swap_in();
+    }
+  }
+  // <w_1, h_b v_0> with weight 1 (slot 0 of segment 0 is v_0)
+  product_dots<RPT, NCH>(R, cf, x, tid, T, D, [&](uint32_t r, bool on) { return on ? at(static_cast<const double*>(seg), r) : 0.0; },
+                         [&](int, uint32_t r, bool, double, double v) { s0 = fma(v, x[r], s0); });
+  const double sq = group_sum(s0, red, lane, wid, nw);
+#pragma unroll
+  for (int b = 0; b < NCH * 8; ++b) {
+    const double t = group_sum(D[b], red + ((b + 1) & 1) * 16, lane, wid, nw);
+    if (tid == 0) a.bond_part[(int64_t)J.ocol * kResMaxBonds + b] = inva * (0.5 * t - 0.25 * sq);
+  }
+}
+
+// dL/dJ of problem blockIdx.x: its columns' parts, one bond per thread, the
+// columns in order.
+__global__ __launch_bounds__(64) void res_bond_sum_kernel(const ResArgs a, const UnitDev* units, double* dJ) {
+  const ProbDev P = a.probs[blockIdx.x];
+  const UnitDev U = units[blockIdx.x];
+  const int b = threadIdx.x;
+  if (b >= P.n_bonds) return;
+  const double* p = a.bond_part + (int64_t)U.col_off * kResMaxBonds + b;
+  double s = 0.0;
+  for (int c = 0; c < U.ncols; ++c) s += p[(int64_t)c * kResMaxBonds];
+  dJ[P.bond_off + b] = s;
+}
+
 // ------------------------------------------------------------------ Lanczos
 
 // Eigenvalues of the symmetric tridiagonal (al[0..L), be2[0..L-1) = squared
@@ -327,8 +572,12 @@ __device__ __forceinline__ int sturm_below(const double* al, const double* be2, 
   int cnt = 0;
   double q = 1.0;
   for (int i = 0; i < L; ++i) {
-    q = al[i] - x - (i ? be2[i - 1] / q : 0.0);
-    if (q == 0.0) q = -1e-300;
+    // the quotient by the hardware reciprocal and two Newton steps
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(fma(-q, r, 1.0), r, r);
+    r = fma(fma(-q, r, 1.0), r, r);
+    q = al[i] - x - (i ? be2[i - 1] * r : 0.0);
+    if (fabs(q) < 1e-290) q = -1e-290;
     cnt += q < 0.0;
   }
   return cnt;
@@ -340,7 +589,7 @@ __device__ __forceinline__ int sturm_below(const double* al, const double* be2, 
 template <int RPT, int NCH>
 __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
   extern __shared__ __align__(16) double sm[];
-  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, nw = T >> 6;
+  const int tid = threadIdx.x, T = group_threads<RPT>(1024), lane = tid & 63, nw = T >> 6;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ResJob J = a.lz_jobs[blockIdx.x];
   const ProbDev P = a.probs[J.prob];
@@ -349,15 +598,15 @@ __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
   double* red = sm;                       // [2][16]
   double* al = sm + 32;                   // [kResLanczos]
   double* be = al + kResLanczos;          // [kResLanczos]: beta_{j+1}^2
-  double* x = be + kResLanczos;           // [dim + 1]
+  double* x = be + kResLanczos;           // [dim]
   const cptr<double> cf = cview(a.coef) + I.coef_off;
   Rows<RPT, NCH> R;
   rows_init(R, a, I, dim, tid, T);
+  const double hs = half_sum(cf);
   double y[RPT];
   start_rows(a, P, KPM_RES_GAUSSIAN, J.col, 2, tid, T, lane, wid, nw, red, x);
 #pragma unroll
   for (int k = 0; k < RPT; ++k) y[k] = 0.0;
-  if (tid == 0) x[dim] = 0.0;
   __syncthreads();
   const int steps = (int)min((uint32_t)a.lz_steps, dim);
   double b = 0.0;
@@ -366,7 +615,7 @@ __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
     double s = 0.0;
     product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
       const double xr = x[r];
-      const double w = on ? fma(R.diag(k, r), xr, h) - b * y[k] : 0.0;
+      const double w = on ? fma(-hs, xr, h) - b * y[k] : 0.0;
       s = fma(w, xr, s);
       y[k] = w;
     });
@@ -509,41 +758,56 @@ static hipError_t launch_res(K kernel, const ResArgs& a, int grid, int threads, 
 }
 
 template <int RPT, int NCH>
-static hipError_t launch_res_t(const ResArgs& a, bool lanczos, int grid, int threads, size_t lds, hipStream_t st) {
-  return lanczos ? launch_res(res_lanczos_kernel<RPT, NCH>, a, grid, threads, lds, st)
-                 : launch_res(res_moments_kernel<RPT, NCH>, a, grid, threads, lds, st);
+static hipError_t launch_res_t(const ResArgs& a, int what, int grid, int threads, size_t lds, hipStream_t st) {
+  if constexpr (RPT <= 19 && RPT != 16) {
+    if (what == kResLz) return launch_res(res_lanczos_kernel<RPT, NCH>, a, grid, threads, lds, st);
+    if (what == kResMom)
+      return a.seg ? launch_res(res_moments_kernel<RPT, NCH, true>, a, grid, threads, lds, st)
+                   : launch_res(res_moments_kernel<RPT, NCH, false>, a, grid, threads, lds, st);
+  }
+  if constexpr (RPT != 13 && RPT != 19) {
+    if (what == kResAdj) return launch_res(res_adjoint_kernel<RPT, NCH>, a, grid, threads, lds, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int RPT>
-static hipError_t launch_res_n(const ResArgs& a, bool lanczos, int nch, int grid, int threads, size_t lds,
-                               hipStream_t st) {
-  if (nch <= 2) return launch_res_t<RPT, 2>(a, lanczos, grid, threads, lds, st);
-  if (nch <= 3) return launch_res_t<RPT, 3>(a, lanczos, grid, threads, lds, st);
-  return launch_res_t<RPT, 4>(a, lanczos, grid, threads, lds, st);
+static hipError_t launch_res_n(const ResArgs& a, int what, int nch, int grid, int threads, size_t lds, hipStream_t st) {
+  if (nch <= 2) return launch_res_t<RPT, 2>(a, what, grid, threads, lds, st);
+  if (nch <= 3) return launch_res_t<RPT, 3>(a, what, grid, threads, lds, st);
+  return launch_res_t<RPT, 4>(a, what, grid, threads, lds, st);
 }
 
 // Rows per thread: the smallest instantiation that covers the largest sector
-// with at most 1024 threads.
-static hipError_t launch_res_any(const ResArgs& a, bool lanczos, int nch, int grid, uint32_t max_dim, hipStream_t st) {
+// with at most 1024 threads (the gradient: kResAdjThreads).
+static hipError_t launch_res_any(const ResArgs& a, int what, int nch, int grid, uint32_t max_dim, hipStream_t st) {
   if (max_dim > (uint32_t)kResMaxDim || nch > kResMaxBonds / 8 || grid < 1) return hipErrorInvalidValue;
   // the bounds end on three rows of omega in the vector's place
-  const size_t lds = lanczos ? (std::max<size_t>(max_dim + 1, 3 * (kResLanczos + 2)) + 32 + 2 * kResLanczos) * 8
-                             : ((size_t)max_dim + 1 + kResRing * 32) * 8;
-  const int threads = (int)std::min<uint32_t>(1024u, std::max(64u, (max_dim + 63u) / 64u * 64u));
+  const size_t lds = what == kResLz ? (std::max<size_t>(max_dim, 3 * (kResLanczos + 2)) + 32 + 2 * kResLanczos) * 8
+                                    : ((size_t)max_dim + (what == kResMom ? kResRing * 32 : 32)) * 8;
+  const uint32_t most = what == kResAdj ? (uint32_t)kResAdjThreads : 1024u;
+  const int threads = (int)std::min<uint32_t>(most, std::max(64u, (max_dim + 63u) / 64u * 64u));
   const int rpt = (int)((max_dim + threads - 1) / threads);
-  if (rpt <= 1) return launch_res_n<1>(a, lanczos, nch, grid, threads, lds, st);
-  if (rpt <= 2) return launch_res_n<2>(a, lanczos, nch, grid, threads, lds, st);
-  if (rpt <= 4) return launch_res_n<4>(a, lanczos, nch, grid, threads, lds, st);
-  if (rpt <= 8) return launch_res_n<8>(a, lanczos, nch, grid, threads, lds, st);
-  if (rpt <= 13) return launch_res_n<13>(a, lanczos, nch, grid, threads, lds, st);
-  return launch_res_n<19>(a, lanczos, nch, grid, threads, lds, st);
+  if (rpt <= 1) return launch_res_n<1>(a, what, nch, grid, threads, lds, st);
+  if (rpt <= 2) return launch_res_n<2>(a, what, nch, grid, threads, lds, st);
+  if (rpt <= 4) return launch_res_n<4>(a, what, nch, grid, threads, lds, st);
+  if (rpt <= 8) return launch_res_n<8>(a, what, nch, grid, threads, lds, st);
+  if (what == kResAdj) {
+    if (rpt <= 16) return launch_res_n<16>(a, what, nch, grid, threads, lds, st);
+    if (rpt <= 26) return launch_res_n<26>(a, what, nch, grid, threads, lds, st);
+    return launch_res_n<38>(a, what, nch, grid, threads, lds, st);
+  }
+  if (rpt <= 13) return launch_res_n<13>(a, what, nch, grid, threads, lds, st);
+  return launch_res_n<19>(a, what, nch, grid, threads, lds, st);
 }
 
-hipError_t launch_res_moments(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st) {
-  return launch_res_any(a, false, nch, n_jobs, max_dim, st);
+hipError_t launch_resident(const ResArgs& a, int what, int nch, int n_jobs, uint32_t max_dim, hipStream_t st) {
+  return launch_res_any(a, what, nch, n_jobs, max_dim, st);
 }
-hipError_t launch_res_lanczos(const ResArgs& a, int nch, int n_jobs, uint32_t max_dim, hipStream_t st) {
-  return launch_res_any(a, true, nch, n_jobs, max_dim, st);
+
+hipError_t launch_res_bond_sum(const ResArgs& a, const UnitDev* units, int n_probs, double* dJ, hipStream_t st) {
+  hipLaunchKernelGGL(res_bond_sum_kernel, dim3(n_probs), dim3(64), 0, st, a, units, dJ);
+  return hipGetLastError();
 }
 
 }  // namespace kpm

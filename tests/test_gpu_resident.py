@@ -128,3 +128,65 @@ def test_window_too_narrow_is_reported(kpm):
     with pytest.raises(kpm.KPMError) as ei:
         kpm.chebyshev_moments([s], 200, 2, bounds=[(-1.0, 1.0)])
     assert ei.value.code == kpm.KPM_EBOUNDS
+
+
+def _gradient(kpm, sec, M, R, kind, ckpt, seed):
+    """dL/dJ of one sector, from the resumed and from the single call, against the oracle."""
+    import torch
+
+    from oracle import adjoint
+    ps = kpm.ProblemSet([sec])
+    mu, ab, ws = kpm.moments_ckpt(None, M, R, kind, seed=seed, ckpt_every=ckpt, problems=ps)
+    mu0, ab0 = kpm.chebyshev_moments([sec], M, R, kind, seed=seed)
+    assert kpm.last_run_stats()["kernel"] == 6
+    assert torch.equal(ab, ab0) and torch.equal(mu, mu0)
+    lam = np.random.default_rng(M).normal(size=(1, M))
+    lam_d = torch.tensor(lam, device="cuda")
+    got = kpm.moments_vjp_resume(ps, M, R, ab, lam_d, ws, kind, seed=seed, ckpt_every=ckpt).cpu().numpy()
+    once = kpm.moments_vjp([sec], M, R, ab, lam_d, kind, seed=seed, ckpt_every=ckpt).cpu().numpy()
+    a, b = ab.cpu().numpy()[0]
+    want = adjoint.sector_moments_vjp(sec, a, b, M, R, kind, seed, lam[0])
+    assert np.abs(got - want).max() <= 1e-9 * np.abs(want).max(), (sec.dim, M, ckpt)
+    assert np.array_equal(got, once)
+
+
+@pytest.mark.parametrize("n,n_up,n_bonds", [
+    (2, 1, 1), (4, 2, 6), (12, 8, 8), (12, 6, 16),      # 2, 6, 495, 924 states: 1 and 2 rows per thread
+    (13, 7, 24), (14, 7, 17), (15, 8, 32), (16, 8, 9),  # 1716, 3432, 6435, 12870: 4, 8, 16, 26 rows
+    (17, 10, 25),                                       # 19448: 38 rows
+])
+def test_gradient_sizes(kpm, n, n_up, n_bonds):
+    sec = W.Sector(_graph(n, n_bonds, 8), n_up, 0)
+    _gradient(kpm, sec, 15, 2, "rademacher", 64, 3)      # every vector kept
+    _gradient(kpm, sec, 15, 2, "rademacher", 2, 3)       # checkpoints every second step
+
+
+@pytest.mark.parametrize("kind,R", [("rademacher", 3), ("gaussian", 2), ("complex_gaussian", 2), ("basis", 0)])
+@pytest.mark.parametrize("M,ckpt", [(2, 2), (3, 2), (17, 4), (18, 4), (40, 6), (41, 20), (42, 21), (64, 32)])
+def test_gradient_kinds_and_checkpoints(kpm, kind, R, M, ckpt):
+    """Moment counts even and odd, intervals that divide the steps or not, one
+    short of the whole trajectory and the whole of it."""
+    _gradient(kpm, W.Sector(_graph(9, 14, 9), 5, 2), M, R, kind, ckpt, 4)
+
+
+def test_gradient_of_several_sectors_matches_the_step_kernels(kpm, monkeypatch):
+    secs = W.sectors(_graph(10, 15, 10), cluster_id=0) + W.sectors(W.ring(7), cluster_id=1)
+    T = W.log_temperatures(20, 0.5, 5.0)
+    wC, wX = np.random.default_rng(1).uniform(0.5, 1.5, (2, 2, 20))
+    out = []
+    for env in ("1", "0"):
+        monkeypatch.setenv("KPM_RESIDENT", env)
+        L, dJ, ab = kpm.thermo_grad(secs, 60, 3, T, wC, wX, "complex_gaussian", kernel="jackson", ckpt_every=8, seed=5)
+        out.append((float(L), dJ.cpu().numpy(), ab.cpu().numpy()))
+    assert abs(out[0][0] - out[1][0]) <= 1e-10 * abs(out[1][0])
+    assert np.abs(out[0][1] - out[1][1]).max() <= 1e-9 * np.abs(out[1][1]).max()
+
+
+def test_gradient_refuses_an_unusable_map(kpm):
+    import torch
+    sec = W.Sector(W.ring(8), 4, 0)
+    ab = torch.tensor([[0.0, 1.0]], dtype=torch.float64, device="cuda")
+    lam = torch.ones((1, 8), dtype=torch.float64, device="cuda")
+    with pytest.raises(kpm.KPMError) as ei:
+        kpm.moments_vjp([sec], 8, 2, ab, lam, ckpt_every=4)
+    assert ei.value.code == kpm.KPM_EINVAL
