@@ -71,7 +71,7 @@ struct SliceBlk {    // written once per call with the per-block tables
   uint32_t size;     // members C(L, k), k = n_up - popcount(h) (0 if k is out of range)
   uint32_t kofs;     // position of popcount class k in the low-word tables
   uint32_t nh;       // acting high-high bonds
-  uint32_t pad;
+  uint32_t hmx;      // bit q: the high site's bit of mixed bond q
   double dhh;        // -b/a + high-high part of the diagonal
 };
 

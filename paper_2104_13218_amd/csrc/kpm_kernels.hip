@@ -1393,6 +1393,8 @@ __global__ __launch_bounds__(kThreads) void tab_meta_kernel(const ProbDev* probs
         r.size = (k >= 0 && k <= L) ? sb[L * kBinomN + k] : 0u;
         r.kofs = (k >= 0 && k <= L) ? (uint32_t)koff[k] : 0u;
         r.nh = (uint32_t)n;
+        for (int q = 0; q < P.n_mx; ++q)
+          r.hmx |= (h & (bmask[P.bond_off + bperm[q_mx + q]] >> L)) ? 1u << q : 0u;
         r.dhh = d;
         brec[g] = r;
       }

@@ -162,14 +162,6 @@ struct Rows {
   }
 };
 
-// The value as one that may change between steps: without this the compiler
-// moves every unpacked index and address of the recursion out of its loop and
-// spills them.
-__device__ __forceinline__ uint32_t fresh(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 // One product: h[k] = sum_b (J_b/2) x[nb] for the thread's rows, passed to
 // use(k, row, on, h).
 template <int RPT, int NCH, typename F>

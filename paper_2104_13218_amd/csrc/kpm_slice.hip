@@ -26,10 +26,20 @@
 //      and whose scalar offset is the target block's start.
 // Per lane, one row of a per-call word table (indexed by the low word's
 // position in its class) gives the low-low part of the diagonal, the low
-// word l, the colex rank of l ^ m_low for each mixed bond, and per low-low
+// site's bit and the colex rank of l ^ m_low for each mixed bond, and per low-low
 // bond the LDS row of the neighbour (0, the zero row, when the bond does not
 // act).  Sum order per element: diagonal, low-low, high-high, mixed, each in
 // bond order.
+//
+// Which mixed bonds act is one exclusive-or: the word row holds the low sites'
+// bits, the block record the high sites' bits.  Their coefficients are in LDS
+// and the loops' conditions are kept inside the slice loop (fresh_uniform):
+// held in scalar registers across it, they spilled 166 of them to vector
+// lanes (64-byte word rows; now 43) and cost more than the mixed rows' loads.
+// Measured before and after, us per step: 24-site ring, 20 float32 columns 287
+// and 280; 20-site sawtooth chain, all sectors, 20 float64 columns, one
+// sub-tile of 4 waves, 232 and 174; eight random clusters, 32 float32 columns
+// in blocks of 8, 1302 and 1070.
 //
 // Why nw > 1: the far high-high partners of a row are re-read from the L2
 // only while their rows are still there.  The rows in use at any time span
@@ -188,7 +198,7 @@ __device__ __forceinline__ RowIn<T, CPL, RES> load_row(__amdgpu_buffer_rsrc_t rh
 // Word-table layout (one row of WB bytes per low word, indexed by the word's
 // position koff[k] + i in the class-ordered list):
 //   bytes 0..7       low-low part of the diagonal, sum_b (+-) J_b/(4a), float64
-//   bytes 8..9       the low word l
+//   bytes 8..9       bit q: the low site's bit of mixed bond q
 //   bytes 12..       per mixed bond: colex rank of l ^ m_low (u16)
 //   bytes kLlOff..   per low-low bond: LDS row of the neighbour (1 + its member
 //                    index) when the bond acts on l, else 0 (u8)
@@ -229,11 +239,12 @@ __global__ __launch_bounds__(kThreads) void slice_words_kernel(const ProbDev* pr
     __builtin_memcpy(&db, &d, 8);
     dw[0] = (uint32_t)db;
     dw[1] = (uint32_t)(db >> 32);
-    dw[2] = l;
     const uint32_t lmask = (1u << Lb) - 1u;
     const int mx0 = P.n_ll + P.n_hh;
     for (int q = 0; q < P.n_mx; ++q) {
-      const uint32_t r = lrank[l ^ (cm[mx0 + q] & lmask)];
+      const uint32_t m = cm[mx0 + q] & lmask;
+      dw[2] |= (l & m) ? 1u << q : 0u;
+      const uint32_t r = lrank[l ^ m];
       const int byte = 12 + 2 * q;
       dw[byte >> 2] |= r << ((byte & 3) * 8);
     }
@@ -255,26 +266,28 @@ hipError_t build_slice_words(const DevicePlan& p, uint8_t* wtab, hipStream_t st)
   return hipGetLastError();
 }
 
-// LDS of the slice kernel: the low-low coefficients of the tile's problem
-// (kLlMax doubles, zero past its count), then the rows of the largest block
+// LDS of the slice kernel: the low-low and mixed coefficients of the tile's
+// problem (kSliceCoef bytes, zero past their counts), then the rows of the largest block
 // (at most 254 members, storage precision) after the zero row.
 constexpr int kLlMax = 32;
+constexpr int kMxMax = 12;
+constexpr size_t kSliceCoef = (kLlMax + 2 * kMxMax) * 8;
 
 size_t slice_lds_bytes(const DevicePlan& p) {
   const size_t rowb = (size_t)p.ld_max * (p.fp32 ? 4 : 8);
   // nw > 1: one buffer of the largest tile's rows after the zero row, then
   // each wave's partial dots (2 ld doubles per wave)
   if (p.slice_nw > 1 && p.resid)   // decoded float64 rows, staged through registers
-    return (size_t)kLlMax * 8 + (size_t)(p.slice_tile_rows + 1) * p.ld_max * 8 + (size_t)p.slice_nw * 2 * p.ld_max * 8;
+    return kSliceCoef + (size_t)(p.slice_tile_rows + 1) * p.ld_max * 8 + (size_t)p.slice_nw * 2 * p.ld_max * 8;
   if (p.slice_nw > 1)
-    return (size_t)kLlMax * 8 + rowb + ((size_t)p.slice_tile_rows * rowb + 1023) / 1024 * 1024 +
+    return kSliceCoef + rowb + ((size_t)p.slice_tile_rows * rowb + 1023) / 1024 * 1024 +
            (size_t)p.slice_nw * 2 * p.ld_max * 8;
   // rows of a multiple of 16 bytes: two buffers for direct staging, each the
   // zero row plus the largest block rounded up to whole 1 KB loads
   if (!p.resid && rowb % 16 == 0)
-    return (size_t)kLlMax * 8 + 2 * (rowb + ((size_t)p.blk_lds_rows * rowb + 1023) / 1024 * 1024);
+    return kSliceCoef + 2 * (rowb + ((size_t)p.blk_lds_rows * rowb + 1023) / 1024 * 1024);
   // float32 + residual storage: the block's rows are staged decoded (float64)
-  return (size_t)kLlMax * 8 + (size_t)(p.blk_lds_rows + 1) * p.ld_max * (p.fp32 && !p.resid ? 4 : 8);
+  return kSliceCoef + (size_t)(p.blk_lds_rows + 1) * p.ld_max * (p.fp32 && !p.resid ? 4 : 8);
 }
 
 template <int WB>
@@ -364,8 +377,7 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
 #pragma unroll
     for (int e = 0; e < CPL; ++e) ysc[e] = a.yscale[U.col_off + cc + e];
   }
-  const int Lb = P.blk_L, nll = P.n_ll, nhh = P.n_hh, nmx = P.n_mx;
-  const uint32_t lmask = (1u << Lb) - 1u;
+  const int nll = P.n_ll, nhh = P.n_hh, nmx = P.n_mx;
 
   T* base = reinterpret_cast<T*>(a.vec) + U.vec_off;
   const T* X = base + a.x_slot * a.slot_stride;
@@ -388,18 +400,15 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
     rol = make_rsrc(lbase + a.yout_slot * a.slot_stride, slot_bytes / 2);
   }
 
-  // bonds in class order (padded with zeros past the last problem)
-  const cptr<uint32_t> cm = cview(a.cmask) + P.bond_off;
-  const cptr<double> co = cview(a.coff) + P.bond_off;
-  const cptr<double> cz = cview(a.czz) + P.bond_off;
-
-  // LDS: low-low coefficients, then the staged rows of v_n ([1 + members][LD],
+  // LDS: low-low and mixed coefficients (zeros past the counts), then the staged rows of v_n ([1 + members][LD],
   // row 0 = 0).  Rows of a multiple of 16 bytes are staged by direct
   // buffer-to-LDS loads into two buffers, the next block's while the current
   // one is computed; other rows go through registers into one buffer.
   constexpr bool DIRECT = !RES && (ROWB % 16u == 0u);
   double* lco = reinterpret_cast<double*>(smem);
-  LT* xs0 = reinterpret_cast<LT*>(lco + kLlMax);
+  double* lmo = lco + kLlMax;            // mixed bonds: J_b/(2a)
+  double* lmz = lmo + kMxMax;            // ... J_b/(4a)
+  LT* xs0 = reinterpret_cast<LT*>(lmz + kMxMax);
   // (nw > 1 with rows staged through registers: the zero row and the tile's rows)
   const int buf_elems = DIRECT ? (int)(LD + (((uint32_t)a.blk_lds_rows * ROWB + 1023u) / 1024u) * 1024u / sizeof(T))
                                : (NW > 1 ? LD + a.blk_lds_rows * LD : 0);
@@ -412,6 +421,10 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
       if constexpr (DIRECT && NW == 1) xs1[e] = LT(0);
     }
     for (int q = lane; q < kLlMax; q += 64) lco[q] = q < nll ? a.coff[P.bond_off + q] : 0.0;
+    for (int q = lane; q < kMxMax; q += 64) {
+      lmo[q] = q < nmx ? a.coff[P.bond_off + nll + nhh + q] : 0.0;
+      lmz[q] = q < nmx ? a.czz[P.bond_off + nll + nhh + q] : 0.0;
+    }
   }
   // a run of rows, contiguous in v_n, to LDS rows 1.. of buf: 1 KB per
   // instruction (lane i writes bytes 16i..16i+15 of the instruction's 1 KB);
@@ -459,9 +472,19 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
         }
       }
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
   }
+  // nw > 1: the one barrier after staging comes once the wave's first slice
+  // has requested its rows (or at the end, for a wave without a slice), so
+  // that their latency runs beside the staging's: with few slices per wave
+  // that is one round trip less in a wave's short life
+  bool staged = NW == 1;
+  auto stage_done = [&]() {
+    if constexpr (NW > 1) {
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      staged = true;
+    }
+  };
   auto valid = [&](const SliceBlk& b) {
     if constexpr (NW > 1) return tile_ok && b.size != 0u;
     return b.size != 0u && (int)b.size <= a.blk_lds_rows;
@@ -492,7 +515,6 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
         wave_sync();
         if (g + 1 < gend && valid(Bn)) stage_direct(Bn, ((g + 1 - R.g0) & 1) ? xs1 : xs0);
       }
-      const uint32_t h = B.h;
       const uint32_t st = B.start;
       const int bsz = (int)B.size;
       const int nsl = (bsz + RPS - 1) / RPS;
@@ -562,6 +584,7 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
         }
       };
       for (int s = s_first; s < nsl; s += NW) {
+        const int nll = fresh_uniform(P.n_ll), nmx = fresh_uniform(P.n_mx);
         const int i = s * RPS + rl;
         const bool on = i < bsz;
         const uint32_t ii = on ? (uint32_t)i : 0u;
@@ -587,25 +610,19 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
           bstore_nt<T, CPL>(ro, pend_off, pend.v);
           if constexpr (RES) bstore_lo_nt<CPL>(rol, pend_off >> 1, pend.lo);
         }
+        if (!staged) stage_done();
 
-        const uint32_t l = w[2] & 0xFFFFu;
         double dll;
         {
           const uint64_t db = (uint64_t)w[0] | ((uint64_t)w[1] << 32);
           __builtin_memcpy(&dll, &db, 8);
         }
         // mixed bonds act where their low and high sites differ
-        bool mact[RowT::kMx];
+        uint32_t mact = (w[2] & 0xFFFFu) ^ B.hmx;
         double d = dhh + dll;
 #pragma unroll
-        for (int q = 0; q < RowT::kMx; ++q) {
-          mact[q] = false;
-          if (q < nmx) {
-            const uint32_t m = cm[nll + nhh + q];
-            mact[q] = ((l & m & lmask) != 0u) != ((h & (m >> Lb)) != 0u);
-            d = fma(mact[q] ? -1.0 : 1.0, cz[nll + nhh + q], d);
-          }
-        }
+        for (int q = 0; q < RowT::kMx; ++q)
+          if (q < nmx) d = fma((mact >> q) & 1u ? -1.0 : 1.0, lmz[q], d);
         double acc[CPL];
         {
           const VecT<LT, CPL> xv = *reinterpret_cast<const VecT<LT, CPL>*>(xs + (1 + xbase + ii) * LD + cc);
@@ -635,19 +652,17 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
           }
         }
         // mixed rows (requested now; their latency overlaps the high-high sums)
-        RowIn<T, CPL, RES> mv[2];
+        constexpr int MB = RowT::kMx > 2 ? 4 : 2;
+        RowIn<T, CPL, RES> mv[MB];
+        mact = fresh(mact);
         auto mx_issue = [&](int q0) {
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
+          for (int u = 0; u < MB; ++u) {
             const int q = q0 + u;
             uint32_t row = own;
-            if (q < nmx && q < RowT::kMx) {
-              const uint32_t stq = ms[q];
-              if (mact[q] && stq == kNoRun) {
-                if (a.err) atomicOr(a.err, 2);
-                mact[q] = false;
-              }
-              if (mact[q]) row = stq + row_u16<WB>(w, 12 + 2 * q);
+            if (q < RowT::kMx) {
+              const uint32_t r = ms[q] + row_u16<WB>(w, 12 + 2 * q);   // acting: its target block exists
+              row = (mact >> q) & 1u ? r : own;
             }
             mv[u] = load_row<T, CPL, RES, 0>(rx, rxl, row * ROWB + cc * (uint32_t)sizeof(T), 0);
           }
@@ -675,16 +690,18 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
           }
         }
 #pragma unroll
-        for (int q0 = 0; q0 < RowT::kMx; q0 += 2) {
+        for (int q0 = 0; q0 < RowT::kMx; q0 += MB) {
           if (q0 < nmx) {
+            mact = fresh(mact);
             if (q0 > 0) mx_issue(q0);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
+            for (int u = 0; u < MB; ++u) {
               const int q = q0 + u;
-              const double cq = co[nll + nhh + q];
-              const double cf = (q < nmx && mact[q]) ? cq : 0.0;
+              if (q < RowT::kMx) {
+                const double cf = (mact >> q) & 1u ? lmo[q] : 0.0;
 #pragma unroll
-              for (int e = 0; e < CPL; ++e) acc[e] = fma(cf, row_val(mv[u], e), acc[e]);
+                for (int e = 0; e < CPL; ++e) acc[e] = fma(cf, row_val(mv[u], e), acc[e]);
+              }
             }
           }
         }
@@ -727,6 +744,7 @@ __global__ __launch_bounds__(64 * NW) void slice_kernel(const StepArgs a) {
       wave_sync();
     }
   }
+  if (!staged) stage_done();
 
   // dots: the lanes' sums over the member bits not folded per slice (fixed
   // order); lane l < 2 CPL * NCH then holds chunk l % NCH's value of index

@@ -167,4 +167,16 @@ __device__ __forceinline__ double lane_xor(double x) {
   return __hiloint2double(hi, lo);
 }
 
+// The value as one that may change from here on: keeps the compiler from
+// moving what depends on it (unpacked indices, addresses, branch conditions,
+// lane masks) out of a loop, where it would be spilled.
+__device__ __forceinline__ uint32_t fresh(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ int fresh_uniform(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 }  // namespace kpm
