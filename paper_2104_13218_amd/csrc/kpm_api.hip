@@ -224,6 +224,7 @@ struct Tune {
   int lds_x = -1;         // block-table kernel: 1 rows of v_n staged in LDS, 0 not, -1 heuristic
   int rows = 0;           // slice kernel: rows per sub-tile (0 = heuristic)
   int waves = 0;          // slice kernel: waves per workgroup (0 = heuristic)
+  int blk_max = 0;        // slice kernel: blocks per sub-tile (0 = 64)
 };
 
 struct RunShape {
@@ -236,6 +237,7 @@ struct RunShape {
   bool allow_row = true;  // the row kernel may run the recursion
   bool split_vectors = false;  // complex vectors may be split across blocks (one column each)
   bool allow_relabel = true;   // block kernels may relabel sites (rows then in relabelled order)
+  bool allow_slice = true;     // large sectors may take the slice kernel by default (large_slice)
 };
 
 constexpr int kAdjMaxLd = 16;
@@ -524,8 +526,71 @@ void apply_scale(const kpm_problem* p, int n, const double* a_arr, const double*
     }
 }
 
+// Sectors from kSliceRows on have tiles enough to give every wave several
+// slices (two sub-tiles per workgroup: 24-site ring, 20 float32 columns, 281
+// against 290 us); below, one sub-tile.
+constexpr int64_t kSliceRows = int64_t(1) << 21;
+// Below this the recursion is bound by the chain of loads inside one step
+// (13-15 us either way) and keeps the row and block-table kernels.
+constexpr int64_t kSliceLeast = int64_t(1) << 15;
+
+int64_t largest_sector(const kpm_problem* p, int n) {
+  int64_t d = 0;
+  for (int i = 0; i < n; ++i) d = std::max<int64_t>(d, (int64_t)prob_dim(p[i]));
+  return d;
+}
+
+// The slice kernel's launch shape for these problems.  At most four blocks a
+// sub-tile: in sectors of high S^z a block has few members, and a tile of 64
+// of them kept one wave busy for 60 us while the chip waited (20-site sawtooth
+// chain, all sectors, 20 float64 columns: 197 us per step with up to 64
+// blocks, 137 with 4; one column 181 and 20).
+Tune slice_tune(const kpm_problem* p, int n, int precision, int L) {
+  Tune t;
+  const bool large = largest_sector(p, n) >= kSliceRows;
+  t.kernel = 5;
+  t.col_block = precision == KPM_FP32_STORE && !large ? 8 : 4;
+  t.block_L = L;
+  t.spt = large ? 2 : 1;
+  t.gather_batch = 4;
+  t.waves = large && precision == KPM_FP64 ? 4 : 2;
+  t.blk_max = 4;
+  return t;
+}
+
+int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double* a_arr,
+                    const double* b_arr, Planned& P);
+
+// The plan of a run.  Where nobody chose a kernel or a block width, spin-1/2
+// sectors from kSliceLeast on take the slice kernel, with 10 low bits or else 9
+// (a word row holds so many bonds), and the planner's heuristic where neither
+// fits.  Per step, slice kernel against what ran before: 30-site 4-regular
+// graph, 4 float32 columns, 9.2 against 23.3 ms (row kernel); 24-site ring, 20
+// float64 columns, 505 against 961 us (block-table kernel); 20-site sawtooth
+// chain, all sectors, 20 float64 columns, 129 against 230 us, 20 float32
+// columns, 94 against 109; 20-site J1-J2 chain, S^z = 0, 16 float64 columns,
+// 42 against 63; 18-site ladder, all sectors, 1 to 20 float64 columns, 13-35
+// against 15-88.
 int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_arr,
               const double* b_arr, Planned& P) {
+  if (s.allow_slice && !s.adjoint && s.tune.kernel < 0 && s.tune.col_block == 0 && s.col_block == 0 &&
+      s.precision != KPM_FP32R_STORE && largest_sector(p, n) >= kSliceLeast && !any_spin(p, n) &&
+      !std::getenv("KPM_BLOCK") && !std::getenv("KPM_ROW_KERNEL") && !std::getenv("KPM_BLOCK_L")) {
+    for (int L : {10, 9}) {
+      RunShape t = s;
+      t.tune = slice_tune(p, n, s.precision, L);
+      Planned Q;
+      if (make_plan_shape(p, n, t, a_arr, b_arr, Q) == KPM_OK && Q.plan.block == 3) {
+        P = std::move(Q);
+        return KPM_OK;
+      }
+    }
+  }
+  return make_plan_shape(p, n, s, a_arr, b_arr, P);
+}
+
+int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double* a_arr,
+                    const double* b_arr, Planned& P) {
   const int resid = s.precision == KPM_FP32R_STORE;
   const int fp32 = s.precision == KPM_FP32_STORE || resid;
   int rb = pick_col_block(p, n, s);
@@ -676,7 +741,7 @@ int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_ar
   if (!spin && !s.adjoint && s.allow_row && (block_env == 1 || tab || (block_env < 0 && block_default))) {
     D.ld_max = adj_ld ? adj_ld : (rb + cpl - 1) / cpl * cpl;
     // slice kernel: one lane per block of a sub-tile in its table pass (<= 64)
-    D.blk_max = slice ? std::max(1, std::min(64, env_int("KPM_BLOCK_MAX", 64)))
+    D.blk_max = slice ? std::max(1, std::min(64, env_int("KPM_BLOCK_MAX", s.tune.blk_max > 0 ? s.tune.blk_max : 64)))
                       : std::max(1, std::min(255, env_int("KPM_BLOCK_MAX", 16)));
     const size_t cap = (size_t)env_int("KPM_BLOCK_LDS", 64 * 1024);
     // rows of v_n staged in LDS: measured faster for float32 storage only
@@ -854,7 +919,7 @@ int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_ar
   D.sub_per_tile = spt;
   // slice kernel: every XCD on the same column block at a time (measured 4 %
   // faster on the 24-site ring than contiguous tile ranges per XCD)
-  D.xcd_remap = env_int("KPM_XCD_REMAP", D.block == 3 ? 2 : 1);
+  D.xcd_remap = env_int("KPM_XCD_REMAP", D.block == 3 ? -1 : 1);
   D.dense = env_int("KPM_DENSE_LISTS", 0);
   const int64_t tile_rows = (int64_t)D.sub_rows * spt;
 
@@ -958,8 +1023,8 @@ int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_ar
   D.n_tiles = tiles;
   D.grid_tiles = (tiles + 7) / 8 * 8;
   // Slice kernel: one record per workgroup (its tile, column block, problem
-  // and block range).  KPM_XCD_REMAP=2 (default): each column block's tiles
-  // in 8 contiguous chunks, chunk x to XCD x (workgroup b runs on XCD b mod
+  // and block range).  KPM_XCD_REMAP=3: each column block on one XCD; 2: each
+  // column block's tiles in 8 contiguous chunks, chunk x to XCD x (workgroup b runs on XCD b mod
   // 8), column blocks one after the other, so that all XCDs sweep the same
   // column block at a time; 1: contiguous tile ranges per XCD; 0: in order.
   P.wg_rec.clear();
@@ -979,7 +1044,38 @@ int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_ar
       }
       return w;
     };
-    if (D.xcd_remap == 2) {
+    if (D.xcd_remap < 0 || D.xcd_remap == 3) {
+      // each column block on one XCD, the largest first to the least loaded
+      std::vector<int> order(P.units.size());
+      for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
+      std::stable_sort(order.begin(), order.end(),
+                       [&](int x, int y) { return P.units[x].ntiles > P.units[y].ntiles; });
+      std::vector<int32_t> queue[8];
+      for (int k : order) {
+        int x = 0;
+        for (int c = 1; c < 8; ++c)
+          if (queue[c].size() < queue[x].size()) x = c;
+        for (int t = 0; t < P.units[k].ntiles; ++t) queue[x].push_back(P.units[k].tile0 + t);
+      }
+      size_t len = 0;
+      for (auto& q : queue) len = std::max(len, q.size());
+      // its rows are then fetched into one L2 instead of eight; taken where
+      // no XCD gets over 5 % more than the mean and a slot is of the size it
+      // was measured at (20-site sawtooth chain, 55 blocks: 129 against 137
+      // us; eight random clusters, 228 blocks of up to 23 MB: 958 against
+      // 978; with 22 blocks, unevenly, 61 against 59)
+      if (D.xcd_remap < 0)
+        D.xcd_remap = (double)len * 8 <= 1.05 * tiles &&
+                              largest_sector(p, n) * D.ld_max * elt <= (int64_t(24) << 20)
+                          ? 3
+                          : 2;
+      if (D.xcd_remap == 3)
+        for (size_t j = 0; j < len; ++j)
+          for (auto& q : queue) P.wg_rec.push_back(rec(j < q.size() ? q[j] : -1));
+    }
+    if (D.xcd_remap == 3) {
+      // done above
+    } else if (D.xcd_remap == 2) {
       for (const UnitDev& u : P.units) {
         const int c = (u.ntiles + 7) / 8;
         for (int j = 0; j < c; ++j)
@@ -1164,27 +1260,35 @@ LzLayout lanczos_layout(const Planned& P, int steps) {
   return L;
 }
 
-// Lanczos bounds: one float64 column per problem, on the slice kernel for
-// spin-1/2 problems (the planner falls back to the other kernels where it
-// does not apply)
-RunShape lanczos_shape(const kpm_problem* p, int n) {
+// Lanczos bounds: one float64 column per problem.  Spin-1/2 problems take the
+// slice kernel in slice_tune's shape; `reference`: in the shape of large
+// sectors with up to 64 blocks per sub-tile, whose order of summation decides
+// the windows that hang on rounding (settle_bounds) and which large sectors
+// keep.
+RunShape lanczos_shape(const kpm_problem* p, int n, bool reference) {
   RunShape s;
   s.precision = KPM_FP64;
   s.vec_kind = KPM_VEC_RADEMACHER;
   s.R = 1;
   s.col_block = 1;
+  s.allow_slice = false;
   if (!any_spin(p, n)) {
-    s.tune.kernel = 5;
-    s.tune.block_L = 10;
-    s.tune.spt = 2;
-    s.tune.gather_batch = 4;
+    if (reference || largest_sector(p, n) >= kSliceRows) {
+      s.tune.kernel = 5;
+      s.tune.block_L = 10;
+      s.tune.spt = 2;
+      s.tune.gather_batch = 4;
+    } else {
+      s.tune = slice_tune(p, n, KPM_FP64, 10);
+      s.tune.col_block = 0;
+    }
   }
   return s;
 }
 
-size_t stepped_lanczos_bytes(const kpm_problem* p, int n, int steps) {
+size_t stepped_lanczos_bytes(const kpm_problem* p, int n, int steps, bool reference) {
   Planned P;
-  if (make_plan(p, n, lanczos_shape(p, n), nullptr, nullptr, P) != KPM_OK) return 0;
+  if (make_plan(p, n, lanczos_shape(p, n, reference), nullptr, nullptr, P) != KPM_OK) return 0;
   return lanczos_layout(P, steps).total;
 }
 
@@ -1225,6 +1329,36 @@ void tri_extremes(const std::vector<double>& a, const std::vector<double>& b, do
   hi = kth(n - 1);
 }
 
+// Whether the window [lo, hi] of the tridiagonal (al, be) hangs on the
+// rounding of the recursion that gave it: an end that has not converged (two
+// steps less move it by 1e-11 of the width) while the Lanczos vectors lost
+// their orthogonality to 1e-4 by Simon's recurrence for <q_j, q_k> (the same
+// test as in kpm_resident.hip).
+bool hangs_on_rounding(const std::vector<double>& al, const std::vector<double>& be, double lo, double hi) {
+  const int L = (int)al.size();
+  if (L < 3) return false;
+  const double W = hi - lo;
+  const std::vector<double> a2(al.begin(), al.end() - 2), b2(be.begin(), be.begin() + (L - 3));
+  if (tri_count_below(a2, b2, lo + 1e-11 * W) > 0 && tri_count_below(a2, b2, hi - 1e-11 * W) < L - 2) return false;
+  const double ulp = 1.1e-16;
+  std::vector<double> prev(L + 1, 0.0), cur(L + 1, 0.0), nxt(L + 1, 0.0);
+  cur[0] = 1.0;
+  double top = 0.0;
+  for (int j = 0; j + 1 < L; ++j) {
+    for (int k = 0; k < j; ++k) {
+      double v = be[k] * cur[k + 1] + (al[k] - al[j]) * cur[k] - be[j - 1] * prev[k];
+      if (k > 0) v += be[k - 1] * cur[k - 1];
+      nxt[k] = (v + std::copysign(2.0 * ulp * W, v)) / be[j];
+      top = std::max(top, std::fabs(nxt[k]));
+    }
+    nxt[j] = 30.0 * ulp * be[0] / be[j];
+    nxt[j + 1] = 1.0;
+    std::swap(prev, cur);
+    std::swap(cur, nxt);
+  }
+  return top > 1e-4;
+}
+
 // Lanczos recursion, every column its own (the spectral bounds of Eqs. (4)-(5)
 // below and the FTLM that Sec. III.C compares against), on
 // a plan of H' = H/2 whose two slots hold the unit start columns (slot 0) and
@@ -1259,11 +1393,14 @@ int lanczos_turns(const DevicePlan& D, double* vec, double* part, double* dots, 
 
 // Batched Lanczos over every problem (one float64 column each), the recursion
 // of lanczos_turns on H' = H/2.
+// `reference` as in lanczos_shape; unstable (may be NULL): per problem, 1
+// where the window hangs on rounding.
 int stepped_lanczos(const kpm_problem* p, int n, int steps, double margin, uint64_t seed,
-                    double* e_lo_hi, unsigned char* work, hipStream_t st) {
+                    double* e_lo_hi, unsigned char* work, hipStream_t st, bool reference,
+                    std::vector<int32_t>* unstable) {
   Planned P;
   const std::vector<double> two(n, 2.0), zero_b(n, 0.0);
-  int r = make_plan(p, n, lanczos_shape(p, n), two.data(), zero_b.data(), P);
+  int r = make_plan(p, n, lanczos_shape(p, n, reference), two.data(), zero_b.data(), P);
   if (r != KPM_OK) return r;
   for (auto& u : P.units) u.col0 = 1023;   // RNG stream r = 1023 for the start vector
   int64_t max_dim = 1;
@@ -1312,6 +1449,10 @@ int stepped_lanczos(const kpm_problem* p, int n, int steps, double margin, uint6
     double lo, hi;
     tri_extremes(av, bv, lo, hi);
     const double W = hi - lo;
+    if (unstable) {
+      const bool exhausted = (int)av.size() < steps_i;
+      (*unstable)[i] = !exhausted && hangs_on_rounding(av, bv, lo, hi);
+    }
     if (W < 1e-8 * std::max({1.0, std::fabs(lo), std::fabs(hi)})) {
       e_lo_hi[2 * i] = lo - 0.5;
       e_lo_hi[2 * i + 1] = hi + 0.5;
@@ -1544,9 +1685,8 @@ struct Spare {
   bool may_alloc;
 };
 
-// The windows that the resident recursion reported as hanging on rounding,
-// once more by the stepped recursion, whose values these calls have always
-// had.  e_lo_hi [n][2] holds the others already.
+// The windows reported as hanging on rounding, once more by the reference
+// recursion, whose values these calls have always had.  e_lo_hi [n][2] holds the others already.
 int settle_bounds(const kpm_problem* p, int n, const std::vector<int32_t>& unstable, int steps, double margin,
                   uint64_t seed, double* e_lo_hi, const Spare& mem, hipStream_t st) {
   std::vector<kpm_problem> sub;
@@ -1556,7 +1696,7 @@ int settle_bounds(const kpm_problem* p, int n, const std::vector<int32_t>& unsta
       sub.push_back(p[i]);
       at.push_back(i);
     }
-  const size_t need = stepped_lanczos_bytes(sub.data(), (int)sub.size(), steps);
+  const size_t need = stepped_lanczos_bytes(sub.data(), (int)sub.size(), steps, true);
   if (need == 0) return KPM_EINVAL;
   DevBuf own;
   unsigned char* work = mem.work;
@@ -1567,7 +1707,8 @@ int settle_bounds(const kpm_problem* p, int n, const std::vector<int32_t>& unsta
     work = static_cast<unsigned char*>(own.p);
   }
   std::vector<double> got(2 * sub.size());
-  const int r = stepped_lanczos(sub.data(), (int)sub.size(), steps, margin, seed, got.data(), work, st);
+  const int r =
+      stepped_lanczos(sub.data(), (int)sub.size(), steps, margin, seed, got.data(), work, st, true, nullptr);
   if (r != KPM_OK) return r;
   for (size_t k = 0; k < at.size(); ++k) {
     e_lo_hi[2 * at[k]] = got[2 * k];
@@ -1578,15 +1719,21 @@ int settle_bounds(const kpm_problem* p, int n, const std::vector<int32_t>& unsta
 
 size_t lanczos_bytes(const kpm_problem* p, int n, int steps) {
   if (steps <= kResLanczos && resident_problems(p, n)) return res_layout(p, n, 0, 0, n).total;
-  return stepped_lanczos_bytes(p, n, steps);
+  return stepped_lanczos_bytes(p, n, steps, false);
 }
 
 // Windows of every problem, estimated (their own bounds are not used), in
 // lanczos_bytes() bytes at mem.work (mem.bytes are at hand there).
 int run_lanczos(const kpm_problem* p, int n, int steps, double margin, uint64_t seed, double* e_lo_hi,
                 const Spare& mem, hipStream_t st) {
-  if (steps > kResLanczos || !resident_problems(p, n))
-    return stepped_lanczos(p, n, steps, margin, seed, e_lo_hi, mem.work, st);
+  if (steps > kResLanczos || !resident_problems(p, n)) {
+    // spin-s plans and large sectors have one recursion, their own reference
+    std::vector<int32_t> unstable(n, 0);
+    const bool check = !any_spin(p, n) && largest_sector(p, n) < kSliceRows;
+    const int r = stepped_lanczos(p, n, steps, margin, seed, e_lo_hi, mem.work, st, false, check ? &unstable : nullptr);
+    if (r != KPM_OK || std::find(unstable.begin(), unstable.end(), 1) == unstable.end()) return r;
+    return settle_bounds(p, n, unstable, steps, margin, seed, e_lo_hi, mem, st);
+  }
   std::vector<kpm_problem> open(p, p + n);
   for (auto& o : open) o.e_lo = o.e_hi = NAN;
   kpm_params q{};
@@ -2247,6 +2394,7 @@ bool forward_plan_for(const kpm_problem* p, int n, const kpm_params& q, const Pl
   if (env_int("KPM_ADJ_FWD", 1) == 0 || P.units.empty()) return false;
   RunShape s = shape_of(q);
   s.allow_relabel = false;
+  s.allow_slice = false;
   s.col_block = P.units[0].ncols;
   if (make_plan(p, n, s, a, b, F) != KPM_OK) return false;
   if (F.units.size() != P.units.size() || F.plan.slot_stride != P.plan.slot_stride || F.plan.fp32 != P.plan.fp32)
@@ -2648,20 +2796,18 @@ struct FtlmLayout {
 // blocks like the Chebyshev recursion (q->col_block, 0 = the planner's width;
 // width 1 splits a complex vector's Re and Im into separate blocks).
 // FTLM runs float64 vectors.  Without a requested block width, spin-1/2
-// problems take the slice kernel on blocks of 4 columns, 2 sub-tiles per
-// tile, 4 high-high rows in flight (ring N=24, 20 columns, 200 steps: 195 ms
-// per call, 201 ms on blocks of 2, 301 ms with the planner's block-table
-// default); the planner falls back where no slice plan exists.
+// problems take the slice kernel on blocks of 4 columns (ring N=24, 20
+// columns, 200 steps: 195 ms per call, 201 ms on blocks of 2, 301 ms with the
+// block-table kernel); the planner falls back where no slice plan exists.
 RunShape ftlm_shape(const kpm_params& q, const kpm_problem* p, int n) {
   RunShape s = shape_of(q);
   s.precision = KPM_FP64;
   s.split_vectors = q.col_block == 1;
+  s.allow_slice = false;
   if (q.col_block == 0 && !any_spin(p, n)) {
-    s.col_block = 4;
-    s.tune.kernel = 5;
-    s.tune.block_L = 10;
-    s.tune.spt = 2;
-    s.tune.gather_batch = 4;
+    s.tune = slice_tune(p, n, KPM_FP64, 10);
+    s.tune.waves = 2;
+    s.col_block = s.tune.col_block;
   }
   return s;
 }
