@@ -2718,6 +2718,7 @@ struct ThermoDev {
   DevBuf buf;
   double* g = nullptr;
   double* gamma = nullptr;
+  double* enode = nullptr;
   double* stats = nullptr;
   double* adj = nullptr;
   ThermoProb* tp = nullptr;
@@ -2736,6 +2737,7 @@ int thermo_forward(const double* d_mu, const double* d_ab, const kpm_problem* p,
   int r = thermo_meta(p, n, tp, start, list, n_clusters);
   if (r != KPM_OK) return r;
   const int Nt = n_nodes ? n_nodes : M;
+  const int chunk = thermo_chunk(n, n_T);
   size_t o = 0;
   auto put = [&](size_t bytes) {
     const size_t rr = o;
@@ -2743,7 +2745,8 @@ int thermo_forward(const double* d_mu, const double* d_ab, const kpm_problem* p,
     return rr;
   };
   const size_t og = put((size_t)M * 8), ogam = put((size_t)n * Nt * 8),
-               ost = put((size_t)n_clusters * n_T * 6 * 8),
+               oen = put((size_t)n * Nt * 8), osum = put((size_t)n * chunk * sizeof(SectorSums)),
+               osame = put((size_t)chunk * 4), ost = put((size_t)n_clusters * n_T * 6 * 8),
                oadj = put(keep_adj ? (size_t)n * Nt * 8 : 8), otp = put(tp.size() * sizeof(ThermoProb)),
                ostart = put(start.size() * 4), olist = put(list.size() * 4);
   r = TD.buf.alloc(o);
@@ -2751,6 +2754,7 @@ int thermo_forward(const double* d_mu, const double* d_ab, const kpm_problem* p,
   unsigned char* w = static_cast<unsigned char*>(TD.buf.p);
   TD.g = reinterpret_cast<double*>(w + og);
   TD.gamma = reinterpret_cast<double*>(w + ogam);
+  TD.enode = reinterpret_cast<double*>(w + oen);
   TD.stats = reinterpret_cast<double*>(w + ost);
   TD.adj = reinterpret_cast<double*>(w + oadj);
   TD.tp = reinterpret_cast<ThermoProb*>(w + otp);
@@ -2760,13 +2764,15 @@ int thermo_forward(const double* d_mu, const double* d_ab, const kpm_problem* p,
   KPM_HIP(hipMemcpyAsync(TD.start, start.data(), start.size() * 4, hipMemcpyHostToDevice, st));
   KPM_HIP(hipMemcpyAsync(TD.list, list.data(), list.size() * 4, hipMemcpyHostToDevice, st));
   KPM_HIP(launch_kernel_coef(M, kernel, TD.g, st));
-  KPM_HIP(launch_gamma(n, M, Nt, TD.g, d_mu, TD.gamma, st));
+  KPM_HIP(launch_gamma(n, M, Nt, TD.g, d_mu, d_ab, TD.gamma, TD.enode, st));
   ThermoArgs ta{};
   ta.tp = TD.tp;
   ta.cl_start = TD.start;
   ta.cl_list = TD.list;
   ta.gamma = TD.gamma;
-  ta.ab = d_ab;
+  ta.enode = TD.enode;
+  ta.sums = reinterpret_cast<SectorSums*>(w + osum);
+  ta.same = reinterpret_cast<int32_t*>(w + osame);
   ta.T = d_T;
   ta.lnZ = lnZ;
   ta.E = E;
@@ -2777,10 +2783,10 @@ int thermo_forward(const double* d_mu, const double* d_ab, const kpm_problem* p,
   ta.n_nodes = Nt;
   ta.n_T = n_T;
   ta.n_clusters = n_clusters;
+  ta.n_probs = n;
   ta.h = d_h;
   ta.mag = d_mag;
-  if (d_h) KPM_HIP(launch_thermo_field(ta, st));
-  else KPM_HIP(launch_thermo(ta, st));
+  KPM_HIP(launch_thermo(ta, st));
   // the host staging vectors die with the caller's frame: finish the copies now
   KPM_HIP(hipStreamSynchronize(st));
   return KPM_OK;
@@ -3362,7 +3368,7 @@ int kpm_thermo_vjp(const double* d_mu, const double* d_ab, const kpm_problem* p,
     if (r != KPM_OK) return r;
     ThermoVjpArgs va{};
     va.tp = TD.tp;
-    va.ab = d_ab;
+    va.enode = TD.enode;
     va.stats = TD.stats;
     va.wC = d_wC;
     va.wchi = d_wchi;
@@ -3827,6 +3833,7 @@ int kpm_thermo_hybrid(const double* d_mu, const double* d_ab, const kpm_problem*
     hipStream_t st = static_cast<hipStream_t>(stream);
     StreamSync guard{st};
     const int Nt = n_nodes ? n_nodes : M;
+    const int chunk = thermo_chunk(n, n_pts);
     size_t o = 0;
     auto put = [&](size_t bytes) {
       const size_t rr = o;
@@ -3834,6 +3841,8 @@ int kpm_thermo_hybrid(const double* d_mu, const double* d_ab, const kpm_problem*
       return rr;
     };
     const size_t og = put((size_t)M * 8), ogam = put((size_t)n * Nt * 8),
+                 oen = put((size_t)n * Nt * 8), osum = put((size_t)n * chunk * sizeof(SectorSums)),
+                 osame = put((size_t)chunk * 4),
                  otp = put(tp.size() * sizeof(ThermoProb)), ostart = put(start.size() * 4),
                  olist = put(list.size() * 4), ocnt = put(cnt.size() * 4);
     DevBuf buf;
@@ -3847,13 +3856,16 @@ int kpm_thermo_hybrid(const double* d_mu, const double* d_ab, const kpm_problem*
     double* g = reinterpret_cast<double*>(w + og);
     double* gamma = reinterpret_cast<double*>(w + ogam);
     KPM_HIP(launch_kernel_coef(M, kernel, g, st));
-    KPM_HIP(launch_gamma(n, M, Nt, g, d_mu, gamma, st));
+    double* enode = reinterpret_cast<double*>(w + oen);
+    KPM_HIP(launch_gamma(n, M, Nt, g, d_mu, d_ab, gamma, enode, st));
     ThermoArgs ta{};
     ta.tp = reinterpret_cast<const ThermoProb*>(w + otp);
     ta.cl_start = reinterpret_cast<const int32_t*>(w + ostart);
     ta.cl_list = reinterpret_cast<const int32_t*>(w + olist);
     ta.gamma = gamma;
-    ta.ab = d_ab;
+    ta.enode = enode;
+    ta.sums = reinterpret_cast<SectorSums*>(w + osum);
+    ta.same = reinterpret_cast<int32_t*>(w + osame);
     ta.T = d_T;
     ta.lnZ = d_lnZ;
     ta.E = d_E;
@@ -3863,12 +3875,13 @@ int kpm_thermo_hybrid(const double* d_mu, const double* d_ab, const kpm_problem*
     ta.n_nodes = Nt;
     ta.n_T = n_pts;
     ta.n_clusters = nc;
+    ta.n_probs = n;
     ta.h = d_h;
     ta.mag = d_mag;
     ta.ed_count = reinterpret_cast<const int32_t*>(w + ocnt);
     ta.evals = d_evals;
     ta.evals_ld = evals_ld;
-    KPM_HIP(launch_thermo_hybrid(ta, st));
+    KPM_HIP(launch_thermo(ta, st));
     KPM_HIP(hipStreamSynchronize(st));
     return KPM_OK;
   });

@@ -1,6 +1,5 @@
 // Exact spectra of small S^z sectors (Sec. II: a sector of small dimension is
-// diagonalised completely instead of being estimated stochastically) and the
-// thermodynamics that mix such spectra with the moments of the other sectors.
+// diagonalised completely instead of being estimated stochastically).
 //
 // The dense float64 matrix of H on each sector basis (rank order) is built in
 // the workspace and reduced to a symmetric tridiagonal matrix by Householder
@@ -322,92 +321,6 @@ hipError_t launch_sector_eig(const EigArgs& a, const int* dims, int n_sectors, s
   }
   hipLaunchKernelGGL(ed_tri_kernel, dim3(n_sectors), dim3(kThreads), 0, st, a);
   hipLaunchKernelGGL(ed_bisect_kernel, dim3(n_sectors, (dims[0] + 63) / 64), dim3(64), lds_finish, st, a);
-  return hipGetLastError();
-}
-
-// Thermodynamics at the points (T, h) of every cluster: a sector with an
-// exact spectrum (ed_count > 0) contributes its eigenvalues with weight Nt
-// each (the scale on which a dimension-D sector's gamma_k sum to Nt * D),
-// the others their nodes and gamma_k as in thermo_field_kernel.  Mirror
-// sectors, the shift by the lowest energy of the point and the centred
-// second passes as there.
-__global__ __launch_bounds__(kThreads) void thermo_hybrid_kernel(const ThermoArgs a) {
-  __shared__ double sh[4];
-  const int t = blockIdx.x, c = blockIdx.y;
-  const int Nt = a.n_nodes;
-  const int p0 = a.cl_start[c], p1 = a.cl_start[c + 1];
-  const double beta = 1.0 / a.T[t];
-  const double hf = a.h ? a.h[t] : 0.0;
-
-  double emin = INFINITY, s0 = 0.0, s1 = 0.0, s2 = 0.0, ve = 0.0, vm = 0.0;
-  double eref = 0.0, S0 = 0.0, Ebar = 0.0, Mbar = 0.0;
-  for (int pass = 0; pass < 3; ++pass) {
-    for (int qq = p0; qq < p1; ++qq) {
-      const int p = a.cl_list[qq];
-      const ThermoProb tp = a.tp[p];
-      const int ned = a.ed_count[p];
-      const int items = ned > 0 ? ned : Nt;
-      const int nm = tp.weight > 1.0 ? 2 : 1;
-      for (int i = threadIdx.x; i < items; i += kThreads) {
-        double E, g;
-        if (ned > 0) {
-          E = a.evals[(int64_t)p * a.evals_ld + i];
-          g = (double)Nt;
-        } else {
-          const double x = cos(M_PI * ((double)i + 0.5) / (double)Nt);
-          E = a.ab[2 * p] * x + a.ab[2 * p + 1];
-          g = a.gamma[(int64_t)p * Nt + i];
-        }
-        for (int j = 0; j < nm; ++j) {
-          const double m = j == 0 ? tp.sz : -tp.sz;
-          const double Et = E + hf * m;
-          if (pass == 0) {
-            emin = fmin(emin, Et);
-          } else {
-            const double wgt = g * exp(-beta * (Et - eref));
-            if (pass == 1) {
-              s0 += wgt;
-              s1 = fma(wgt, Et, s1);
-              s2 = fma(wgt, m, s2);
-            } else {
-              const double de = Et - Ebar, dm = m - Mbar;
-              ve = fma(wgt, de * de, ve);
-              vm = fma(wgt, dm * dm, vm);
-            }
-          }
-        }
-      }
-    }
-    if (pass == 0) {
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) emin = fmin(emin, __shfl_down(emin, off, 64));
-      const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-      __syncthreads();
-      if (lane == 0) sh[wv] = emin;
-      __syncthreads();
-      eref = fmin(fmin(sh[0], sh[1]), fmin(sh[2], sh[3]));
-      __syncthreads();
-    } else if (pass == 1) {
-      S0 = ed_sum(s0, sh);
-      Ebar = ed_sum(s1, sh) / S0;
-      Mbar = ed_sum(s2, sh) / S0;
-    }
-  }
-  const double VarE = ed_sum(ve, sh) / S0;
-  const double VarM = ed_sum(vm, sh) / S0;
-  if (threadIdx.x == 0) {
-    const int64_t o = (int64_t)c * a.n_T + t;
-    a.lnZ[o] = (S0 > 0.0 ? log(S0 / (double)Nt) : NAN) - beta * eref;
-    a.E[o] = Ebar;
-    a.C[o] = beta * beta * VarE;
-    a.chi[o] = beta * VarM;
-    if (a.mag) a.mag[o] = Mbar;
-    if (a.znonpos) a.znonpos[o] = S0 > 0.0 ? 0 : 1;
-  }
-}
-
-hipError_t launch_thermo_hybrid(const ThermoArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(thermo_hybrid_kernel, dim3(a.n_T, a.n_clusters), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 

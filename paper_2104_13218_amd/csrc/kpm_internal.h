@@ -298,12 +298,18 @@ struct ThermoProb {
   double sz;        // S^z = n_up - N/2
 };
 
+// Sums over the nodes of one sector at one temperature, with w the node's
+// weight times exp(-beta (E - lo)) and d = E - c.
+struct SectorSums {
+  double lo, s0, c, s1, v;   // lowest energy, sum w, centre, sum w d, sum w d^2
+};
+
 struct ThermoArgs {
   const ThermoProb* tp;
   const int32_t* cl_start;   // [n_clusters + 1] into cl_list
   const int32_t* cl_list;    // problems grouped by cluster
   const double* gamma;       // [n_probs][n_nodes]
-  const double* ab;          // [n_probs][2]
+  const double* enode;       // [n_probs][n_nodes] node energies
   const double* T;           // [n_T]
   double* lnZ;
   double* E;
@@ -311,10 +317,13 @@ struct ThermoArgs {
   double* chi;
   uint8_t* znonpos;
   double* stats;             // [n_clusters][n_T][6]: S0, Ebar, Var, <m^2>, Eref, beta
-  int32_t n_nodes, n_T, n_clusters;
-  const double* h;           // [n_T] Zeeman energies g mu_B B (field kernel only)
-  double* mag;               // [n_clusters][n_T] <S^z> (field kernel, may be NULL)
-  // hybrid kernel: problem p with ed_count[p] > 0 contributes the eigenvalues
+  int32_t n_nodes, n_T, n_clusters, n_probs;
+  int32_t t0, t1;            // the chunk's points
+  SectorSums* sums;          // [n_probs][t1 - t0]
+  int32_t* same;             // [t1 - t0] (with h only)
+  const double* h;           // [n_T] Zeeman energies g mu_B B, or NULL for none
+  double* mag;               // [n_clusters][n_T] <S^z> (may be NULL)
+  // exact levels (ed_count may be NULL): problem p with ed_count[p] > 0 contributes the eigenvalues
   // evals[p * evals_ld + i], i < ed_count[p], instead of its nodes
   const int32_t* ed_count;
   const double* evals;
@@ -352,7 +361,6 @@ struct EigArgs {
 // probs sorted by descending dim; dims[i] = probs[i].dim on the host.
 hipError_t launch_sector_eig(const EigArgs& a, const int* dims, int n_sectors, size_t lds_build,
                              size_t lds_finish, hipStream_t st);
-hipError_t launch_thermo_hybrid(const ThermoArgs& a, hipStream_t st);
 
 // Finite-temperature Lanczos: Ritz values/weights per column and the sums.
 struct FtlmArgs {
@@ -434,7 +442,7 @@ hipError_t launch_res_bond_sum(const ResArgs& a, const UnitDev* units, int n_pro
 
 struct ThermoVjpArgs {
   const ThermoProb* tp;
-  const double* ab;
+  const double* enode;
   const double* stats;
   const double* wC;          // [n_clusters][n_T]
   const double* wchi;
@@ -564,9 +572,9 @@ hipError_t launch_lz_fix(const DevicePlan& p, double* vec, int y_hi, const doubl
                          const double* fixed, double* beta2, double* ybeta, hipStream_t st);
 hipError_t launch_kernel_coef(int M, int kernel, double* g, hipStream_t st);
 hipError_t launch_gamma(int n_probs, int M, int n_nodes, const double* g, const double* mu,
-                        double* gamma, hipStream_t st);
-hipError_t launch_thermo(const ThermoArgs& a, hipStream_t st);
-hipError_t launch_thermo_field(const ThermoArgs& a, hipStream_t st);
+                        const double* ab, double* gamma, double* enode, hipStream_t st);
+int thermo_chunk(int n_probs, int n_T);
+hipError_t launch_thermo(ThermoArgs a, hipStream_t st);
 hipError_t launch_thermo_vjp(const ThermoVjpArgs& a, hipStream_t st);
 
 }  // namespace kpm
