@@ -1330,25 +1330,29 @@ void tri_extremes(const std::vector<double>& a, const std::vector<double>& b, do
 }
 
 // Whether the window [lo, hi] of the tridiagonal (al, be) hangs on the
-// rounding of the recursion that gave it: an end that has not converged (two
-// steps less move it by 1e-11 of the width) while the Lanczos vectors lost
-// their orthogonality to 1e-4 by Simon's recurrence for <q_j, q_k> (the same
-// test as in kpm_resident.hip).
+// rounding of the recursion that gave it: two steps less move an end by c
+// widths while the Lanczos vectors lost their orthogonality to omega by
+// Simon's recurrence for <q_j, q_k>, with c >= kRoundingEnd and c omega^2 >=
+// kRoundingReach (the same test as in kpm_resident.hip).
 bool hangs_on_rounding(const std::vector<double>& al, const std::vector<double>& be, double lo, double hi) {
   const int L = (int)al.size();
   if (L < 3) return false;
   const double W = hi - lo;
   const std::vector<double> a2(al.begin(), al.end() - 2), b2(be.begin(), be.begin() + (L - 3));
-  if (tri_count_below(a2, b2, lo + 1e-11 * W) > 0 && tri_count_below(a2, b2, hi - 1e-11 * W) < L - 2) return false;
+  auto converged = [&](double c) {
+    return tri_count_below(a2, b2, lo + c * W) > 0 && tri_count_below(a2, b2, hi - c * W) < L - 2;
+  };
+  if (converged(kRoundingEnd)) return false;
   const double ulp = 1.1e-16;
   std::vector<double> prev(L + 1, 0.0), cur(L + 1, 0.0), nxt(L + 1, 0.0);
   cur[0] = 1.0;
-  double top = 0.0;
+  double top = 0.0, size = 0.0;
+  for (double x : al) size = std::max(size, std::fabs(x));
   for (int j = 0; j + 1 < L; ++j) {
     for (int k = 0; k < j; ++k) {
       double v = be[k] * cur[k + 1] + (al[k] - al[j]) * cur[k] - be[j - 1] * prev[k];
       if (k > 0) v += be[k - 1] * cur[k - 1];
-      nxt[k] = (v + std::copysign(2.0 * ulp * W, v)) / be[j];
+      nxt[k] = (v + std::copysign(2.0 * ulp * size, v)) / be[j];
       top = std::max(top, std::fabs(nxt[k]));
     }
     nxt[j] = 30.0 * ulp * be[0] / be[j];
@@ -1356,7 +1360,8 @@ bool hangs_on_rounding(const std::vector<double>& al, const std::vector<double>&
     std::swap(prev, cur);
     std::swap(cur, nxt);
   }
-  return top > 1e-4;
+  const double w2 = std::min(top * top, 1.0);
+  return w2 > kRoundingReach && !converged(std::max(kRoundingEnd, kRoundingReach / w2));
 }
 
 // Lanczos recursion, every column its own (the spectral bounds of Eqs. (4)-(5)

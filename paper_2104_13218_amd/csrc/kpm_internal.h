@@ -397,6 +397,8 @@ hipError_t launch_ftlm_thermo(const FtlmArgs& a, hipStream_t st);
 constexpr int kResMaxDim = 19456;     // 19 rows per thread of 1024; v_n and the bookkeeping in 160 KB of LDS
 constexpr int kResMaxBonds = 32;
 constexpr int kResLanczos = 256;      // Lanczos steps whose coefficients are kept in LDS
+// c and c omega^2 of a Lanczos window from which on its ends hang on rounding
+constexpr double kRoundingEnd = 1e-13, kRoundingReach = 3e-15;
 constexpr int KPM_RES_GAUSSIAN = 2;   // start_value's kind of the Lanczos start column
 constexpr int kResAdjThreads = 512;   // threads of the gradient's workgroups
 constexpr int kResMom = 0, kResLz = 1, kResAdj = 2;   // launch_resident: moments, bounds, reverse sweep

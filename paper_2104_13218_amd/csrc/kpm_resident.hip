@@ -688,17 +688,21 @@ __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
     a.scale[2 * J.prob + 1] = sb;
     if (!(sa > 0.0) || !isfinite(sa) || !isfinite(sb)) atomicOr(a.flag, 8);
   }
-  // Does the window hang on rounding?  Only where an end has not converged
-  // (the value of two steps less differs by 1e-11 of the width) after the
-  // Lanczos vectors lost their orthogonality (Simon's recurrence for
-  // omega_{j,k} = <q_j, q_k>, 1984, above 1e-4): a copy of the other,
-  // converged end then takes steps from this one, at a point that the last
-  // bits decide.  Over 1080 sectors (six lattices of 8-16 sites) every window
-  // that moved by more than 1e-12 with the order of summation is caught.
+  // Does the window hang on rounding?  A copy of the other, converged end takes
+  // steps from an end that has not converged, from a point on that the last
+  // bits decide.  An end's value of two steps less differs by c widths, and the
+  // Lanczos vectors have lost their orthogonality by omega (Simon's recurrence
+  // for omega_{j,k} = <q_j, q_k>, 1984): the order of summation moves the end
+  // by about c omega^2.  Over 8640 sectors (six lattices of 8-16 sites) no
+  // window with c under 1e-13 or c omega^2 under 3e-15 moved by more than 4e-15
+  // of its width; a tenth of the sectors is above, most of them sawtooth chains.
   const double elo = 0.5 * (lo0 + hi0), ehi = 0.5 * (lo1 + hi1), width = ehi - elo;
   if (L < 3 || (L < steps && (uint32_t)L < dim)) return;       // the Krylov space is exhausted
   const int Ls = L - 2;
-  if (sturm_below(al, be, Ls, elo + 1e-11 * width) > 0 && sturm_below(al, be, Ls, ehi - 1e-11 * width) < Ls) return;
+  auto converged = [&](double c) {
+    return sturm_below(al, be, Ls, elo + c * width) > 0 && sturm_below(al, be, Ls, ehi - c * width) < Ls;
+  };
+  if (converged(kRoundingEnd)) return;
   __syncthreads();
   constexpr int S = kResLanczos + 2;
   double *prev = x, *cur = x + S, *nxt = x + 2 * S;            // omega_{j-1}, omega_j, omega_{j+1}
@@ -706,12 +710,13 @@ __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
   for (int k = tid; k < L; k += T) be[k] = sqrt(be[k]);
   __syncthreads();
   const double ulp = 1.1e-16;
-  double top_w = 0.0;
+  double top_w = 0.0, size = 0.0;
+  for (int k = 0; k < L; ++k) size = fmax(size, fabs(al[k]));
   for (int j = 0; j + 1 < L; ++j) {
     for (int k = tid; k < j; k += T) {
       double v = be[k] * cur[k + 1] + (al[k] - al[j]) * cur[k] - be[j - 1] * prev[k];
       if (k > 0) v += be[k - 1] * cur[k - 1];
-      v = (v + copysign(2.0 * ulp * width, v)) / be[j];
+      v = (v + copysign(2.0 * ulp * size, v)) / be[j];
       nxt[k] = v;
       top_w = fmax(top_w, fabs(v));
     }
@@ -725,7 +730,10 @@ __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
     cur = nxt;
     nxt = t;
   }
-  if (top_w > 1e-4) {
+  for (int k = tid; k < L; k += T) be[k] *= be[k];
+  __syncthreads();
+  const double w2 = fmin(top_w * top_w, 1.0);   // over this thread's entries
+  if (w2 > kRoundingReach && !converged(fmax(kRoundingEnd, kRoundingReach / w2))) {
     a.unstable[J.prob] = 1;
     atomicOr(a.flag, 16);
   }
