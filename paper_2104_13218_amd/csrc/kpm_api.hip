@@ -561,6 +561,29 @@ Tune slice_tune(const kpm_problem* p, int n, int precision, int L) {
 int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double* a_arr,
                     const double* b_arr, Planned& P);
 
+// Whether the split spin kernel takes a spin-s plan, and the halves of its
+// problems (B0, B1, B2): up to 16 sites (two 32-bit words of digits) with at
+// most 2^16 low and high codes each, per-bond tables in half of the LDS that
+// four workgroups leave each other, and records no larger than the lists that
+// they replace (few rows of many sites: their lists are the smaller).
+bool split_spin(Planned& P, int cpl) {
+  if (env_int("KPM_SPIN_SPLIT", 1) == 0) return false;
+  int64_t lists = 0, records = 0;
+  for (ProbDev& d : P.probs) {
+    if (d.n_sites < 2 || d.n_sites > 16) return false;
+    d.B0 = d.n_sites / 2;
+    int64_t low = 1, high = 1;
+    for (int i = 0; i < d.n_sites; ++i) (i < d.B0 ? low : high) *= d.two_s + 1;
+    if (low > 65536 || high > 65536) return false;
+    d.B1 = (int32_t)high;
+    d.B2 = (int32_t)low;
+    if (spin_split_lds_bytes(d.n_bonds, d.two_s, cpl) > 40 * 1024) return false;
+    lists += d.dim * (1 + 2 * (int64_t)d.n_bonds);
+    records += spin_split_words(d.B1, d.B2, d.n_bonds);
+  }
+  return records <= lists;
+}
+
 // The plan of a run.  Where nobody chose a kernel or a block width, spin-1/2
 // sectors from kSliceLeast on take the slice kernel, with 10 low bits or else 9
 // (a word row holds so many bonds), and the planner's heuristic where neither
@@ -711,6 +734,15 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
   if (row_ld) D.sub_rows = kThreads;
   D.n_states = spin ? n_states * (2 + D.lds_nb) : n_states;   // spin: digits + neighbour ranks
   D.spin_rows = spin ? n_states : 0;
+  if (spin && split_spin(P, cpl)) {
+    D.spin = 2;
+    D.n_states = (n_states + 3) & ~int64_t(3);
+    for (ProbDev& d : P.probs) {
+      d.split_off = D.n_states;
+      D.n_states += spin_split_words(d.B1, d.B2, d.n_bonds);
+      D.split_lds = std::max(D.split_lds, spin_split_lds_bytes(d.n_bonds, d.two_s, cpl));
+    }
+  }
 
   // Block kernel (tiles of whole low-bit blocks) when its LDS fits: bonds in
   // class order low-low, high-high, mixed.
@@ -919,7 +951,11 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
   D.sub_per_tile = spt;
   // slice kernel: every XCD on the same column block at a time (measured 4 %
   // faster on the 24-site ring than contiguous tile ranges per XCD)
-  D.xcd_remap = env_int("KPM_XCD_REMAP", D.block == 3 ? -1 : 1);
+  // spin plans: consecutive tiles on consecutive XCDs, so that all of them read
+  // the same stretch of a vector at a time (ten spin-5/2 sites, 32 float32
+  // columns: 7.1 ms a step, 8.1 with contiguous ranges, 8.8 with an eighth of
+  // every sector per XCD)
+  D.xcd_remap = env_int("KPM_XCD_REMAP", D.block == 3 ? -1 : (spin ? 0 : 1));
   D.dense = env_int("KPM_DENSE_LISTS", 0);
   const int64_t tile_rows = (int64_t)D.sub_rows * spt;
 
@@ -977,6 +1013,16 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
     }
   }
   P.prob_unit0.push_back((int32_t)P.units.size());
+  if (D.spin == 2) {
+    // eight float32 columns per lane where every unit has whole lanes
+    D.split_cpl = cpl;
+    bool eights = fp32 && cpl == 4;
+    for (const UnitDev& u : P.units) eights = eights && u.ld % 8 == 0;
+    if (eights) D.split_cpl = 8;
+    D.split_lds = 0;
+    for (const ProbDev& d : P.probs)
+      D.split_lds = std::max(D.split_lds, spin_split_lds_bytes(d.n_bonds, d.two_s, D.split_cpl));
+  }
   // the row and block kernels also stream the 4-byte state word of every row;
   // the block-table kernel reads its per-block tables instead
   // the per-block table layout depends on the problem count (word tables)
@@ -994,10 +1040,12 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
   } else if (D.row_ld || D.block) {
     for (const auto& u : P.units) P.bytes_per_step += 4.0 * (double)P.probs[u.prob].dim;
   } else if (D.spin) {
-    // the spin kernel reads each row's digit string and its neighbour-rank slots
+    // the spin kernel reads each row's digit string and its neighbour-rank
+    // slots, the split spin kernel each row's high code and the records
     for (const auto& u : P.units) {
       const ProbDev& d = P.probs[u.prob];
-      P.bytes_per_step += (8.0 + 8.0 * d.n_bonds) * (double)d.dim;
+      P.bytes_per_step += D.spin == 2 ? 4.0 * (double)d.dim + 4.0 * spin_split_words(d.B1, d.B2, d.n_bonds)
+                                      : (8.0 + 8.0 * d.n_bonds) * (double)d.dim;
     }
   }
   // bonds in class order (the slice kernel reads them with scalar loads)

@@ -36,6 +36,9 @@ struct ProbDev {
   // P[i][r][d] = number of digit strings of sites 0..i with sum r and digit
   // < d at site i, [n_sites][2s n_sites + 1][2s + 1]; bond masks hold i | j << 8.
   int32_t two_s;
+  // Split spin kernel: B0 low sites, B1 codes of the high sites, B2 of the low
+  // ones; the records begin at split_off (u32 entries of the state table).
+  int64_t split_off;
   // Block kernels: the sites are relabelled (site i of the problem is bit
   // perm[i] of the words the kernels see) so that few bonds join the low
   // bits to the high bits.  Rows are then in the rank order of the
@@ -88,7 +91,8 @@ struct StepArgs {
   const double* bzz;           // per bond: J_b / (4a)   (diagonal contribution)
   const uint32_t* binom;       // C(n, j) [33][33]
   const uint32_t* states;      // basis words of every sector, rank order (row kernel);
-                               // spin kernel: digit strings (u64) then neighbour ranks
+                               // spin kernel: digit strings (u64) then neighbour ranks;
+                               // split spin kernel: high codes, then records
   int64_t spin_rows;           // spin kernel: rows of all problems (u64 digit strings)
   void* vec;                   // vector storage base (float or double)
   int64_t slot_stride;         // elements between consecutive slots
@@ -200,7 +204,10 @@ struct DevicePlan {
   int32_t n_blk = 0;           // block-table kernel: blocks of all problems
   int32_t meta_hh = 1, meta_mx = 1;   // per-block table widths (StepArgs)
   int32_t tab_xl = 0;          // block-table kernel: sub-tile rows of v_n staged in LDS
-  int32_t spin = 0;            // 1: spin-s plan (spin kernel for every step)
+  int32_t spin = 0;            // spin-s plan: 1 spin kernel, 2 split spin kernel
+  int32_t split_cpl = 0;       // split spin kernel: columns per lane
+  size_t split_lds = 0;        // split spin kernel: LDS per workgroup; its state table holds
+                               // the high code of every row, then per problem its records
   int64_t spin_rows = 0;       // spin plan: rows of all problems; the state table holds
                                // the u64 digit string of every row, then per problem
                                // [lds_nb][dim] u32 neighbour ranks (slot 2b + w: bond b,
@@ -555,6 +562,8 @@ hipError_t fill_states(const DevicePlan& p, hipStream_t st);
 size_t row_lds_bytes(const DevicePlan& p);
 size_t block_lds_bytes(const DevicePlan& p);
 size_t spin_lds_bytes(const DevicePlan& p);
+int64_t spin_split_words(int n_high, int n_low, int n_bonds);
+size_t spin_split_lds_bytes(int n_bonds, int two_s, int cpl);
 size_t tab_lds_bytes(const DevicePlan& p);
 size_t slice_lds_bytes(const DevicePlan& p);
 int slice_word_bytes(int n_mx, int n_ll);   // 32, 64, or 0 when a word row cannot hold the bonds

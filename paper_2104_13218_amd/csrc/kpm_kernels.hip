@@ -480,6 +480,360 @@ __global__ __launch_bounds__(kThreads) void spin_kernel(const StepArgs a) {
   }
 }
 
+// ------------------------------------------------------ split spin kernel
+//
+// The neighbour ranks of a digit string follow from its two halves.  The low L
+// sites and the high N - L sites of a row rho = start(h) + l have codes of
+// their own: h the number of the high digits in base 2s + 1, l the place of
+// the low string among those of its digit sum.  A bond's neighbour is
+// start(h') + l', with h' from a record of h and l' from a record of (digit
+// sum, l), so a row reads no list of its own: two records per half that fit
+// the caches stand for (8 + 8 n_bonds) bytes a row and column block, and no
+// list is staged in LDS.  Amplitudes and diagonal come from per-bond tables
+// over the two digits in LDS.  Every row sums the terms of spin_kernel in its
+// order, and with the same tiles and columns per lane the dots do too: the
+// results are the same bits.
+//
+// Bound by the neighbour rows that miss a slice of the L2 (the bonds of the
+// most significant sites reach rows far off: 344 M lines of 128 bytes a step
+// for the 26 sectors of ten spin-5/2 sites with 32 float32 columns, 44 GB in
+// 7.1 ms; spin_kernel took 8.85 ms).  Eight columns per lane, since a lane's
+// places and amplitudes cost more than four columns' sums (7.4 ms with four);
+// the next row's records and the next bonds' places are requested while rows
+// arrive (7.5 ms without).  One float64 column, where the lists
+// were most of the traffic: 3.7 -> 0.86 ms.
+//
+// High record: start, digits, first low record, -, then per bond the starts of
+// S^+_i S^-_j and S^-_i S^+_j (its own start where a bond leaves h alone or
+// does not act).  Low record: per bond the two places as 16-bit halves, then
+// the digits.  Both padded to an even number of bonds.
+
+__host__ __device__ inline int split_bonds(int n_bonds) { return (n_bonds + 1) & ~1; }
+__host__ __device__ inline int split_high_words(int nb2) { return 4 + 2 * nb2; }
+__host__ __device__ inline int split_low_words(int nb2) { return nb2 + 2; }
+
+int64_t spin_split_words(int n_high, int n_low, int n_bonds) {
+  const int nb2 = split_bonds(n_bonds);
+  return ((int64_t)n_high * split_high_words(nb2) + (int64_t)n_low * split_low_words(nb2) + 3) & ~int64_t(3);
+}
+
+size_t spin_split_lds_bytes(int n_bonds, int two_s, int cpl) {
+  const size_t B2 = (size_t)(two_s + 1) * (two_s + 1), nb2 = split_bonds(n_bonds);
+  return (16 + B2 + nb2 + nb2 * B2 + (size_t)2 * cpl * kThreads) * 8;
+}
+
+template <typename T, int CPL>
+__global__ __launch_bounds__(kThreads) void spin_split_kernel(const StepArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x;
+
+  if (a.n_jobs > 0) {
+    const int64_t s = (a.step_base ? *a.step_base : 0) + a.step_add;
+    double* sh = reinterpret_cast<double*>(smem);
+    for (int job = blockIdx.x; job < a.n_jobs; job += gridDim.x) {
+      const UnitDev U = a.units[a.job_unit[job]];
+      const int v = job - 2 * U.col_off;
+      const double sum = sum_partials(a.part_in + U.part_off + (int64_t)v * U.ntiles, U.ntiles, sh);
+      if (tid == 0) {
+        if (v < U.ld) a.alpha[s * a.total_cols + U.col_off + v] = sum;
+        else a.beta[(s - 1) * a.total_cols + U.col_off + (v - U.ld)] = sum;
+      }
+    }
+    __syncthreads();
+  }
+
+  const int tile = a.xcd_remap ? xcd_tile(blockIdx.x, a.grid_tiles) : (int)blockIdx.x;
+  if (tile >= a.n_tiles) return;
+  const UnitDev U = a.units[a.tile_unit[tile]];
+  const ProbDev P = a.probs[U.prob];
+  const int two_s = P.two_s, B = two_s + 1, B2 = B * B;
+  const int nb2 = split_bonds(P.n_bonds);
+  const double sv = 0.5 * two_s;
+  double* up = reinterpret_cast<double*>(smem);   // [2s + 1]: sqrt(s(s+1) - m(m+1)), m = d - s
+  double* prod = up + 16;                         // [d1][d2]: m1 m2
+  double* c4 = prod + B2;                         // per bond: J_b / a
+  double* amp = c4 + nb2;                         // per bond [d1][d2]: site 1 raised, site 2 lowered
+  double* red = amp + nb2 * B2;
+  if (tid < B) {
+    const double m = tid - sv;
+    up[tid] = sqrt(fmax(sv * (sv + 1.0) - m * (m + 1.0), 0.0));
+  }
+  __syncthreads();
+  for (int i = tid; i < B2; i += kThreads) prod[i] = (i / B - sv) * (i % B - sv);
+  for (int i = tid; i < nb2; i += kThreads) c4[i] = i < P.n_bonds ? 4.0 * a.bzz[P.bond_off + i] : 0.0;
+  for (int i = tid; i < nb2 * B2; i += kThreads) {
+    const int b = i / B2, d1 = i % B2 / B, d2 = i % B;
+    amp[i] = b < P.n_bonds && d1 < two_s && d2 > 0 ? a.boff[P.bond_off + b] * up[d1] * up[d2 - 1] : 0.0;
+  }
+  __syncthreads();
+
+  const uint32_t* hmap = a.states + P.state_off;
+  const uint32_t* hrec = a.states + P.split_off;
+  const int hw = split_high_words(nb2), lw = split_low_words(nb2), shift = 4 * P.B0;
+  const uint32_t* lrec = hrec + (int64_t)P.B1 * hw;
+  const cptr<uint32_t> sites = cview(a.bmask) + P.bond_off;
+
+  const int ld = U.ld;
+  const int nch = ld / CPL;
+  const int nrg = kThreads / nch;
+  const int c = tid % nch;
+  const int rg = tid / nch;
+  T* base = reinterpret_cast<T*>(a.vec) + U.vec_off;
+  const T* X = base + a.x_slot * a.slot_stride + c * CPL;
+  const T* Yin = base + a.yin_slot * a.slot_stride + c * CPL;
+  T* Y = base + a.yout_slot * a.slot_stride + c * CPL;
+  double acc_a[CPL], acc_b[CPL];
+#pragma unroll
+  for (int i = 0; i < CPL; ++i) acc_a[i] = acc_b[i] = 0.0;
+
+  // spin_kernel gives the rows of a sub-tile to at most sub_rows row groups:
+  // where more fit the workgroup, `fold` sub-tiles run at once and the first
+  // groups sum their dots in order
+  const int fold = nrg > a.sub_rows ? nrg / a.sub_rows : 1;
+  const int groups = nrg > a.sub_rows ? fold * a.sub_rows : nrg;
+  const int64_t row0 = a.tile_row0[tile];
+  const int rows = a.tile_nrows[tile];
+  // the records of the next row are requested while this one is summed
+  struct RowAt {
+    const uint32_t *hr, *lr;
+    uint64_t dg;
+    uint32_t rho;
+  };
+  auto row_code = [&](int r0) {   // past the end: the last row, not used
+    return (int64_t)hmap[row0 + min(r0 + rg, rows - 1)] * hw;
+  };
+  auto row_at = [&](int r0, int64_t code) {
+    RowAt R;
+    R.rho = (uint32_t)(row0 + min(r0 + rg, rows - 1));
+    R.hr = hrec + code;
+    const uint4 head = *reinterpret_cast<const uint4*>(R.hr);
+    R.lr = lrec + (int64_t)(head.z + (R.rho - head.x)) * lw;
+    R.dg = (uint64_t)R.lr[nb2] | (uint64_t)head.y << shift;
+    return R;
+  };
+  RowAt R = row_at(0, row_code(0));
+  for (int r0 = 0; r0 < rows; r0 += groups) {
+    const int rr = r0 + rg;
+    const bool on = rg < groups && rr < rows;
+    double ovs[CPL] = {}, xvs[CPL] = {};
+    const int64_t code = row_code(r0 + groups);
+    RowAt next{};
+    if (on) {
+      const uint32_t rho = R.rho;
+      const uint64_t dg = R.dg;
+      const VecT<T, CPL> xv = vload<T, CPL>(X + (int64_t)rho * ld);
+      VecT<T, CPL> yv;
+      if (!a.first) yv = vload_nt<T, CPL>(Yin + (int64_t)rho * ld);
+      uint4 hs = *reinterpret_cast<const uint4*>(R.hr + 4);
+      uint2 ls = *reinterpret_cast<const uint2*>(R.lr);
+      double dgn = P.shift, acc[CPL];
+      // the diagonal is a factor of the first term: summed before the others
+      for (int b = 0; b < P.n_bonds; ++b) {
+        const uint32_t s = sites[b];
+        const int di = (int)((dg >> (4 * (s & 0xFFu))) & 15u), dj = (int)((dg >> (4 * (s >> 8))) & 15u);
+        dgn = fma(c4[b], prod[di * B + dj], dgn);
+      }
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) acc[i] = dgn * (double)xv.v[i];
+      for (int b = 0; b < nb2; b += 2) {
+        const uint32_t s0 = sites[b], s1 = b + 1 < P.n_bonds ? sites[b + 1] : s0;
+        const int i0 = (int)((dg >> (4 * (s0 & 0xFFu))) & 15u), j0 = (int)((dg >> (4 * (s0 >> 8))) & 15u);
+        const int i1 = (int)((dg >> (4 * (s1 & 0xFFu))) & 15u), j1 = (int)((dg >> (4 * (s1 >> 8))) & 15u);
+        const double* am = amp + b * B2;
+        double cf[4] = {am[i0 * B + j0], am[j0 * B + i0], am[B2 + i1 * B + j1], am[B2 + j1 * B + i1]};
+        uint32_t nb[4] = {hs.x + (ls.x & 0xFFFFu), hs.y + (ls.x >> 16), hs.z + (ls.y & 0xFFFFu), hs.w + (ls.y >> 16)};
+        VecT<T, CPL> nv[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (cf[j] == 0.0) nb[j] = rho;   // does not act: the two halves need not meet in a row
+          nv[j] = vload<T, CPL>(X + (int64_t)nb[j] * ld);
+        }
+        const int bn = min(b + 2, nb2 - 2);   // the next bonds' places, while these rows arrive
+        hs = *reinterpret_cast<const uint4*>(R.hr + 4 + 2 * bn);
+        ls = *reinterpret_cast<const uint2*>(R.lr + bn);
+        if (b == 0) next = row_at(r0 + groups, code);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+          for (int i = 0; i < CPL; ++i) acc[i] = fma(cf[j], (double)nv[j].v[i], acc[i]);
+        }
+      }
+      VecT<T, CPL> ov;
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        ov.v[i] = a.first ? (T)acc[i] : (T)(2.0 * acc[i] - (double)yv.v[i]);
+        ovs[i] = (double)ov.v[i];
+        xvs[i] = (double)xv.v[i];
+      }
+      vstore_nt<T, CPL>(Y + (int64_t)rho * ld, ov);
+    }
+    R = next;
+    if (fold == 1) {
+      if (on) {
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+          acc_a[i] = fma(ovs[i], ovs[i], acc_a[i]);
+          acc_b[i] = fma(ovs[i], xvs[i], acc_b[i]);
+        }
+      }
+      continue;
+    }
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      red[(2 * i) * kThreads + tid] = ovs[i];
+      red[(2 * i + 1) * kThreads + tid] = xvs[i];
+    }
+    __syncthreads();
+    if (rg < a.sub_rows) {
+      for (int g = 0; g < fold; ++g) {
+        if (r0 + g * a.sub_rows + rg >= rows) break;
+        const int at = tid + g * a.sub_rows * nch;
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+          const double o = red[(2 * i) * kThreads + at];
+          acc_a[i] = fma(o, o, acc_a[i]);
+          acc_b[i] = fma(o, red[(2 * i + 1) * kThreads + at], acc_b[i]);
+        }
+      }
+    }
+    __syncthreads();
+  }
+
+  if (rg < nrg) {
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      red[(2 * i) * kThreads + tid] = acc_a[i];
+      red[(2 * i + 1) * kThreads + tid] = acc_b[i];
+    }
+  }
+  int p2 = 1;
+  while (p2 < nrg) p2 <<= 1;
+  for (int sstride = p2 >> 1; sstride > 0; sstride >>= 1) {
+    __syncthreads();
+    if (rg < sstride && rg + sstride < nrg) {
+#pragma unroll
+      for (int v = 0; v < 2 * CPL; ++v) red[v * kThreads + tid] += red[v * kThreads + tid + sstride * nch];
+    }
+  }
+  __syncthreads();
+  if (tid < nch) {
+    const int tl = tile - U.tile0;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      const int col = c * CPL + i;
+      a.part_out[U.part_off + (int64_t)col * U.ntiles + tl] = red[(2 * i) * kThreads + tid];
+      a.part_out[U.part_off + (int64_t)(ld + col) * U.ntiles + tl] = red[(2 * i + 1) * kThreads + tid];
+    }
+  }
+}
+
+// The records of every problem (blockIdx.y), and every row's h.
+__global__ __launch_bounds__(kThreads) void spin_split_tables_kernel(const ProbDev* probs, const uint32_t* tables,
+                                                                     const uint32_t* bmask, uint32_t* states) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t* tab = reinterpret_cast<uint32_t*>(smem);
+  const ProbDev P = probs[blockIdx.y];
+  for (int i = threadIdx.x; i < P.tab_len; i += kThreads) tab[i] = tables[P.tab_off + i];
+  __syncthreads();
+  const int N = P.n_sites, L = P.B0, two_s = P.two_s, B = two_s + 1, R1 = two_s * N + 1;
+  const int nb2 = split_bonds(P.n_bonds), hw = split_high_words(nb2), lw = split_low_words(nb2);
+  uint32_t* hmap = states + P.state_off;
+  uint32_t* hrec = states + P.split_off;
+  uint32_t* lrec = hrec + (int64_t)P.B1 * hw;
+  const int64_t first = (int64_t)blockIdx.x * kThreads + threadIdx.x, step = (int64_t)gridDim.x * kThreads;
+  auto digit = [](uint64_t dg, int i) { return (int)((dg >> (4 * i)) & 15u); };
+  // the rank of the entries of sites top .. bottom with r the sum below them
+  auto partial = [&](uint64_t dg, int top, int bottom, int r) {
+    uint32_t rank = 0;
+    for (int i = top; i >= bottom; --i) {
+      rank += tab[(i * R1 + r) * B + digit(dg, i)];
+      r -= digit(dg, i);
+    }
+    return rank;
+  };
+  auto sum_of = [&](uint64_t dg) {
+    int s = 0;
+    for (int i = 0; i < N; ++i) s += digit(dg, i);
+    return s;
+  };
+  auto holds = [&](int low_sum) { return low_sum >= 0 && low_sum <= two_s * L; };
+  auto low_base = [&](int s) {   // first low record of digit sum s: the strings of L sites with smaller sums
+    uint32_t n = 0;
+    for (int v = 0; v < s; ++v) n += tab[(L * R1 + v) * B + 1];
+    return n;
+  };
+  for (int64_t rho = first; rho < P.dim; rho += step) {
+    uint32_t rem = (uint32_t)rho, h = 0;
+    int r = P.n_up;
+    for (int i = N - 1; i >= L; --i) {
+      int d = min(two_s, r);
+      while (d > 0 && tab[(i * R1 + r) * B + d] > rem) --d;
+      rem -= tab[(i * R1 + r) * B + d];
+      h = h * B + d;
+      r -= d;
+    }
+    hmap[rho] = h;
+  }
+  for (int64_t h = first; h < P.B1; h += step) {
+    uint64_t dg = 0;
+    for (int64_t i = L, v = h; i < N; ++i, v /= B) dg |= (uint64_t)(v % B) << (4 * i);
+    const int low_sum = P.n_up - sum_of(dg);
+    uint32_t* rec = hrec + h * hw;
+    if (!holds(low_sum)) continue;   // no row has these high digits
+    const uint32_t own = partial(dg, N - 1, L, P.n_up);
+    rec[0] = own;
+    rec[1] = (uint32_t)(dg >> (4 * L));
+    rec[2] = low_base(low_sum);
+    rec[3] = 0u;
+    for (int b = 0; b < nb2; ++b) {
+      const uint32_t sij = b < P.n_bonds ? bmask[P.bond_off + b] : 0u;
+      for (int w = 0; w < 2; ++w) {
+        const int i = (int)(sij & 0xFFu), j = (int)(sij >> 8), u = w == 0 ? i : j, v = w == 0 ? j : i;
+        uint64_t d2 = dg;
+        bool acts = b < P.n_bonds && (u >= L || v >= L);
+        if (acts && u >= L) {
+          acts = digit(dg, u) < two_s;
+          d2 += (uint64_t)1 << (4 * u);
+        }
+        if (acts && v >= L) {
+          acts = digit(dg, v) > 0;
+          d2 -= (uint64_t)1 << (4 * v);
+        }
+        rec[4 + 2 * b + w] = acts && holds(P.n_up - sum_of(d2)) ? partial(d2, N - 1, L, P.n_up) : own;
+      }
+    }
+  }
+  for (int64_t code = first; code < P.B2; code += step) {
+    uint64_t dg = 0;
+    for (int64_t i = 0, v = code; i < L; ++i, v /= B) dg |= (uint64_t)(v % B) << (4 * i);
+    const int s = sum_of(dg);
+    if (s > P.n_up) continue;   // the rank table ends at n_up's sum
+    const uint32_t own = partial(dg, L - 1, 0, s);
+    uint32_t* rec = lrec + (int64_t)(low_base(s) + own) * lw;
+    for (int b = 0; b < nb2; ++b) {
+      const uint32_t sij = b < P.n_bonds ? bmask[P.bond_off + b] : 0u;
+      uint32_t at[2];
+      for (int w = 0; w < 2; ++w) {
+        const int i = (int)(sij & 0xFFu), j = (int)(sij >> 8), u = w == 0 ? i : j, v = w == 0 ? j : i;
+        uint64_t d2 = dg;
+        bool acts = b < P.n_bonds && (u < L || v < L);
+        if (acts && u < L) {
+          acts = digit(dg, u) < two_s;
+          d2 += (uint64_t)1 << (4 * u);
+        }
+        if (acts && v < L) {
+          acts = digit(dg, v) > 0;
+          d2 -= (uint64_t)1 << (4 * v);
+        }
+        at[w] = acts ? partial(d2, L - 1, 0, sum_of(d2)) : own;
+      }
+      rec[b] = at[0] | at[1] << 16;
+    }
+    rec[nb2] = (uint32_t)dg;
+    rec[nb2 + 1] = 0u;
+  }
+}
+
 // Digit strings and neighbour ranks of every row of every spin-s problem
 // (grid: x strides over rows, y = problem); the rank table in LDS.
 __global__ __launch_bounds__(kThreads) void spin_lists_kernel(const ProbDev* probs,
@@ -528,31 +882,42 @@ __global__ __launch_bounds__(kThreads) void spin_lists_kernel(const ProbDev* pro
 
 static hipError_t build_spin_lists(const DevicePlan& p, hipStream_t st) {
   const size_t lds = (size_t)p.lds_tab * 4;
+  if (p.spin == 2) {
+    hipLaunchKernelGGL(spin_split_tables_kernel, dim3(1024, p.n_probs), dim3(kThreads), lds, st, p.probs, p.tables,
+                       p.bmask, p.states);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(spin_lists_kernel, dim3(1024, p.n_probs), dim3(kThreads), lds, st, p.probs, p.tables,
                      p.bmask, p.states, p.spin_rows, p.lds_nb, p.err);
   return hipGetLastError();
 }
 
 template <typename T, int CPL>
-static hipError_t launch_spin_t(const StepArgs& a, size_t lds, int grid, hipStream_t st) {
-  hipLaunchKernelGGL((spin_kernel<T, CPL, 4>), dim3(grid), dim3(kThreads), lds, st, a);
+static hipError_t launch_spin_t(const StepArgs& a, bool split, size_t lds, int grid, hipStream_t st) {
+  if (split) hipLaunchKernelGGL((spin_split_kernel<T, CPL>), dim3(grid), dim3(kThreads), lds, st, a);
+  else hipLaunchKernelGGL((spin_kernel<T, CPL, 4>), dim3(grid), dim3(kThreads), lds, st, a);
   return hipGetLastError();
 }
 
 static hipError_t launch_spin(const DevicePlan& p, const StepArgs& a, hipStream_t st) {
-  const size_t lds = spin_lds_bytes(p);
+  const bool split = p.spin == 2;
+  const size_t lds = split ? p.split_lds : spin_lds_bytes(p);
   const int grid = p.grid_tiles;
+  if (split && p.split_cpl == 8) {
+    hipLaunchKernelGGL((spin_split_kernel<float, 8>), dim3(grid), dim3(kThreads), lds, st, a);
+    return hipGetLastError();
+  }
   if (p.fp32) {
     switch (p.cpl) {
-      case 1: return launch_spin_t<float, 1>(a, lds, grid, st);
-      case 2: return launch_spin_t<float, 2>(a, lds, grid, st);
-      case 4: return launch_spin_t<float, 4>(a, lds, grid, st);
+      case 1: return launch_spin_t<float, 1>(a, split, lds, grid, st);
+      case 2: return launch_spin_t<float, 2>(a, split, lds, grid, st);
+      case 4: return launch_spin_t<float, 4>(a, split, lds, grid, st);
       default: return hipErrorInvalidValue;
     }
   }
   switch (p.cpl) {
-    case 1: return launch_spin_t<double, 1>(a, lds, grid, st);
-    case 2: return launch_spin_t<double, 2>(a, lds, grid, st);
+    case 1: return launch_spin_t<double, 1>(a, split, lds, grid, st);
+    case 2: return launch_spin_t<double, 2>(a, split, lds, grid, st);
     default: return hipErrorInvalidValue;
   }
 }

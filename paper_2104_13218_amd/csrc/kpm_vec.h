@@ -37,38 +37,35 @@ template <> struct NtVec<double, 1> { typedef double type; };
 template <typename T, int N>
 __device__ __forceinline__ VecT<T, N> vload_nt(const T* p) {
   VecT<T, N> r;
-  if constexpr (N == 4 && sizeof(T) == 8) {
-    typedef typename NtVec<double, 2>::type V;
-    const V a = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
-    const V b = __builtin_nontemporal_load(reinterpret_cast<const V*>(p) + 1);
-    r.v[0] = a[0]; r.v[1] = a[1]; r.v[2] = b[0]; r.v[3] = b[1];
-  } else if constexpr (N == 1) {
+  if constexpr (N == 1) {
     r.v[0] = __builtin_nontemporal_load(p);
   } else {
-    typedef typename NtVec<T, N>::type V;
-    const V a = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+    constexpr int W = sizeof(T) * N > 16 ? 16 / sizeof(T) : N;   // elements of one load
+    typedef typename NtVec<T, W>::type V;
 #pragma unroll
-    for (int i = 0; i < N; ++i) r.v[i] = a[i];
+    for (int k = 0; k < N / W; ++k) {
+      const V a = __builtin_nontemporal_load(reinterpret_cast<const V*>(p) + k);
+#pragma unroll
+      for (int i = 0; i < W; ++i) r.v[k * W + i] = a[i];
+    }
   }
   return r;
 }
 
 template <typename T, int N>
 __device__ __forceinline__ void vstore_nt(T* p, const VecT<T, N>& x) {
-  if constexpr (N == 4 && sizeof(T) == 8) {
-    typedef typename NtVec<double, 2>::type V;
-    V a, b;
-    a[0] = x.v[0]; a[1] = x.v[1]; b[0] = x.v[2]; b[1] = x.v[3];
-    __builtin_nontemporal_store(a, reinterpret_cast<V*>(p));
-    __builtin_nontemporal_store(b, reinterpret_cast<V*>(p) + 1);
-  } else if constexpr (N == 1) {
+  if constexpr (N == 1) {
     __builtin_nontemporal_store(x.v[0], p);
   } else {
-    typedef typename NtVec<T, N>::type V;
-    V a;
+    constexpr int W = sizeof(T) * N > 16 ? 16 / sizeof(T) : N;
+    typedef typename NtVec<T, W>::type V;
 #pragma unroll
-    for (int i = 0; i < N; ++i) a[i] = x.v[i];
-    __builtin_nontemporal_store(a, reinterpret_cast<V*>(p));
+    for (int k = 0; k < N / W; ++k) {
+      V a;
+#pragma unroll
+      for (int i = 0; i < W; ++i) a[i] = x.v[k * W + i];
+      __builtin_nontemporal_store(a, reinterpret_cast<V*>(p) + k);
+    }
   }
 }
 
