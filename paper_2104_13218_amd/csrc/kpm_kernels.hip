@@ -2377,6 +2377,7 @@ hipError_t launch_reduce(const DevicePlan& p, const double* part, double* dst_a,
 template <typename T>
 __global__ __launch_bounds__(kThreads) void init_kernel(const InitArgs a) {
   __shared__ double red[kThreads];
+  __shared__ uint32_t binom[kBinomN * kBinomN], drawn[kThreads];
   const int tile = xcd_tile(blockIdx.x, a.grid_tiles);
   if (tile >= a.n_tiles) return;
   const UnitDev U = a.units[a.tile_unit[tile]];
@@ -2399,15 +2400,27 @@ __global__ __launch_bounds__(kThreads) void init_kernel(const InitArgs a) {
     scale = sqrt((double)P.dim / n2);
   }
   double acc = 0.0;
-  if (rg < nrg) {
-    for (int64_t rho = row0 + rg; rho < row1; rho += nrg) {
+  // a relabelled row draws the value of its word's original rank: a thread
+  // finds that of one row, for all columns (ld x nrg rows at a time; each
+  // column's thread on its own took 21 ms for 155 M rows of four columns, 9.0
+  // now)
+  const int chunk = ld * nrg;
+  if (P.relabel) {
+    for (int i = tid; i < kBinomN * kBinomN; i += kThreads) binom[i] = a.binom[i];
+    __syncthreads();
+  }
+  for (int64_t at = row0; at < row1; at += chunk) {
+    if (P.relabel) {
+      if (tid < chunk && at + tid < row1)
+        drawn[tid] = word_rank(relabel_word(unrank((uint32_t)(at + tid), P.n_sites, P.n_up, binom), P.perm,
+                                            P.n_sites, false),
+                               binom);
+      __syncthreads();
+    }
+    const int64_t end = min(at + chunk, row1);
+    for (int64_t rho = rg < nrg ? at + rg : end; rho < end; rho += nrg) {
       double x = 0.0;
-      // a relabelled row draws the value of its word's original rank
-      const int64_t idx = P.relabel ? (int64_t)word_rank(relabel_word(unrank((uint32_t)rho, P.n_sites, P.n_up,
-                                                                                a.binom),
-                                                                         P.perm, P.n_sites, false),
-                                                             a.binom)
-                                    : rho;
+      const int64_t idx = P.relabel ? (int64_t)drawn[rho - at] : rho;
       if (c < U.ncols) x = start_value(a.vec_kind, a.seed, P, U.col0 + c, idx);
       if (a.mode == 0) {
         acc = fma(x, x, acc);
@@ -2426,6 +2439,7 @@ __global__ __launch_bounds__(kThreads) void init_kernel(const InitArgs a) {
         acc = fma((double)xs, (double)xs, acc);
       }
     }
+    if (P.relabel) __syncthreads();
   }
   red[tid] = rg < nrg ? acc : 0.0;
   int p2 = 1;
