@@ -238,6 +238,7 @@ struct RunShape {
   bool split_vectors = false;  // complex vectors may be split across blocks (one column each)
   bool allow_relabel = true;   // block kernels may relabel sites (rows then in relabelled order)
   bool allow_slice = true;     // large sectors may take the slice kernel by default (large_slice)
+  bool slice_only = false;     // KPM_EINVAL instead of another kernel's plan
 };
 
 constexpr int kAdjMaxLd = 16;
@@ -467,6 +468,8 @@ struct BlockList {
 void block_tiles(int N, int k, int L, int rows, int blk_max, std::vector<int64_t>& row0,
                  std::vector<int32_t>& nrows, BlockList* blocks = nullptr) {
   const uint64_t nh = 1ull << (N - L);
+  int sizes[65];   // rows of a block by the popcount of its low words
+  for (int c = 0; c <= L; ++c) sizes[c] = (int)binom64(L, c);
   int64_t start = 0, cur0 = 0;
   int cur_rows = 0, cur_blk = 0, cur_b0 = 0, nblk = 0;
   auto close = [&]() {
@@ -477,10 +480,19 @@ void block_tiles(int N, int k, int L, int rows, int blk_max, std::vector<int64_t
       blocks->sub_nb.push_back(cur_blk);
     }
   };
+  const size_t subs = nh / std::max(1, blk_max) + 1;
+  row0.reserve(subs);
+  nrows.reserve(subs);
+  if (blocks) {
+    blocks->h.reserve(nh);
+    blocks->start.reserve(nh);
+    blocks->sub_b0.reserve(subs);
+    blocks->sub_nb.reserve(subs);
+  }
   for (uint64_t h = 0; h < nh; ++h) {
     const int c = k - __builtin_popcountll(h);
     if (c < 0 || c > L) continue;
-    const int size = (int)binom64(L, c);
+    const int size = sizes[c];
     if (cur_blk > 0 && (cur_rows + size > rows || cur_blk == blk_max)) {
       close();
       cur0 = start;
@@ -602,6 +614,7 @@ int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_ar
     for (int L : {10, 9}) {
       RunShape t = s;
       t.tune = slice_tune(p, n, s.precision, L);
+      t.slice_only = true;
       Planned Q;
       if (make_plan_shape(p, n, t, a_arr, b_arr, Q) == KPM_OK && Q.plan.block == 3) {
         P = std::move(Q);
@@ -856,6 +869,7 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
     }
   }
   int bspt = 1;
+  if (s.slice_only && D.block != 3) return KPM_EINVAL;
   if (resid && (D.block != 3 || spin)) return KPM_EINVAL;   // no slice plan for these problems
   D.resid = resid;
   if (D.block) D.row_ld = row_ld = 0;
@@ -895,8 +909,13 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
       if (bl) {
         if (P.blk_h.size() + bl->h.size() > (size_t)INT32_MAX) return KPM_EINVAL;
         P.probs[i].n_blk = (int32_t)bl->h.size();
-        P.blk_h.insert(P.blk_h.end(), bl->h.begin(), bl->h.end());
-        P.blk_start.insert(P.blk_start.end(), bl->start.begin(), bl->start.end());
+        if (P.blk_h.empty()) {
+          P.blk_h = std::move(bl->h);
+          P.blk_start = std::move(bl->start);
+        } else {
+          P.blk_h.insert(P.blk_h.end(), bl->h.begin(), bl->h.end());
+          P.blk_start.insert(P.blk_start.end(), bl->start.begin(), bl->start.end());
+        }
       }
       max_sub = std::max(max_sub, btile_row0[i].size());
       maxL = std::max(maxL, P.probs[i].blk_L);
@@ -959,6 +978,21 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
   D.dense = env_int("KPM_DENSE_LISTS", 0);
   const int64_t tile_rows = (int64_t)D.sub_rows * spt;
 
+  size_t all_tiles = 0, all_subs = 0;
+  for (int i = 0; i < n; ++i) {
+    const size_t units = (size_t)((total_columns(p[i], s) + rb - 1) / rb), subs = btile_row0[i].size();
+    all_subs += units * subs;
+    all_tiles += units * (D.block ? (subs + bspt - 1) / bspt : (size_t)((P.probs[i].dim + tile_rows - 1) / tile_rows));
+  }
+  P.tile_unit.reserve(all_tiles);
+  P.tile_row0.reserve(all_tiles);
+  P.tile_nrows.reserve(all_tiles);
+  if (D.block) {
+    P.tile_sub0.reserve(all_tiles + 1);
+    P.sub_nrows.reserve(all_subs);
+    P.sub_blk0.reserve(all_subs);
+    P.sub_nblk.reserve(all_subs);
+  }
   int64_t vec_elems = 0, part_len = 0, bd_len = 0;
   int32_t tiles = 0, col_off = 0;
   for (int i = 0; i < n; ++i) {
@@ -1121,6 +1155,7 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
         for (size_t j = 0; j < len; ++j)
           for (auto& q : queue) P.wg_rec.push_back(rec(j < q.size() ? q[j] : -1));
     }
+    P.wg_rec.reserve((size_t)tiles + 8 * P.units.size() + 8);
     if (D.xcd_remap == 3) {
       // done above
     } else if (D.xcd_remap == 2) {
