@@ -65,7 +65,7 @@ METRIC = "Chebyshev steps·dim/s + HBM GB/s at N=24 S^z=0; speedup vs FP64 at C(
 HBM_PEAK_GBS = 8000.0
 # step kernel families as reported by kpm_last_run_stats()["kernel"]
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X, dense float64 vector arithmetic
-KERNEL_FAMILY = {0: "step_kernel", 1: "row_kernel", 2: "block_kernel", 3: "tab_kernel", 4: "spin_kernel",
+KERNEL_FAMILY = {0: "step_kernel", 1: "row_kernel", 2: "block_kernel", 3: "tab_kernel", 4: "spin_split_kernel",
                  5: "slice_kernel", 6: "res_moments_kernel"}
 PROFILES = os.path.join(ROOT, "profiles")
 

@@ -215,8 +215,9 @@ size_t chebyshev_vectors_workspace_size(const kpm_problem* p, const kpm_params* 
 
 /* The Chebyshev vectors behind Eq. (6) for ONE problem: v_0 = the random
  * vectors of chebyshev_moments (same seeds and normalisation), v_1 = H' v_0,
- * v_{n+1} = 2 H' v_n - v_{n-1}; returns v_{n_vec} computed by the same plan
- * and step kernels as chebyshev_moments (q->M is ignored).
+ * v_{n+1} = 2 H' v_n - v_{n-1}; returns v_{n_vec} computed by the plan and
+ * step kernels of chebyshev_moments (q->M is ignored; the float64 moments of
+ * small sectors run on other kernels and agree with it to rounding).
  *  d_out device [dim][R_cols] row-major, R_cols = R (x2 for complex vectors,
  *        Re and Im adjacent; C(N, n_up) for the complete basis), float for
  *        KPM_FP32_STORE, double for KPM_FP64
@@ -409,7 +410,7 @@ typedef struct {
                               the block-table kernel reads per-block tables
                               instead: per block of low-bit states
                               12 + 6 * (high-high bonds) + 4 * (mixed bonds);
-                              the spin-s kernel reads 8 + 8 * n_bonds per row
+                              the spin-s kernel reads 4 or 8 + 8 * n_bonds per row
                               (digit string, neighbour-rank slots) */
   double state_col_steps;  /* sum over blocks of dim * real columns * steps */
   int32_t col_block;       /* real columns per block chosen */

@@ -2122,13 +2122,39 @@ size_t moments_workspace(const kpm_problem* p, int n, const kpm_params& q) {
   return r ? r : stepped_workspace(p, n, q);
 }
 
-size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q) {
+size_t moments_lanczos_bytes(const kpm_problem* p, int n, const kpm_params& q) {
   std::vector<kpm_problem> need;
   for (int i = 0; i < n; ++i)
     if (std::isnan(p[i].e_lo) || std::isnan(p[i].e_hi)) need.push_back(p[i]);
-  const size_t lz = need.empty() ? 0 : lanczos_bytes(need.data(), (int)need.size(), lanczos_steps_of(q));
+  return need.empty() ? 0 : lanczos_bytes(need.data(), (int)need.size(), lanczos_steps_of(q));
+}
+
+// shape_of with the default slice kernel left out where its blocks, all padded
+// to one width, would not fit the allocation-free entry point's array and the
+// other kernels' do (20-site sawtooth chain, 11 float32 columns: 84 and 62 MB).
+RunShape moments_shape(const kpm_problem* p, int n, const kpm_params& q, const Tune* t = nullptr) {
+  RunShape s = shape_of(q, t);
+  if (s.tune.kernel >= 0) return s;
+  double least = 0.0;   // two vectors of the real columns
+  for (int i = 0; i < n; ++i)
+    least += 2.0 * (q.precision == KPM_FP64 ? 8 : 4) * (double)prob_dim(p[i]) * (double)total_columns(p[i], s);
+  if (least > (double)KPM_NOALLOC_MAX_BYTES) return s;
+  const size_t lz = moments_lanczos_bytes(p, n, q);
+  auto fits = [&]() {
+    Planned P;
+    return make_plan(p, n, s, nullptr, nullptr, P) != KPM_OK || (s.allow_slice && P.plan.block != 3) ||
+           moments_layout(P, n_steps(q.M), lz).total <= KPM_NOALLOC_MAX_BYTES;
+  };
+  if (fits()) return s;
+  s.allow_slice = false;
+  if (!fits()) s.allow_slice = true;
+  return s;
+}
+
+size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q) {
+  const size_t lz = moments_lanczos_bytes(p, n, q);
   Planned P;
-  if (make_plan(p, n, shape_of(q), nullptr, nullptr, P) != KPM_OK) return 0;
+  if (make_plan(p, n, moments_shape(p, n, q), nullptr, nullptr, P) != KPM_OK) return 0;
   size_t total = moments_layout(P, n_steps(q.M), lz).total;
   if (q.autotune) {
     // Before the first trial runs the workspace must hold every candidate's
@@ -3084,7 +3110,7 @@ int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, doubl
   if (known) {
     try {
       planned = std::async(std::launch::async,
-                           [&]() { return make_plan(p, n, shape_of(*q, &tn), nullptr, nullptr, P); });
+                           [&]() { return make_plan(p, n, moments_shape(p, n, *q, &tn), nullptr, nullptr, P); });
     } catch (const std::system_error&) {
       known = false;   // no thread to be had: plan after the bounds
     }
@@ -3101,7 +3127,7 @@ int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, doubl
       r = get_tune(p, n, *q, a.data(), b.data(), work, need, st, tn);
       if (r != KPM_OK) return r;
     }
-    r = make_plan(p, n, shape_of(*q, &tn), a.data(), b.data(), P);
+    r = make_plan(p, n, moments_shape(p, n, *q, &tn), a.data(), b.data(), P);
     if (r != KPM_OK) return r;
   }
   const MomLayout L = moments_layout(P, n_steps(q->M), 0);
