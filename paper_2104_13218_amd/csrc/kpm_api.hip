@@ -2968,8 +2968,6 @@ FtlmLayout ftlm_layout(const Planned& P, int steps) {
 
 // ------------------------------------------------ exact spectra (small sectors)
 
-constexpr int kEdMaxDim = 1024;
-
 struct EdPlan {
   std::vector<EigProb> probs;
   std::vector<uint32_t> bmask;
@@ -3028,7 +3026,7 @@ int ed_plan(const kpm_problem* p, int n, int max_dim, EdPlan& E) {
   E.o_tab = put(std::max<size_t>(E.tables.size(), 1) * 4);
   E.o_err = put(256);
   E.o_mat = put((size_t)std::max<int64_t>(mat, 1) * 8);
-  E.o_vecs = put((size_t)std::max<int64_t>(E.vec_len, 1) * 4 * 8);
+  E.o_vecs = put((size_t)std::max<int64_t>(E.vec_len, 1) * 6 * 8);
   E.total = o;
   return KPM_OK;
 }
@@ -3898,9 +3896,11 @@ int kpm_sector_eigenvalues(const kpm_problem* p, int32_t n, int32_t max_dim, dou
     a.mat = reinterpret_cast<double*>(work + E.o_mat);
     double* vecs = reinterpret_cast<double*>(work + E.o_vecs);
     a.hv = vecs;
-    a.hp = vecs + E.vec_len;
-    a.hd = vecs + 2 * E.vec_len;
-    a.he = vecs + 3 * E.vec_len;
+    a.vec_len = E.vec_len;
+    a.hp = vecs + 2 * E.vec_len;
+    a.hw = vecs + 3 * E.vec_len;
+    a.hd = vecs + 4 * E.vec_len;
+    a.he = vecs + 5 * E.vec_len;
     a.evals = d_evals;
     a.ld = max_dim;
     a.max_dim = 1;

@@ -4,7 +4,7 @@
 // The dense float64 matrix of H on each sector basis (rank order) is built in
 // the workspace and reduced to a symmetric tridiagonal matrix by Householder
 // reflections applied from both sides, one column per step for all sectors at
-// once (three launches per step, the trailing block split over row tiles so
+// once (two launches per step, the trailing block split over row tiles so
 // that large sectors spread over the chip); the eigenvalues of the
 // tridiagonal matrix then come from bisection on Sturm counts, one
 // workgroup per sector and one eigenvalue per thread.
@@ -120,20 +120,50 @@ __global__ __launch_bounds__(kThreads) void ed_build_kernel(const EigArgs a) {
 // Householder step k, part 1 (one workgroup per active sector): the part of
 // row k right of the diagonal, x, becomes alpha e_1 under I - 2 v v^T with
 // v = (x - alpha e_1) / |x - alpha e_1|, alpha = -sign(x_0) |x|; d[k], e[k]
-// are recorded.  A row that is already zero there keeps v = 0.
+// are recorded.  A row that is already zero there keeps v = 0.  Step k - 1's
+// update A' -= v w^T + w v^T (w = p - K v, K = v.p) has not reached the matrix
+// yet: it is applied to row k here, and to the other rows in part 2, which
+// reads the trailing block once a step for both.  v of step k lies in slot
+// k & 1.
 __global__ __launch_bounds__(kThreads) void ed_hh_vec_kernel(const EigArgs a, int k) {
   __shared__ double sh[4];
+  __shared__ double x[kEdMaxDim];
   const EigProb P = a.probs[blockIdx.x];
   const int D = P.dim, n2 = D - k - 1;
   if (k + 2 >= D) return;
-  const double* x = a.mat + P.mat_off + (int64_t)k * D + (k + 1);
-  double* v = a.hv + P.vec_off;
-  double part = 0.0;
-  for (int i = threadIdx.x; i < n2; i += kThreads) part = fma(x[i], x[i], part);
-  const double sigma = ed_sum(part, sh);
+  const double* row = a.mat + P.mat_off + (int64_t)k * D + k;   // from the diagonal on
+  double* v = a.hv + (k & 1) * a.vec_len + P.vec_off;
+  double part = 0.0, diag = 0.0;
+  if (k == 0) {
+    if (threadIdx.x == 0) diag = row[0];
+    for (int i = threadIdx.x; i < n2; i += kThreads) {
+      x[i] = row[i + 1];
+      part = fma(x[i], x[i], part);
+    }
+  } else {
+    const double* u = a.hv + ((k - 1) & 1) * a.vec_len + P.vec_off;
+    const double* pv = a.hp + P.vec_off;
+    double* w = a.hw + P.vec_off;
+    double kk = 0.0;
+    for (int i = threadIdx.x; i <= n2; i += kThreads) kk = fma(u[i], pv[i], kk);
+    const double K = ed_sum(kk, sh);
+    const double u0 = u[0], w0 = fma(-K, u0, pv[0]);
+    for (int i = threadIdx.x; i <= n2; i += kThreads) {
+      const double wi = fma(-K, u[i], pv[i]);
+      w[i] = wi;
+      const double r = fma(-u0, wi, fma(-w0, u[i], row[i]));
+      if (i == 0) {
+        diag = r;
+      } else {
+        x[i - 1] = r;
+        part = fma(r, r, part);
+      }
+    }
+  }
+  const double sigma = ed_sum(part, sh);   // x is whole behind its barriers
   const double x0 = x[0];
   const double tail = sigma - x0 * x0;
-  if (threadIdx.x == 0) a.hd[P.vec_off + k] = a.mat[P.mat_off + (int64_t)k * D + k];
+  if (threadIdx.x == 0) a.hd[P.vec_off + k] = diag;
   if (!(tail > 1e-300)) {
     if (threadIdx.x == 0) a.he[P.vec_off + k] = x0;
     for (int i = threadIdx.x; i < n2; i += kThreads) v[i] = 0.0;
@@ -146,50 +176,39 @@ __global__ __launch_bounds__(kThreads) void ed_hh_vec_kernel(const EigArgs a, in
   for (int i = threadIdx.x; i < n2; i += kThreads) v[i] = (i == 0 ? v0 : x[i]) * inv;
 }
 
-// Part 2 (grid: active sectors x tiles of kEdRows rows): p = 2 A' v over the
-// trailing block A' (rows and columns k+1..D-1); each wave takes rows of the
-// tile, its lanes stride over the row.
-__global__ __launch_bounds__(kThreads) void ed_hh_matvec_kernel(const EigArgs a, int k) {
+// Part 2 (grid: active sectors x tiles of kEdRows rows): step k - 1's update of
+// the trailing block A' (rows and columns k+1..D-1), then p = 2 A' v; each wave
+// takes rows of the tile, its lanes stride over the row.  Bound by the block's
+// read and write, and by the launches.  72 sectors of up to 1001 states:
+// with the update in a launch of its own (a second read, and every
+// workgroup's own sum of K) a step took 24.0 us, 18.8 now.
+__global__ __launch_bounds__(kThreads) void ed_hh_rows_kernel(const EigArgs a, int k) {
   const EigProb P = a.probs[blockIdx.x];
   const int D = P.dim, n2 = D - k - 1;
   if (k + 2 >= D) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const double* v = a.hv + P.vec_off;
+  const double* v = a.hv + (k & 1) * a.vec_len + P.vec_off;
+  const double* u = a.hv + ((k + 1) & 1) * a.vec_len + P.vec_off + 1;   // of step k - 1, whose block had one row more
+  const double* w = a.hw + P.vec_off + 1;
   double* pv = a.hp + P.vec_off;
   for (int rr = wv; rr < kEdRows; rr += kThreads / 64) {
     const int i = blockIdx.y * kEdRows + rr;
     if (i >= n2) break;
-    const double* row = a.mat + P.mat_off + (int64_t)(k + 1 + i) * D + (k + 1);
+    double* row = a.mat + P.mat_off + (int64_t)(k + 1 + i) * D + (k + 1);
     double acc = 0.0;
-    for (int j = lane; j < n2; j += 64) acc = fma(row[j], v[j], acc);
+    if (k == 0) {
+      for (int j = lane; j < n2; j += 64) acc = fma(row[j], v[j], acc);
+    } else {
+      const double ui = u[i], wi = w[i];
+      for (int j = lane; j < n2; j += 64) {
+        const double r = fma(-ui, w[j], fma(-wi, u[j], row[j]));
+        row[j] = r;
+        acc = fma(r, v[j], acc);
+      }
+    }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
     if (lane == 0) pv[i] = 2.0 * acc;
-  }
-}
-
-// Part 3 (same grid): K = v.p, w = p - K v, A' -= v w^T + w v^T on the tile's
-// rows (every workgroup sums K in the same order).
-__global__ __launch_bounds__(kThreads) void ed_hh_update_kernel(const EigArgs a, int k) {
-  __shared__ double sh[4];
-  const EigProb P = a.probs[blockIdx.x];
-  const int D = P.dim, n2 = D - k - 1;
-  if (k + 2 >= D) return;
-  const double* v = a.hv + P.vec_off;
-  const double* pv = a.hp + P.vec_off;
-  double part = 0.0;
-  for (int i = threadIdx.x; i < n2; i += kThreads) part = fma(v[i], pv[i], part);
-  const double K = ed_sum(part, sh);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int rr = wv; rr < kEdRows; rr += kThreads / 64) {
-    const int i = blockIdx.y * kEdRows + rr;
-    if (i >= n2) break;
-    const double vi = v[i], wi = fma(-K, vi, pv[i]);
-    double* row = a.mat + P.mat_off + (int64_t)(k + 1 + i) * D + (k + 1);
-    for (int j = lane; j < n2; j += 64) {
-      const double wj = fma(-K, v[j], pv[j]);
-      row[j] = fma(-vi, wj, fma(-wi, v[j], row[j]));
-    }
   }
 }
 
@@ -234,9 +253,19 @@ __global__ __launch_bounds__(kThreads) void ed_tri_kernel(const EigArgs a) {
   const double* A = a.mat + P.mat_off;
   if (tid == 0) {
     if (D >= 2) {
-      d[D - 2] = A[(int64_t)(D - 2) * D + (D - 2)];
-      d[D - 1] = A[(int64_t)(D - 1) * D + (D - 1)];
-      e[D - 2] = A[(int64_t)(D - 1) * D + (D - 2)];
+      double u0 = 0.0, u1 = 0.0, w0 = 0.0, w1 = 0.0;   // the last step's update
+      if (D >= 3) {
+        const double* u = a.hv + ((D - 3) & 1) * a.vec_len + P.vec_off;
+        const double p0 = a.hp[P.vec_off], p1 = a.hp[P.vec_off + 1];
+        u0 = u[0];
+        u1 = u[1];
+        const double K = fma(u1, p1, u0 * p0);
+        w0 = fma(-K, u0, p0);
+        w1 = fma(-K, u1, p1);
+      }
+      d[D - 2] = fma(-u0, w0, fma(-w0, u0, A[(int64_t)(D - 2) * D + (D - 2)]));
+      d[D - 1] = fma(-u1, w1, fma(-w1, u1, A[(int64_t)(D - 1) * D + (D - 1)]));
+      e[D - 2] = fma(-u1, w0, fma(-w1, u0, A[(int64_t)(D - 1) * D + (D - 2)]));
     } else {
       d[0] = A[0];
     }
@@ -316,8 +345,7 @@ hipError_t launch_sector_eig(const EigArgs& a, const int* dims, int n_sectors, s
     const int n2 = dims[0] - k - 1;
     const dim3 grid(active, (n2 + kEdRows - 1) / kEdRows);
     hipLaunchKernelGGL(ed_hh_vec_kernel, dim3(active), dim3(kThreads), 0, st, a, k);
-    hipLaunchKernelGGL(ed_hh_matvec_kernel, grid, dim3(kThreads), 0, st, a, k);
-    hipLaunchKernelGGL(ed_hh_update_kernel, grid, dim3(kThreads), 0, st, a, k);
+    hipLaunchKernelGGL(ed_hh_rows_kernel, grid, dim3(kThreads), 0, st, a, k);
   }
   hipLaunchKernelGGL(ed_tri_kernel, dim3(n_sectors), dim3(kThreads), 0, st, a);
   hipLaunchKernelGGL(ed_bisect_kernel, dim3(n_sectors, (dims[0] + 63) / 64), dim3(64), lds_finish, st, a);

@@ -6,7 +6,7 @@
 // Lanczos recursion itself runs through the same step kernels as the
 // Chebyshev recursion; these kernels turn its coefficients into Ritz values
 // and weights and sum the thermodynamics (with the optional Zeeman term h S^z,
-// mirror sectors at -S^z, as in thermo_field_kernel).
+// mirror sectors at -S^z, as in points_kernel).
 #include <hip/hip_runtime.h>
 
 #include "kpm_internal.h"

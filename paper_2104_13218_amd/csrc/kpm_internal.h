@@ -346,6 +346,7 @@ struct EigProb {
   int64_t vec_off;             // doubles from the work-vector bases (hv, hp, hd, he)
 };
 
+constexpr int kEdMaxDim = 1024;   // largest sector diagonalised (kpm_sector_eigenvalues)
 constexpr int kEdRows = 4;     // rows of the trailing block per workgroup (Householder steps)
 
 struct EigArgs {
@@ -355,13 +356,16 @@ struct EigArgs {
   const uint32_t* binom;       // C(n, j) [33][33]
   const uint32_t* tables;      // spin-s rank tables P[i][r][d] (as ProbDev)
   double* mat;                 // dense sector matrices
-  double* hv;                  // per sector [max(dim, 4)]: Householder vector of the current
-                               // step, then the bisection interval, pivot floor and radius
+  double* hv;                  // [2][vec_len], per sector [max(dim, 4)]: Householder vectors of
+                               // the current and the last step, then (first half) the
+                               // bisection interval, pivot floor and radius
   double* hp;                  // per sector [dim]: 2 A' v
+  double* hw;                  // per sector [dim]: w of the last step's update
   double* hd;                  // per sector [dim]: diagonal of the tridiagonal matrix
   double* he;                  // per sector [dim]: its off-diagonal
   double* evals;               // [rows][ld] ascending eigenvalues
   int* err;                    // bit 1: rank out of range
+  int64_t vec_len;             // doubles of each of these vectors, all sectors
   int32_t ld, max_dim;
   int32_t o_bonds;             // LDS byte offset of the bond J values (build kernel)
 };
