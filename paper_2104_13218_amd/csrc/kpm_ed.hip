@@ -181,7 +181,10 @@ __global__ __launch_bounds__(kThreads) void ed_hh_vec_kernel(const EigArgs a, in
 // takes rows of the tile, its lanes stride over the row.  Bound by the block's
 // read and write, and by the launches.  72 sectors of up to 1001 states:
 // with the update in a launch of its own (a second read, and every
-// workgroup's own sum of K) a step took 24.0 us, 18.8 now.
+// workgroup's own sum of K) a step took 24.0 us, 18.1 now
+// (18.8 with one row a wave and its own reads of the three vectors; four rows a
+// wave are faster in the first steps, 50 us against 55, and slower in the
+// last, 2.9 against 2.3).
 __global__ __launch_bounds__(kThreads) void ed_hh_rows_kernel(const EigArgs a, int k) {
   const EigProb P = a.probs[blockIdx.x];
   const int D = P.dim, n2 = D - k - 1;
@@ -191,24 +194,41 @@ __global__ __launch_bounds__(kThreads) void ed_hh_rows_kernel(const EigArgs a, i
   const double* u = a.hv + ((k + 1) & 1) * a.vec_len + P.vec_off + 1;   // of step k - 1, whose block had one row more
   const double* w = a.hw + P.vec_off + 1;
   double* pv = a.hp + P.vec_off;
-  for (int rr = wv; rr < kEdRows; rr += kThreads / 64) {
-    const int i = blockIdx.y * kEdRows + rr;
-    if (i >= n2) break;
-    double* row = a.mat + P.mat_off + (int64_t)(k + 1 + i) * D + (k + 1);
-    double acc = 0.0;
-    if (k == 0) {
-      for (int j = lane; j < n2; j += 64) acc = fma(row[j], v[j], acc);
-    } else {
-      const double ui = u[i], wi = w[i];
-      for (int j = lane; j < n2; j += 64) {
-        const double r = fma(-ui, w[j], fma(-wi, u[j], row[j]));
-        row[j] = r;
-        acc = fma(r, v[j], acc);
-      }
-    }
+  // a wave's rows together: the three vectors are read once for all of them
+  constexpr int kWaves = kThreads / 64, kOwn = kEdRows / kWaves;
+  const int i0 = blockIdx.y * kEdRows + wv;
+  if (i0 >= n2) return;   // the same across the wave
+  double* row[kOwn];
+  double ui[kOwn], wi[kOwn], acc[kOwn];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-    if (lane == 0) pv[i] = 2.0 * acc;
+  for (int q = 0; q < kOwn; ++q) {
+    const int i = min(i0 + q * kWaves, n2 - 1);   // past the last row: not stored
+    row[q] = a.mat + P.mat_off + (int64_t)(k + 1 + i) * D + (k + 1);
+    ui[q] = k > 0 ? u[i] : 0.0;
+    wi[q] = k > 0 ? w[i] : 0.0;
+    acc[q] = 0.0;
+  }
+  for (int j = lane; j < n2; j += 64) {
+    const double vj = v[j], uj = k > 0 ? u[j] : 0.0, wj = k > 0 ? w[j] : 0.0;
+    double r[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q)
+      if (q == 0 || i0 + q * kWaves < n2) r[q] = row[q][j];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      if (q > 0 && i0 + q * kWaves >= n2) continue;
+      if (k > 0) {
+        r[q] = fma(-ui[q], wj, fma(-wi[q], uj, r[q]));
+        row[q][j] = r[q];
+      }
+      acc[q] = fma(r[q], vj, acc[q]);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kOwn; ++q) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_down(acc[q], off, 64);
+    if (lane == 0 && i0 + q * kWaves < n2) pv[i0 + q * kWaves] = 2.0 * acc[q];
   }
 }
 

@@ -347,7 +347,7 @@ struct EigProb {
 };
 
 constexpr int kEdMaxDim = 1024;   // largest sector diagonalised (kpm_sector_eigenvalues)
-constexpr int kEdRows = 4;     // rows of the trailing block per workgroup (Householder steps)
+constexpr int kEdRows = 8;     // rows of the trailing block per workgroup (Householder steps)
 
 struct EigArgs {
   const EigProb* probs;        // one per workgroup
