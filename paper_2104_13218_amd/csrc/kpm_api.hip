@@ -3385,7 +3385,7 @@ size_t chebyshev_vectors_workspace_size(const kpm_problem* p, const kpm_params* 
     if (check_problems(p, 1) != KPM_OK || !q || n_vec < 0) return 0;
     const kpm_params q2 = vectors_params(*q, n_vec);
     if (check_params(q2) != KPM_OK) return 0;
-    return moments_workspace(p, 1, q2);
+    return stepped_workspace(p, 1, q2);
   });
 }
 
@@ -3399,7 +3399,8 @@ int chebyshev_vectors(const kpm_problem* p, const kpm_params* q, int32_t n_vec, 
     if (check_params(q2) != KPM_OK) return KPM_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     StreamSync guard{st};
-    const size_t need = moments_workspace(p, 1, q2);
+    // every sector on the step kernels, whose vectors it returns
+    const size_t need = stepped_workspace(p, 1, q2);
     if (need == 0) return KPM_EINVAL;
     DevBuf own;
     unsigned char* work = static_cast<unsigned char*>(d_work);
