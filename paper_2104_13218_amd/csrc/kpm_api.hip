@@ -3411,15 +3411,17 @@ int chebyshev_vectors(const kpm_problem* p, const kpm_params* q, int32_t n_vec, 
     } else if (work_bytes < need) {
       return KPM_EWORKSPACE;
     }
+    const RunShape shape = moments_shape(p, 1, q2);   // as the size query
     Planned P0;
-    r = make_plan(p, 1, shape_of(q2), nullptr, nullptr, P0);
+    r = make_plan(p, 1, shape, nullptr, nullptr, P0);
     if (r != KPM_OK) return r;
-    const MomLayout L0 = moments_layout(P0, n_steps(q2.M), 0);
+    const MomLayout L0 = moments_layout(P0, n_steps(q2.M), moments_lanczos_bytes(p, 1, q2));
+    if (L0.total > need) return KPM_EWORKSPACE;
     std::vector<double> a, b;
     r = resolve_scale(p, 1, q2, Spare{work + L0.lz, 0, true}, st, a, b);
     if (r != KPM_OK) return r;
     Planned P;
-    r = make_plan(p, 1, shape_of(q2), a.data(), b.data(), P);
+    r = make_plan(p, 1, shape, a.data(), b.data(), P);
     if (r != KPM_OK) return r;
     const MomLayout L = moments_layout(P, n_steps(q2.M), 0);
     std::vector<unsigned char> staging;

@@ -58,3 +58,37 @@ def test_vectors_of_small_sectors(kpm, n, n_up, R, given, kind):
     V0 = rng.random_columns(kind, 5, 0, n_up, R, sec.dim)[0]
     want = moments.chebyshev_dots(hamiltonian.rescaled(H, *ab), V0, 4, keep=True)[2][4]
     assert np.abs(V - want).max() <= 1e-12 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("n,n_up,precision", [
+    (8, 4, "fp64"), (16, 8, "fp32"), (17, 9, "fp64"), (18, 9, "fp64"), (20, 10, "fp32"), (20, 10, "fp64"),
+    (21, 11, "fp32"), (22, 11, "fp32"), (22, 12, "fp32"), (22, 12, "fp64"), (22, 14, "fp32")])
+@pytest.mark.parametrize("R", [1, 5, 9, 11, 12, 41, 44, 100])
+@pytest.mark.parametrize("bounds", [(-9.0, 9.0), None])
+def test_plan_of_the_call_fits_the_queried_size(n, n_up, precision, R, bounds):
+    """The call plans on the host and compares its layout with the workspace
+    before the first access to a device: KPM_EWORKSPACE would say that the two
+    disagree, without a device it gets as far as KPM_EDEVICE."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("needs a machine without a GPU: the pointers lead nowhere")
+    ps = K.ProblemSet([W.Sector(W.ring(n), n_up, 0)], [bounds])
+    q = K.make_params(8, R, "rademacher", precision, 0.025, 1)
+    lib = K.load()
+    need = int(lib.chebyshev_vectors_workspace_size(ps.arr, ctypes.byref(q), 4))
+    assert need > 0
+    assert lib.chebyshev_vectors(ps.arr, ctypes.byref(q), 4, 256, None, 4096, need, None) == K.KPM_EDEVICE
+    assert lib.chebyshev_vectors(ps.arr, ctypes.byref(q), 4, 256, None, 4096, need - 1, None) == K.KPM_EWORKSPACE
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,n_up,R", [(18, 9, 41), (20, 10, 41), (20, 12, 60)])
+def test_vectors_next_to_the_allocation_free_limit(kpm, n, n_up, R):
+    """Float32 columns that fit 64 MiB unpadded but not in the slice kernel's
+    padded blocks (20 sites), and ones far from it, on sampled rows."""
+    from oracle import rows
+    sec = W.Sector(W.ring(n), n_up, 0)
+    V, ab = guarded_vectors(kpm, sec, 3, R, "rademacher", "fp32", 2, (-10.0, 6.0), 32 << 20)
+    at = np.concatenate([np.random.default_rng(1).choice(sec.dim, 24, replace=False), [0, sec.dim - 1]])
+    want = rows.recursion_rows(sec.cluster, n_up, ab[0], ab[1], "rademacher", 2, R, at, 3, store=np.float32)
+    assert np.abs(V[at] - want).max() <= 1e-6 * np.abs(want).max()
