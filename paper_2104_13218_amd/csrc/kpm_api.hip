@@ -575,14 +575,16 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
 
 // Whether the split spin kernel takes a spin-s plan, and the halves of its
 // problems (B0, B1, B2): up to 16 sites (two 32-bit words of digits) with at
-// most 2^16 low and high codes each, per-bond tables in half of the LDS that
-// four workgroups leave each other, and records no larger than the lists that
-// they replace (few rows of many sites: their lists are the smaller).
+// most 2^16 low and high codes each, a bond in every problem (the kernel
+// requests the next row's records beside the first bonds' rows), per-bond
+// tables in half of the LDS that four workgroups leave each other, and records
+// no larger than the lists that they replace (few rows of many sites: their
+// lists are the smaller).
 bool split_spin(Planned& P, int cpl) {
   if (env_int("KPM_SPIN_SPLIT", 1) == 0) return false;
   int64_t lists = 0, records = 0;
   for (ProbDev& d : P.probs) {
-    if (d.n_sites < 2 || d.n_sites > 16) return false;
+    if (d.n_sites < 2 || d.n_sites > 16 || d.n_bonds < 1) return false;
     d.B0 = d.n_sites / 2;
     int64_t low = 1, high = 1;
     for (int i = 0; i < d.n_sites; ++i) (i < d.B0 ? low : high) *= d.two_s + 1;
