@@ -3318,9 +3318,10 @@ int kpm_spectral_bounds(const kpm_problem* p, int32_t n, int32_t steps, double m
     hipStream_t st = static_cast<hipStream_t>(stream);
     StreamSync guard{st};
     DevBuf buf;
-    int r = buf.alloc(lanczos_bytes(p, n, steps));
+    const size_t bytes = lanczos_bytes(p, n, steps);
+    int r = buf.alloc(bytes);
     if (r != KPM_OK) return r;
-    return run_lanczos(p, n, steps, margin, seed, e_lo_hi, Spare{static_cast<unsigned char*>(buf.p), 0, true}, st);
+    return run_lanczos(p, n, steps, margin, seed, e_lo_hi, Spare{static_cast<unsigned char*>(buf.p), bytes, true}, st);
   });
 }
 
@@ -3414,18 +3415,16 @@ int chebyshev_vectors(const kpm_problem* p, const kpm_params* q, int32_t n_vec, 
       return KPM_EWORKSPACE;
     }
     const RunShape shape = moments_shape(p, 1, q2);   // as the size query
-    Planned P0;
-    r = make_plan(p, 1, shape, nullptr, nullptr, P0);
-    if (r != KPM_OK) return r;
-    const MomLayout L0 = moments_layout(P0, n_steps(q2.M), moments_lanczos_bytes(p, 1, q2));
-    if (L0.total > need) return KPM_EWORKSPACE;
-    std::vector<double> a, b;
-    r = resolve_scale(p, 1, q2, Spare{work + L0.lz, 0, true}, st, a, b);
-    if (r != KPM_OK) return r;
     Planned P;
-    r = make_plan(p, 1, shape, a.data(), b.data(), P);
+    r = make_plan(p, 1, shape, nullptr, nullptr, P);
     if (r != KPM_OK) return r;
-    const MomLayout L = moments_layout(P, n_steps(q2.M), 0);
+    const MomLayout L = moments_layout(P, n_steps(q2.M), moments_lanczos_bytes(p, 1, q2));
+    if (L.total > need) return KPM_EWORKSPACE;
+    // the bounds run first and may use the whole region
+    std::vector<double> a, b;
+    r = resolve_scale(p, 1, q2, Spare{work, need, true}, st, a, b);
+    if (r != KPM_OK) return r;
+    apply_scale(p, 1, a.data(), b.data(), P);
     std::vector<unsigned char> staging;
     r = upload_plan(P, work + L.plan, staging, st);
     if (r != KPM_OK) return r;
@@ -3569,12 +3568,9 @@ int chebyshev_moments_ckpt(const kpm_problem* p, int32_t n, const kpm_params* q,
     if (resident_gradient(p, n, *q))
       return res_grad_forward(p, n, *q, nullptr, ckpt_every, d_mu, d_ab, work,
                               grad_layout(p, n, *q, count_nan(p, n), ckpt_every), st);
-    Planned P0;
-    r = make_plan(p, n, shape_of(*q), nullptr, nullptr, P0);
-    if (r != KPM_OK) return r;
-    const MomLayout L0 = moments_layout(P0, n_steps(q->M), 0);
+    // the bounds run first and may use the whole region
     std::vector<double> a, b;
-    r = resolve_scale(p, n, *q, Spare{work + L0.lz, 0, true}, st, a, b);
+    r = resolve_scale(p, n, *q, Spare{work, need, true}, st, a, b);
     if (r != KPM_OK) return r;
     std::vector<double> h_ab(2 * n);
     for (int i = 0; i < n; ++i) {
@@ -3710,13 +3706,9 @@ int kpm_thermo_grad(const kpm_problem* p, int32_t n, const kpm_params* q, int32_
       r = between();
       return r != KPM_OK ? r : res_grad_reverse(p, n, *q, nullptr, lam, ckpt_every, d_dJ, work, L, st);
     }
-    // bounds and (a, b) as chebyshev_moments resolves them
-    Planned P0;
-    r = make_plan(p, n, shape_of(*q), nullptr, nullptr, P0);
-    if (r != KPM_OK) return r;
-    const MomLayout L0 = moments_layout(P0, n_steps(q->M), 0);
+    // bounds and (a, b) as chebyshev_moments resolves them, first and in the whole region
     std::vector<double> a, b;
-    r = resolve_scale(p, n, *q, Spare{work + L0.lz, 0, true}, st, a, b);
+    r = resolve_scale(p, n, *q, Spare{work, need, true}, st, a, b);
     if (r != KPM_OK) return r;
     std::vector<double> h_ab(2 * n);
     for (int i = 0; i < n; ++i) {
