@@ -2420,17 +2420,18 @@ FinalArgs res_final(const ResRun& R, const ResLayout& L, unsigned char* work, in
 // ------------------------------------------------ gradient, resident sectors
 
 // Whether the gradient calls run resident (kpm_resident.hip); the checkpoints
-// keep as many vectors as on the step kernels.
+// keep as many vectors as on the step kernels.  Neither this nor the layout
+// depends on the problems' windows (there is room for the bounds of all), so
+// that the reverse sweep finds what the forward pass left where its call gives
+// the windows that the forward call estimated.
 bool resident_gradient(const kpm_problem* p, int n, const kpm_params& q) {
   if (q.precision != KPM_FP64 || q.col_block != 0 || std::getenv("KPM_ADJ_FWD") || !resident_problems(p, n)) return false;
-  if (count_nan(p, n) && lanczos_steps_of(q) > kResLanczos) return false;
+  if (lanczos_steps_of(q) > kResLanczos) return false;
   return res_columns(p, n, q) <= (int64_t(1) << 24);
 }
 
-// The layout depends on the problems as the caller gave them (`n_lz` of their
-// windows open), so that the reverse sweep of a later call finds it.
-ResLayout grad_layout(const kpm_problem* p, int n, const kpm_params& q, int n_lz, int ckpt_every) {
-  return res_layout(p, n, res_columns(p, n, q), n_steps(q.M), n_lz, q.vec_kind == KPM_VEC_BASIS, ckpt_every);
+ResLayout grad_layout(const kpm_problem* p, int n, const kpm_params& q, int ckpt_every) {
+  return res_layout(p, n, res_columns(p, n, q), n_steps(q.M), n, q.vec_kind == KPM_VEC_BASIS, ckpt_every);
 }
 
 // Bounds and moments with the forward vectors kept in `work`; d_ab0 (device):
@@ -2571,7 +2572,7 @@ RunShape adj_shape(const kpm_params& q) {
 }
 
 size_t vjp_workspace(const kpm_problem* p, int n, const kpm_params& q, int ckpt_every) {
-  if (resident_gradient(p, n, q)) return grad_layout(p, n, q, count_nan(p, n), ckpt_every).total;
+  if (resident_gradient(p, n, q)) return grad_layout(p, n, q, ckpt_every).total;
   Planned P, F;
   if (make_plan(p, n, adj_shape(q), nullptr, nullptr, P) != KPM_OK) return 0;
   const bool fwd = forward_plan_for(p, n, q, P, nullptr, nullptr, F);
@@ -3532,7 +3533,7 @@ int chebyshev_moments_vjp(const kpm_problem* p, int32_t n, const kpm_params* q,
       return KPM_EWORKSPACE;
     }
     if (resident_gradient(p, n, *q)) {
-      const ResLayout L = grad_layout(p, n, *q, count_nan(p, n), ckpt_every);
+      const ResLayout L = grad_layout(p, n, *q, ckpt_every);
       r = res_grad_forward(p, n, *q, d_ab, ckpt_every, nullptr, nullptr, work, L, st);
       return r != KPM_OK ? r : res_grad_reverse(p, n, *q, nullptr, d_dmu, ckpt_every, d_dJ, work, L, st);
     }
@@ -3567,7 +3568,7 @@ int chebyshev_moments_ckpt(const kpm_problem* p, int32_t n, const kpm_params* q,
     unsigned char* work = static_cast<unsigned char*>(d_work);
     if (resident_gradient(p, n, *q))
       return res_grad_forward(p, n, *q, nullptr, ckpt_every, d_mu, d_ab, work,
-                              grad_layout(p, n, *q, count_nan(p, n), ckpt_every), st);
+                              grad_layout(p, n, *q, ckpt_every), st);
     // the bounds run first and may use the whole region
     std::vector<double> a, b;
     r = resolve_scale(p, n, *q, Spare{work, need, true}, st, a, b);
@@ -3597,7 +3598,7 @@ int chebyshev_moments_vjp_resume(const kpm_problem* p, int32_t n, const kpm_para
     if (work_bytes < need) return KPM_EWORKSPACE;
     if (resident_gradient(p, n, *q))
       return res_grad_reverse(p, n, *q, d_ab, d_dmu, ckpt_every, d_dJ, static_cast<unsigned char*>(d_work),
-                              grad_layout(p, n, *q, count_nan(p, n), ckpt_every), st);
+                              grad_layout(p, n, *q, ckpt_every), st);
     std::vector<double> h_ab(2 * n);
     KPM_HIP(hipMemcpyAsync(h_ab.data(), d_ab, h_ab.size() * 8, hipMemcpyDeviceToHost, st));
     KPM_HIP(hipStreamSynchronize(st));
@@ -3699,7 +3700,7 @@ int kpm_thermo_grad(const kpm_problem* p, int32_t n, const kpm_params* q, int32_
       return KPM_OK;
     };
     if (resident_gradient(p, n, *q)) {
-      const ResLayout L = grad_layout(p, n, *q, count_nan(p, n), ckpt_every);
+      const ResLayout L = grad_layout(p, n, *q, ckpt_every);
       r = res_grad_forward(p, n, *q, nullptr, ckpt_every, mu, ab, work, L, st);
       if (r != KPM_OK) return r;
       if (d_ab) KPM_HIP(hipMemcpyAsync(d_ab, ab, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
