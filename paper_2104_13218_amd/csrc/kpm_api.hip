@@ -33,12 +33,23 @@ thread_local kpm_run_stats g_stats{};
 
 // ------------------------------------------------------------------ host math
 
+// Pascal's triangle up to n = 64: a plan asks for thousands of entries (the rank
+// table of the low words alone 10240; 18 sites, one column: 120 us a plan with
+// a product per entry).
+struct Pascal {
+  uint64_t c[65][65];
+  constexpr Pascal() : c{} {
+    for (int n = 0; n <= 64; ++n) {
+      c[n][0] = 1;
+      for (int k = 1; k <= n; ++k) c[n][k] = c[n - 1][k - 1] + (k < n ? c[n - 1][k] : 0);
+    }
+  }
+};
+constexpr Pascal kPascal;
+
 uint64_t binom64(int n, int k) {
   if (k < 0 || n < 0 || k > n) return 0;
-  if (k > n - k) k = n - k;
-  uint64_t r = 1;
-  for (int i = 1; i <= k; ++i) r = r * (uint64_t)(n - k + i) / (uint64_t)i;
-  return r;
+  return kPascal.c[n][k];
 }
 
 // Spin-s sectors: 2s of a problem (1 for spin 1/2) and the counts
@@ -598,6 +609,13 @@ bool split_spin(Planned& P, int cpl) {
   return records <= lists;
 }
 
+// Whether make_plan may take the slice kernel by itself.
+bool slice_by_default(const kpm_problem* p, int n, const RunShape& s) {
+  return s.allow_slice && !s.adjoint && s.tune.kernel < 0 && s.tune.col_block == 0 && s.col_block == 0 &&
+         s.precision != KPM_FP32R_STORE && !any_spin(p, n) && largest_sector(p, n) >= kSliceLeast &&
+         !std::getenv("KPM_BLOCK") && !std::getenv("KPM_ROW_KERNEL") && !std::getenv("KPM_BLOCK_L");
+}
+
 // The plan of a run.  Where nobody chose a kernel or a block width, spin-1/2
 // sectors from kSliceLeast on take the slice kernel, with 10 low bits or else 9
 // (a word row holds so many bonds), and the planner's heuristic where neither
@@ -610,9 +628,7 @@ bool split_spin(Planned& P, int cpl) {
 // against 15-88.
 int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_arr,
               const double* b_arr, Planned& P) {
-  if (s.allow_slice && !s.adjoint && s.tune.kernel < 0 && s.tune.col_block == 0 && s.col_block == 0 &&
-      s.precision != KPM_FP32R_STORE && largest_sector(p, n) >= kSliceLeast && !any_spin(p, n) &&
-      !std::getenv("KPM_BLOCK") && !std::getenv("KPM_ROW_KERNEL") && !std::getenv("KPM_BLOCK_L")) {
+  if (slice_by_default(p, n, s)) {
     for (int L : {10, 9}) {
       RunShape t = s;
       t.tune = slice_tune(p, n, s.precision, L);
@@ -2100,6 +2116,14 @@ int get_tune(const kpm_problem* p, int n, const kpm_params& q, const double* a, 
   return KPM_OK;
 }
 
+// Bytes of two vectors of the real columns, less than which no step plan takes.
+double two_vectors_bytes(const kpm_problem* p, int n, const RunShape& s) {
+  double bytes = 0.0;
+  for (int i = 0; i < n; ++i)
+    bytes += 2.0 * (s.precision == KPM_FP64 ? 8 : 4) * (double)prob_dim(p[i]) * (double)total_columns(p[i], s);
+  return bytes;
+}
+
 size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q);
 
 // Bytes of a resident moments call, 0 where the step kernels run it: a call
@@ -2112,7 +2136,7 @@ size_t resident_workspace(const kpm_problem* p, int n, const kpm_params& q) {
   const int64_t cols = res_columns(p, n, q);
   if (cols > (int64_t(1) << 24)) return 0;
   const size_t total = res_layout(p, n, cols, n_steps(q.M), lz, q.vec_kind == KPM_VEC_BASIS).total;
-  if (total > KPM_NOALLOC_MAX_BYTES) {
+  if (total > KPM_NOALLOC_MAX_BYTES && two_vectors_bytes(p, n, shape_of(q)) <= (double)KPM_NOALLOC_MAX_BYTES) {
     const size_t stepped = stepped_workspace(p, n, q);
     if (stepped && stepped <= KPM_NOALLOC_MAX_BYTES) return 0;
   }
@@ -2131,32 +2155,28 @@ size_t moments_lanczos_bytes(const kpm_problem* p, int n, const kpm_params& q) {
   return need.empty() ? 0 : lanczos_bytes(need.data(), (int)need.size(), lanczos_steps_of(q));
 }
 
-// shape_of with the default slice kernel left out where its blocks, all padded
-// to one width, would not fit the allocation-free entry point's array and the
-// other kernels' do (20-site sawtooth chain, 11 float32 columns: 84 and 62 MB).
-RunShape moments_shape(const kpm_problem* p, int n, const kpm_params& q, const Tune* t = nullptr) {
+// The plan of a moments call: make_plan's, with the default slice kernel left
+// out where its blocks, all padded to one width, would not fit the
+// allocation-free entry point's array and the other kernels' do (20-site
+// sawtooth chain, 11 float32 columns: 84 and 62 MB).
+int make_moments_plan(const kpm_problem* p, int n, const kpm_params& q, const Tune* t, Planned& P) {
   RunShape s = shape_of(q, t);
-  if (s.tune.kernel >= 0) return s;
-  double least = 0.0;   // two vectors of the real columns
-  for (int i = 0; i < n; ++i)
-    least += 2.0 * (q.precision == KPM_FP64 ? 8 : 4) * (double)prob_dim(p[i]) * (double)total_columns(p[i], s);
-  if (least > (double)KPM_NOALLOC_MAX_BYTES) return s;
+  const int r = make_plan(p, n, s, nullptr, nullptr, P);
+  if (r != KPM_OK || P.plan.block != 3 || !slice_by_default(p, n, s)) return r;
+  if (two_vectors_bytes(p, n, s) > (double)KPM_NOALLOC_MAX_BYTES) return r;   // no plan fits
   const size_t lz = moments_lanczos_bytes(p, n, q);
-  auto fits = [&]() {
-    Planned P;
-    return make_plan(p, n, s, nullptr, nullptr, P) != KPM_OK || (s.allow_slice && P.plan.block != 3) ||
-           moments_layout(P, n_steps(q.M), lz).total <= KPM_NOALLOC_MAX_BYTES;
-  };
-  if (fits()) return s;
+  auto fits = [&](const Planned& R) { return moments_layout(R, n_steps(q.M), lz).total <= KPM_NOALLOC_MAX_BYTES; };
+  if (fits(P)) return r;
   s.allow_slice = false;
-  if (!fits()) s.allow_slice = true;
-  return s;
+  Planned Q;
+  if (make_plan(p, n, s, nullptr, nullptr, Q) == KPM_OK && fits(Q)) P = std::move(Q);
+  return r;
 }
 
 size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q) {
   const size_t lz = moments_lanczos_bytes(p, n, q);
   Planned P;
-  if (make_plan(p, n, moments_shape(p, n, q), nullptr, nullptr, P) != KPM_OK) return 0;
+  if (make_moments_plan(p, n, q, nullptr, P) != KPM_OK) return 0;
   size_t total = moments_layout(P, n_steps(q.M), lz).total;
   if (q.autotune) {
     // Before the first trial runs the workspace must hold every candidate's
@@ -3111,7 +3131,7 @@ int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, doubl
   if (known) {
     try {
       planned = std::async(std::launch::async,
-                           [&]() { return make_plan(p, n, moments_shape(p, n, *q, &tn), nullptr, nullptr, P); });
+                           [&]() { return make_moments_plan(p, n, *q, &tn, P); });
     } catch (const std::system_error&) {
       known = false;   // no thread to be had: plan after the bounds
     }
@@ -3128,8 +3148,9 @@ int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, doubl
       r = get_tune(p, n, *q, a.data(), b.data(), work, need, st, tn);
       if (r != KPM_OK) return r;
     }
-    r = make_plan(p, n, moments_shape(p, n, *q, &tn), a.data(), b.data(), P);
+    r = make_moments_plan(p, n, *q, &tn, P);
     if (r != KPM_OK) return r;
+    apply_scale(p, n, a.data(), b.data(), P);
   }
   const MomLayout L = moments_layout(P, n_steps(q->M), 0);
   if (L.total > need) return KPM_EWORKSPACE;
@@ -3415,9 +3436,8 @@ int chebyshev_vectors(const kpm_problem* p, const kpm_params* q, int32_t n_vec, 
     } else if (work_bytes < need) {
       return KPM_EWORKSPACE;
     }
-    const RunShape shape = moments_shape(p, 1, q2);   // as the size query
     Planned P;
-    r = make_plan(p, 1, shape, nullptr, nullptr, P);
+    r = make_moments_plan(p, 1, q2, nullptr, P);   // as the size query
     if (r != KPM_OK) return r;
     const MomLayout L = moments_layout(P, n_steps(q2.M), moments_lanczos_bytes(p, 1, q2));
     if (L.total > need) return KPM_EWORKSPACE;
