@@ -584,7 +584,37 @@ Tune slice_tune(const kpm_problem* p, int n, int precision, int L) {
 int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double* a_arr,
                     const double* b_arr, Planned& P);
 
-// Whether the split spin kernel takes a spin-s plan, and the halves of its
+// Float32 columns per lane of the split spin kernel: eight where every unit has
+// whole lanes and the widest slot of one unit (`unit_bytes`) is far from fitting
+// an XCD's L2, else four.  Against four, 10-site rings of spin 5/2 and below: 48
+// MB and more 1.00-1.13 times as fast (32 columns of 4.4 million states 1.11);
+// below, fewer waves wait out the rows: 13 MB in 16 columns 0.75, 22 MB in 48
+// columns 0.8.
+int split_columns(const kpm_problem* p, int n, const RunShape& s, int rb, int cpl, int64_t unit_bytes) {
+  if (cpl != 4 || unit_bytes < (int64_t(48) << 20) || rb % 8 != 0) return cpl;
+  for (int i = 0; i < n; ++i)
+    if ((total_columns(p[i], s) % rb + 3) / 4 % 2 != 0) return cpl;
+  return 8;
+}
+
+// Whether the split spin kernel is the faster one.  Every lane of a row finds
+// its places and amplitudes again, the list kernel once for the whole row in
+// LDS, so the lanes of a row decide: up to eight, or 20 bonds (the list kernel
+// stages a bond at a time), or up to 16 where the lists come from memory.  2400
+// pairs (spin 1 to 7/2, 3 to 15 sites, both storages, 1 to 96 columns): 1.13
+// times the list kernel's speed over all of them, 36 under 0.97 (taken
+// everywhere: 1.12 and 366, the least 0.73, 116304 states in 48 float32 columns).
+bool split_pays(const Planned& P, int lanes) {
+  int least = INT32_MAX;
+  double lists = 0.0;
+  for (const ProbDev& d : P.probs) {
+    least = std::min(least, d.n_bonds);
+    lists += (8.0 + 8.0 * d.n_bonds) * (double)d.dim;
+  }
+  return lanes <= 8 || least >= 20 || (lanes <= 16 && lists >= (double)(1 << 26));
+}
+
+// Whether the split spin kernel can run a spin-s plan, and the halves of its
 // problems (B0, B1, B2): up to 16 sites (two 32-bit words of digits) with at
 // most 2^16 low and high codes each, a bond in every problem (the kernel
 // requests the next row's records beside the first bonds' rows), per-bond
@@ -592,7 +622,6 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
 // no larger than the lists that they replace (few rows of many sites: their
 // lists are the smaller).
 bool split_spin(Planned& P, int cpl) {
-  if (env_int("KPM_SPIN_SPLIT", 1) == 0) return false;
   int64_t lists = 0, records = 0;
   for (ProbDev& d : P.probs) {
     if (d.n_sites < 2 || d.n_sites > 16 || d.n_bonds < 1) return false;
@@ -765,7 +794,11 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
   if (row_ld) D.sub_rows = kThreads;
   D.n_states = spin ? n_states * (2 + D.lds_nb) : n_states;   // spin: digits + neighbour ranks
   D.spin_rows = spin ? n_states : 0;
-  if (spin && split_spin(P, cpl)) {
+  // KPM_SPIN_SPLIT: 0 the list kernel, 2 the split kernel wherever it can run
+  const int split_env = spin ? env_int("KPM_SPIN_SPLIT", 1) : 0;
+  const int spin_ld = (rb + cpl - 1) / cpl * cpl;
+  const int split_cpl = fp32 ? split_columns(p, n, s, rb, cpl, max_dim * spin_ld * elt) : cpl;
+  if (split_env && (split_env == 2 || split_pays(P, (spin_ld + split_cpl - 1) / split_cpl)) && split_spin(P, cpl)) {
     D.spin = 2;
     D.n_states = (n_states + 3) & ~int64_t(3);
     for (ProbDev& d : P.probs) {
@@ -988,11 +1021,7 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
   D.sub_per_tile = spt;
   // slice kernel: every XCD on the same column block at a time (measured 4 %
   // faster on the 24-site ring than contiguous tile ranges per XCD)
-  // spin plans: consecutive tiles on consecutive XCDs, so that all of them read
-  // the same stretch of a vector at a time (ten spin-5/2 sites, 32 float32
-  // columns: 7.1 ms a step, 8.1 with contiguous ranges, 8.8 with an eighth of
-  // every sector per XCD)
-  D.xcd_remap = env_int("KPM_XCD_REMAP", D.block == 3 ? -1 : (spin ? 0 : 1));
+  D.xcd_remap = env_int("KPM_XCD_REMAP", D.block == 3 ? -1 : 1);
   D.dense = env_int("KPM_DENSE_LISTS", 0);
   const int64_t tile_rows = (int64_t)D.sub_rows * spt;
 
@@ -1066,15 +1095,18 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
   }
   P.prob_unit0.push_back((int32_t)P.units.size());
   if (D.spin == 2) {
-    // eight float32 columns per lane where every unit has whole lanes
-    D.split_cpl = cpl;
-    bool eights = fp32 && cpl == 4;
-    for (const UnitDev& u : P.units) eights = eights && u.ld % 8 == 0;
-    if (eights) D.split_cpl = 8;
+    D.split_cpl = split_cpl;
     D.split_lds = 0;
     for (const ProbDev& d : P.probs)
       D.split_lds = std::max(D.split_lds, spin_split_lds_bytes(d.n_bonds, d.two_s, D.split_cpl));
   }
+  // Spin plans: consecutive tiles on consecutive XCDs where a slot is larger
+  // than the 256 MB that all XCDs share, so that all of them read the same
+  // stretch of a vector at a time (ten spin-5/2 sites, 32 float32 columns, 4 GB:
+  // 7.1 ms a step, 8.1 with contiguous ranges, 8.8 with an eighth of every
+  // sector per XCD); below, contiguous ranges, whose far rows stay in one L2
+  // (0.5-4 MB 1.0-1.1, 4-16 MB 1.1-1.25, 100-300 MB 1.0-1.08 times as fast).
+  if (spin) D.xcd_remap = env_int("KPM_XCD_REMAP", vec_elems * elt >= (int64_t(384) << 20) ? 0 : 1);
   // the row and block kernels also stream the 4-byte state word of every row;
   // the block-table kernel reads its per-block tables instead
   // the per-block table layout depends on the problem count (word tables)
