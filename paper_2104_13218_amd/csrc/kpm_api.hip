@@ -1607,8 +1607,9 @@ int stepped_lanczos(const kpm_problem* p, int n, int steps, double margin, uint6
 // Float64 calls whose sectors all fit one compute unit run their whole
 // recursion in one launch, one workgroup per real column (kpm_resident.hip):
 // the bounds and the moments of a 12-site ring took 50 x 5 + 128 launches.
-// The line lies where v_n still fits the 160 KB of LDS (19456 states) and a
-// row's bonds four 16-byte index entries (32).  A larger sector in the call
+// They can where v_n still fits the 160 KB of LDS (19456 states) and a row's
+// bonds four 16-byte index entries (32), and do where that is faster
+// (resident_moments_pay, resident_gradient_pays).  A larger sector in the call
 // keeps every sector on the step kernels: beside its launches the small
 // sectors' rows are nearly free.  Overrides of the step kernels keep them too.
 
@@ -1622,6 +1623,37 @@ bool resident_problems(const kpm_problem* p, int n) {
   for (int i = 0; i < n; ++i)
     if (two_s_of(p[i]) != 1 || prob_dim(p[i]) > (uint64_t)kResMaxDim || p[i].n_bonds > kResMaxBonds) return false;
   return true;
+}
+
+// Columns' worth of the call's largest sector: what its workgroups, one compute
+// unit each, run at once.
+double columns_worth(const kpm_problem* p, int n, const RunShape& s) {
+  double rows = 0.0;
+  for (int i = 0; i < n; ++i) rows += (double)prob_dim(p[i]) * (double)total_columns(p[i], s);
+  return rows / (double)std::max<int64_t>(1, largest_sector(p, n));
+}
+
+// Whether the moments of a call that can run resident are faster so.  A compute
+// unit takes a step of one column in the same time however many columns there
+// are, the step kernels take longer with each.  Measured, us per step, resident
+// and stepped with 1, 4 and 8 columns (9 to 32 bonds): 12870 states 8.1-14.0,
+// 8.7-14.4, 10.2-17.8, 11.4-19.9; 15504 states 9.9-17.0, 8.4-13.6, 10.2-16.3,
+// 11.2-18.1; 19448 states 11.8-20.4, 8.3-14.5, 10.0-17.7, 11.3-19.6; from nine
+// columns on stepped takes 1.5 times as long as resident at any size.  A stepped
+// call costs about 65 us more before its first step, which few steps do not win
+// back.
+bool resident_moments_pay(const kpm_problem* p, int n, const RunShape& s, int64_t K) {
+  const int64_t d = largest_sector(p, n);
+  return d <= 13312 || K < 24 || columns_worth(p, n, s) >= (d <= 16384 ? 3.0 : 6.0);
+}
+
+// The same for the gradient, whose workgroups have half the threads: us per
+// step, resident and stepped with 1, 8 and 16 columns: 8855 states 1.1-1.5 times
+// as fast with one; 12870 states 40-64, 35-54, 40-69, 73-141; 15504 states
+// 50-75, 35-49, 40-63, 79-132; 19448 states 60-91, 35-53, 40-68, 69-139.
+bool resident_gradient_pays(const kpm_problem* p, int n, const RunShape& s, int64_t K) {
+  const int64_t d = largest_sector(p, n);
+  return d <= 10240 || K < 12 || columns_worth(p, n, s) >= (d <= 13312 ? 9.0 : 16.0);
 }
 
 struct ResLayout {
@@ -2166,7 +2198,7 @@ size_t resident_workspace(const kpm_problem* p, int n, const kpm_params& q) {
   const int lz = count_nan(p, n);
   if (lz && lanczos_steps_of(q) > kResLanczos) return 0;
   const int64_t cols = res_columns(p, n, q);
-  if (cols > (int64_t(1) << 24)) return 0;
+  if (cols > (int64_t(1) << 24) || !resident_moments_pay(p, n, shape_of(q), n_steps(q.M))) return 0;
   const size_t total = res_layout(p, n, cols, n_steps(q.M), lz, q.vec_kind == KPM_VEC_BASIS).total;
   if (total > KPM_NOALLOC_MAX_BYTES && two_vectors_bytes(p, n, shape_of(q)) <= (double)KPM_NOALLOC_MAX_BYTES) {
     const size_t stepped = stepped_workspace(p, n, q);
@@ -2479,7 +2511,7 @@ FinalArgs res_final(const ResRun& R, const ResLayout& L, unsigned char* work, in
 bool resident_gradient(const kpm_problem* p, int n, const kpm_params& q) {
   if (q.precision != KPM_FP64 || q.col_block != 0 || std::getenv("KPM_ADJ_FWD") || !resident_problems(p, n)) return false;
   if (lanczos_steps_of(q) > kResLanczos) return false;
-  return res_columns(p, n, q) <= (int64_t(1) << 24);
+  return res_columns(p, n, q) <= (int64_t(1) << 24) && resident_gradient_pays(p, n, shape_of(q), n_steps(q.M));
 }
 
 ResLayout grad_layout(const kpm_problem* p, int n, const kpm_params& q, int ckpt_every) {

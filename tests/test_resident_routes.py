@@ -1,0 +1,95 @@
+"""Which calls the float64 moments and gradients of small sectors run resident:
+one column is one compute unit's work, so large sectors with few columns and many
+steps stay on the step kernels (read off the workspace's size, which those
+routes lay out differently; CPU), and both routes agree (GPU)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import workloads as W
+from paper_2104_13218_amd import kpm as K
+
+
+def _graph(n, n_bonds, seed=1):
+    rng = np.random.default_rng([seed, n, n_bonds])
+    bi = rng.integers(0, n, n_bonds)
+    return W.Cluster(n, bi, (bi + rng.integers(1, n, n_bonds)) % n, rng.uniform(0.5, 1.5, n_bonds))
+
+
+def _sizes(monkeypatch, secs, M, R, kind):
+    """The call's size, and the step kernels' one."""
+    ps = K.ProblemSet(secs, [(-60.0, 60.0)] * len(secs))
+    q, out = K.make_params(M, R, "rademacher", "fp64"), []
+    for env in (None, "0"):
+        monkeypatch.delenv("KPM_RESIDENT", raising=False)
+        if env is not None:
+            monkeypatch.setenv("KPM_RESIDENT", env)
+        out.append(K.moments_workspace_size(ps, q) if kind == "moments" else
+                   int(K.load().chebyshev_moments_vjp_workspace_size(ps.arr, len(ps), ctypes.byref(q), 64)))
+    return out
+
+
+@pytest.mark.parametrize("n,n_up,M,R,resident", [
+    (16, 8, 400, 1, True),                              # 12870 states
+    (20, 15, 400, 2, False), (20, 15, 400, 3, True),    # 15504
+    (17, 10, 400, 5, False), (17, 10, 400, 6, True),    # 19448
+    (17, 10, 47, 1, True), (17, 10, 48, 1, False),      # 23 and 24 steps
+])
+def test_moments_by_columns(monkeypatch, n, n_up, M, R, resident):
+    got, stepped = _sizes(monkeypatch, [W.Sector(_graph(n, 24), n_up, 0)], M, R, "moments")
+    assert (got != stepped) == resident
+
+
+@pytest.mark.parametrize("n,n_up,M,R,resident", [
+    (23, 19, 400, 1, True),                             # 8855
+    (16, 8, 400, 8, False), (16, 8, 400, 9, True),      # 12870
+    (17, 10, 400, 15, False), (17, 10, 400, 16, True),  # 19448
+    (17, 10, 23, 1, True), (17, 10, 24, 1, False),      # 11 and 12 steps
+])
+def test_gradient_by_columns(monkeypatch, n, n_up, M, R, resident):
+    got, stepped = _sizes(monkeypatch, [W.Sector(_graph(n, 24), n_up, 0)], M, R, "gradient")
+    assert (got != stepped) == resident
+
+
+def test_smaller_sectors_count_by_their_rows(monkeypatch):
+    """All sectors of 16 sites: 39203 rows, three times the largest's."""
+    secs = W.sectors(_graph(16, 24))
+    for R, resident in ((2, False), (3, True)):
+        got, stepped = _sizes(monkeypatch, secs, 400, R, "gradient")
+        assert (got != stepped) == resident
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("R", [2, 5, 6])
+def test_moments_on_either_side(kpm, R):
+    from oracle import hamiltonian, moments
+    sec = W.Sector(_graph(17, 24), 10, 0)
+    mu, ab = kpm.chebyshev_moments([sec], 60, R, "rademacher", "fp64", seed=3, bounds=[(-40.0, 40.0)])
+    assert (kpm.last_run_stats()["kernel"] == 6) == (R == 6)
+    ab = ab.cpu().numpy()[0]
+    want = moments.sector_moments(sec, ab[0], ab[1], 60, R, "rademacher", 3, H=hamiltonian.sector_hamiltonian(sec.cluster, 10))
+    assert np.abs(mu.cpu().numpy()[0] - want).max() <= 1e-10 * want[0]
+
+
+@pytest.mark.gpu
+def test_checkpointed_gradient_beside_resident_moments(kpm):
+    """16 sites, four columns: the moments run resident, the gradient on the
+    step kernels; forward, resumed and single call against the oracle."""
+    import torch
+    from oracle import adjoint
+    sec, M, R = W.Sector(_graph(16, 20), 8, 0), 30, 4
+    ps = kpm.ProblemSet([sec])
+    mu, ab, ws = kpm.moments_ckpt(None, M, R, seed=2, ckpt_every=4, problems=ps)
+    mu0, ab0 = kpm.chebyshev_moments([sec], M, R, seed=2)
+    assert kpm.last_run_stats()["kernel"] == 6
+    assert (ab - ab0).abs().max() <= 1e-13 * ab.abs().max()
+    assert (mu - mu0).abs().max() <= 1e-11 * mu0[0, 0]
+    lam = np.random.default_rng(1).normal(size=(1, M))
+    lam_d = torch.tensor(lam, device="cuda")
+    got = kpm.moments_vjp_resume(ps, M, R, ab, lam_d, ws, seed=2, ckpt_every=4).cpu().numpy()
+    once = kpm.moments_vjp([sec], M, R, ab, lam_d, seed=2, ckpt_every=4).cpu().numpy()
+    a, b = ab.cpu().numpy()[0]
+    want = adjoint.sector_moments_vjp(sec, a, b, M, R, "rademacher", 2, lam[0])
+    assert np.abs(got - want).max() <= 1e-9 * np.abs(want).max()
+    assert np.abs(once - want).max() <= 1e-9 * np.abs(want).max()
