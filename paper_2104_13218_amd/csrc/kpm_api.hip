@@ -8,12 +8,10 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
-#include <future>
 #include <map>
 #include <mutex>
 #include <new>
 #include <string>
-#include <system_error>
 #include <vector>
 
 #include "kpm.h"
@@ -135,28 +133,21 @@ void build_tables(int N, int k, Split sp, std::vector<uint32_t>& out) {
   uint32_t* T0 = out.data() + o0;
   uint32_t* T1 = T0 + (size_t(1) << sp.B0);
   uint32_t* T2 = T1 + (size_t(1) << sp.B1) * (sp.B0 + 1);
-  for (uint32_t x = 0; x < (1u << sp.B0); ++x) {
-    uint64_t r = 0;
-    int j = 0;
-    for (int q = 0; q < sp.B0; ++q)
-      if (x >> q & 1) r += binom64(q, ++j);
-    T0[x] = (uint32_t)r;
+  // a word's sum is that of the word without its highest bit (T0, T1), or
+  // without its lowest (T2, whose indices count from the top)
+  for (uint32_t x = 1; x < (1u << sp.B0); ++x) {
+    const int top = 31 - __builtin_clz(x);
+    T0[x] = T0[x ^ (1u << top)] + (uint32_t)binom64(top, __builtin_popcount(x));
   }
-  for (uint32_t x = 0; x < (1u << sp.B1); ++x)
-    for (int c = 0; c <= sp.B0; ++c) {
-      uint64_t r = 0;
-      int j = c;
-      for (int q = 0; q < sp.B1; ++q)
-        if (x >> q & 1) r += binom64(sp.B0 + q, ++j);
-      T1[(size_t)x * (sp.B0 + 1) + c] = (uint32_t)r;
-    }
-  for (uint32_t x = 0; x < (1u << sp.B2); ++x) {
-    int j = k - __builtin_popcount(x);
-    uint64_t r = 0;
-    if (j >= 0)
-      for (int q = 0; q < sp.B2; ++q)
-        if (x >> q & 1) r += binom64(sp.B0 + sp.B1 + q, ++j);
-    T2[x] = (uint32_t)r;
+  const int w = sp.B0 + 1;
+  for (uint32_t x = 1; x < (1u << sp.B1); ++x) {
+    const int top = 31 - __builtin_clz(x), m = __builtin_popcount(x);
+    for (int c = 0; c < w; ++c)
+      T1[(size_t)x * w + c] = T1[(size_t)(x ^ (1u << top)) * w + c] + (uint32_t)binom64(sp.B0 + top, c + m);
+  }
+  for (uint32_t x = 1; x < (1u << sp.B2); ++x) {
+    const int j = k - __builtin_popcount(x);   // below 0: no word of the sector
+    if (j >= 0) T2[x] = T2[x & (x - 1)] + (uint32_t)binom64(sp.B0 + sp.B1 + __builtin_ctz(x), j + 1);
   }
 }
 
@@ -973,12 +964,9 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
     }
     // colex rank of every low word among the words of its popcount
     P.lrank.assign(size_t(1) << maxL, 0);
-    for (uint32_t l = 0; l < (1u << maxL); ++l) {
-      uint64_t r = 0;
-      int j = 0;
-      for (int q = 0; q < maxL; ++q)
-        if ((l >> q) & 1u) r += binom64(q, ++j);
-      P.lrank[l] = (uint16_t)r;
+    for (uint32_t l = 1; l < (1u << maxL); ++l) {
+      const int top = 31 - __builtin_clz(l);
+      P.lrank[l] = (uint16_t)(P.lrank[l ^ (1u << top)] + binom64(top, __builtin_popcount(l)));
     }
     if (D.block >= 2) {
       // low words by popcount class, each class in colex order (its first
@@ -2188,7 +2176,7 @@ double two_vectors_bytes(const kpm_problem* p, int n, const RunShape& s) {
   return bytes;
 }
 
-size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q);
+size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q, Planned* run = nullptr);
 
 // Bytes of a resident moments call, 0 where the step kernels run it: a call
 // that the allocation-free entry point's array held on the step kernels stays
@@ -2207,9 +2195,9 @@ size_t resident_workspace(const kpm_problem* p, int n, const kpm_params& q) {
   return total;
 }
 
-size_t moments_workspace(const kpm_problem* p, int n, const kpm_params& q) {
+size_t moments_workspace(const kpm_problem* p, int n, const kpm_params& q, Planned* run = nullptr) {
   const size_t r = resident_workspace(p, n, q);
-  return r ? r : stepped_workspace(p, n, q);
+  return r ? r : stepped_workspace(p, n, q, run);
 }
 
 size_t moments_lanczos_bytes(const kpm_problem* p, int n, const kpm_params& q) {
@@ -2237,7 +2225,9 @@ int make_moments_plan(const kpm_problem* p, int n, const kpm_params& q, const Tu
   return r;
 }
 
-size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q) {
+// `run` (may be NULL): the plan that the call runs, at the unit map; left empty
+// where its shape is still to be measured.
+size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q, Planned* run) {
   const size_t lz = moments_lanczos_bytes(p, n, q);
   Planned P;
   if (make_moments_plan(p, n, q, nullptr, P) != KPM_OK) return 0;
@@ -2247,20 +2237,22 @@ size_t stepped_workspace(const kpm_problem* p, int n, const kpm_params& q) {
     // plan; once a shape is cached for these problems only its plan is run
     // (planning all ~30 candidates took over a second per call on the 64
     // random clusters).
-    std::vector<Tune> cands;
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) {
-      std::lock_guard<std::mutex> lock(g_tune_mu);
-      auto it = g_tune_cache.find(tune_key(dev, p, n, q));
-      if (it != g_tune_cache.end()) cands.push_back(it->second);
+    Tune tn{};
+    if (cached_tune(p, n, q, tn)) {
+      Planned Pc;
+      if (make_moments_plan(p, n, q, &tn, Pc) != KPM_OK) return 0;
+      total = std::max(total, moments_layout(Pc, n_steps(q.M), lz).total);
+      if (run) *run = std::move(Pc);
+      return total;
     }
-    if (cands.empty()) cands = tune_candidates(p, n, q);
-    for (const Tune& t : cands) {
+    for (const Tune& t : tune_candidates(p, n, q)) {
       Planned Pc;
       if (make_plan(p, n, shape_of(q, &t), nullptr, nullptr, Pc) == KPM_OK)
         total = std::max(total, moments_layout(Pc, n_steps(q.M), lz).total);
     }
+    return total;
   }
+  if (run) *run = std::move(P);
   return total;
 }
 
@@ -3177,45 +3169,27 @@ int run_resident(const kpm_problem* p, int n, const kpm_params& q, double* d_mu,
 }
 
 // chebyshev_moments on `need` bytes of device workspace at `work` (checked by
-// the caller); `direct` as in run_moments.  Arguments are validated already.
-int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, double* d_mu,
+// the caller); `direct` as in run_moments, P as moments_workspace left it.
+// Arguments are validated already.
+int moments_on_workspace(const kpm_problem* p, int n, const kpm_params* q, Planned& P, double* d_mu,
                          double* d_ab, unsigned char* work, size_t need, hipStream_t st,
                          bool direct) {
   const size_t avail = direct ? KPM_NOALLOC_MAX_BYTES : need;
   if (resident_workspace(p, n, *q)) return run_resident(p, n, *q, d_mu, d_ab, work, avail, st, direct);
-  // When the launch shape is known already (no tuning, or measured before),
-  // the host builds the plan at the unit map while the GPU runs the Lanczos
-  // bounds, then applies the map.  The Lanczos region starts the workspace:
-  // every layout of these problems holds at least its bytes, and it is done
-  // (its tridiagonal read back) before anything else is uploaded.
-  Tune tn{};
-  bool known = !q->autotune || cached_tune(p, n, *q, tn);
-  Planned P;
-  std::future<int> planned;
-  if (known) {
-    try {
-      planned = std::async(std::launch::async,
-                           [&]() { return make_moments_plan(p, n, *q, &tn, P); });
-    } catch (const std::system_error&) {
-      known = false;   // no thread to be had: plan after the bounds
-    }
-  }
+  // The bounds run first and may use the whole region: every layout of these
+  // problems holds at least their bytes, and they are done (the tridiagonals
+  // read back) before anything else is uploaded.
   std::vector<double> a, b;
   int r = resolve_scale(p, n, *q, Spare{work, avail, !direct}, st, a, b);
-  const int rp = known ? planned.get() : KPM_OK;
   if (r != KPM_OK) return r;
-  if (known) {
-    if (rp != KPM_OK) return rp;
-    apply_scale(p, n, a.data(), b.data(), P);
-  } else {
-    if (q->autotune) {
-      r = get_tune(p, n, *q, a.data(), b.data(), work, need, st, tn);
-      if (r != KPM_OK) return r;
-    }
+  if (P.units.empty()) {
+    Tune tn{};
+    r = get_tune(p, n, *q, a.data(), b.data(), work, need, st, tn);
+    if (r != KPM_OK) return r;
     r = make_moments_plan(p, n, *q, &tn, P);
     if (r != KPM_OK) return r;
-    apply_scale(p, n, a.data(), b.data(), P);
   }
+  apply_scale(p, n, a.data(), b.data(), P);
   const MomLayout L = moments_layout(P, n_steps(q->M), 0);
   if (L.total > need) return KPM_EWORKSPACE;
   std::vector<unsigned char> staging;
@@ -3257,7 +3231,7 @@ int scratch_address(int dev, unsigned char** out) {
 }
 
 // No C++ exception leaves the library (the C ABI has no way to carry one): a
-// failed host allocation, here or in the planning thread, reports KPM_ENOMEM,
+// failed host allocation reports KPM_ENOMEM,
 // any other exception KPM_EDEVICE; a size query reports 0.
 template <typename F>
 int guarded(F&& f) noexcept {
@@ -3426,7 +3400,8 @@ int chebyshev_moments(const kpm_problem* p, int32_t n, const kpm_params* q, doub
     if (!q || check_params_moments(*q) != KPM_OK || !d_mu) return KPM_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     StreamSync guard{st};
-    const size_t need = moments_workspace(p, n, *q);
+    Planned P;
+    const size_t need = moments_workspace(p, n, *q, &P);
     if (need == 0) return KPM_EINVAL;
     DevBuf own;
     unsigned char* work = static_cast<unsigned char*>(d_work);
@@ -3437,7 +3412,7 @@ int chebyshev_moments(const kpm_problem* p, int32_t n, const kpm_params* q, doub
     } else if (work_bytes < need) {
       return KPM_EWORKSPACE;
     }
-    return moments_on_workspace(p, n, q, d_mu, d_ab, work, need, st, false);
+    return moments_on_workspace(p, n, q, P, d_mu, d_ab, work, need, st, false);
   });
 }
 
@@ -3447,7 +3422,8 @@ int chebyshev_moments_noalloc(const kpm_problem* p, int32_t n, const kpm_params*
     int r = check_problems(p, n);
     if (r != KPM_OK) return r;
     if (!q || check_params_moments(*q) != KPM_OK || !d_mu || q->autotune != 0) return KPM_EINVAL;
-    const size_t need = moments_workspace(p, n, *q);
+    Planned P;
+    const size_t need = moments_workspace(p, n, *q, &P);
     if (need == 0) return KPM_EINVAL;
     if (need > KPM_NOALLOC_MAX_BYTES) return KPM_ETOOLARGE;
     int dev = 0;
@@ -3459,13 +3435,14 @@ int chebyshev_moments_noalloc(const kpm_problem* p, int32_t n, const kpm_params*
     unsigned char* work = nullptr;
     r = scratch_address(dev, &work);
     if (r != KPM_OK) return r;
-    return moments_on_workspace(p, n, q, d_mu, d_ab, work, need, st, true);
+    return moments_on_workspace(p, n, q, P, d_mu, d_ab, work, need, st, true);
   });
 }
 
 static kpm_params vectors_params(const kpm_params& q, int32_t n_vec) {
   kpm_params q2 = q;
   q2.M = std::max(2, 2 * n_vec);
+  q2.autotune = 0;
   return q2;
 }
 
@@ -3489,7 +3466,8 @@ int chebyshev_vectors(const kpm_problem* p, const kpm_params* q, int32_t n_vec, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     StreamSync guard{st};
     // every sector on the step kernels, whose vectors it returns
-    const size_t need = stepped_workspace(p, 1, q2);
+    Planned P;
+    const size_t need = stepped_workspace(p, 1, q2, &P);
     if (need == 0) return KPM_EINVAL;
     DevBuf own;
     unsigned char* work = static_cast<unsigned char*>(d_work);
@@ -3500,10 +3478,7 @@ int chebyshev_vectors(const kpm_problem* p, const kpm_params* q, int32_t n_vec, 
     } else if (work_bytes < need) {
       return KPM_EWORKSPACE;
     }
-    Planned P;
-    r = make_moments_plan(p, 1, q2, nullptr, P);   // as the size query
-    if (r != KPM_OK) return r;
-    const MomLayout L = moments_layout(P, n_steps(q2.M), moments_lanczos_bytes(p, 1, q2));
+    const MomLayout L = moments_layout(P, n_steps(q2.M), 0);
     if (L.total > need) return KPM_EWORKSPACE;
     // the bounds run first and may use the whole region
     std::vector<double> a, b;
