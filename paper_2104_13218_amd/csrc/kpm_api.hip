@@ -629,15 +629,49 @@ bool split_spin(Planned& P, int cpl) {
   return records <= lists;
 }
 
-// Whether make_plan may take the slice kernel by itself.
+int64_t most_columns(const kpm_problem* p, int n, const RunShape& s) {
+  int64_t c = 1;
+  for (int i = 0; i < n; ++i) c = std::max<int64_t>(c, total_columns(p[i], s));
+  return c;
+}
+
+// Whether the slice kernel is the faster one for the call's largest sector.  A
+// wave works on one block of low words at a time, so blocks of few members (high
+// S^z) leave its lanes idle, and rows under 16 bytes (one float64, one or two
+// float32 columns) are staged through registers.  Time on the other kernels over
+// that on the slice kernel, by members per block:
+//   4-10    0.2-0.9      (28-32 sites, S^z 8 to 12)
+//   12-25   0.6-1.3      under 1 in three of four calls
+//   30-57   0.9-1.8;     over 2^20 states with more than 8 columns 0.85-1.0 at 40
+//   80-190  1.0-2.5
+//   narrow rows: 80 members 0.84-0.96, 190 1.0, from 2^19 states on 1.2-3.3
+//   5-8 float32 columns: 30-80 members 0.86-1.06, from 2^18 states on 1.07-1.3
+bool slice_pays(const kpm_problem* p, int n, const RunShape& s) {
+  int at = 0;
+  for (int i = 1; i < n; ++i)
+    if (prob_dim(p[i]) > prob_dim(p[at])) at = i;
+  const int64_t d = (int64_t)prob_dim(p[at]), c = most_columns(p, n, s);
+  const int L = std::min(10, p[at].n_sites);
+  double blocks = 0.0;
+  for (int k = 0; k <= L; ++k) blocks += (double)binom64(p[at].n_sites - L, p[at].n_up - k);
+  const double members = (double)d / blocks;
+  const bool fp32 = s.precision == KPM_FP32_STORE;
+  if (members < (c > 8 && d >= (int64_t(1) << 20) ? 48.0 : 32.0)) return false;
+  if (c <= (fp32 ? 2 : 1)) return members >= 100.0 || d >= (int64_t(1) << 19);
+  if (fp32 && c > 4 && c <= 8) return members >= 100.0 || d >= (int64_t(1) << 18);
+  return true;
+}
+
+// Whether make_plan takes the slice kernel by itself.
 bool slice_by_default(const kpm_problem* p, int n, const RunShape& s) {
   return s.allow_slice && !s.adjoint && s.tune.kernel < 0 && s.tune.col_block == 0 && s.col_block == 0 &&
          s.precision != KPM_FP32R_STORE && !any_spin(p, n) && largest_sector(p, n) >= kSliceLeast &&
-         !std::getenv("KPM_BLOCK") && !std::getenv("KPM_ROW_KERNEL") && !std::getenv("KPM_BLOCK_L");
+         !std::getenv("KPM_BLOCK") && !std::getenv("KPM_ROW_KERNEL") && !std::getenv("KPM_BLOCK_L") && slice_pays(p, n, s);
 }
 
 // The plan of a run.  Where nobody chose a kernel or a block width, spin-1/2
-// sectors from kSliceLeast on take the slice kernel, with 10 low bits or else 9
+// sectors from kSliceLeast on take the slice kernel where it pays (slice_pays),
+// with 10 low bits or else 9
 // (a word row holds so many bonds), and the planner's heuristic where neither
 // fits.  Per step, slice kernel against what ran before: 30-site 4-regular
 // graph, 4 float32 columns, 9.2 against 23.3 ms (row kernel); 24-site ring, 20

@@ -1,0 +1,43 @@
+"""Which calls of 2^15 and more states take the slice kernel by default: not
+where its blocks have few members (high S^z) or its rows are narrow (the route is
+read off the workspace's size, CPU); the moments on both
+sides of the lines against the oracle (GPU)."""
+import numpy as np
+import pytest
+
+import workloads as W
+from paper_2104_13218_amd import kpm as K
+
+
+def _size(secs, R, precision, M=40):
+    ps = K.ProblemSet(secs, [(-20.0, 20.0)] * len(secs))
+    return K.moments_workspace_size(ps, K.make_params(M, R, "rademacher", precision))
+
+
+@pytest.mark.parametrize("n,n_up,R,precision,sliced", [
+    (18, 9, 1, "fp64", True), (18, 9, 2, "fp32", True), (18, 9, 8, "fp32", True),     # 190 members a block
+    (20, 13, 1, "fp64", False), (20, 13, 2, "fp64", True), (20, 13, 2, "fp32", False),  # 80
+    (20, 13, 8, "fp32", False), (22, 14, 8, "fp32", True), (24, 16, 1, "fp64", True),   # 84 and 57, larger sectors
+    (22, 16, 4, "fp64", False), (24, 17, 4, "fp64", True), (28, 23, 20, "fp64", False),  # 30, 35, 8
+    (26, 18, 8, "fp64", True), (26, 18, 12, "fp64", False),                             # 40 members, 1562275 states
+])
+def test_route(monkeypatch, n, n_up, R, precision, sliced):
+    secs = [W.Sector(W.ring(n), n_up, 0)]
+    got = _size(secs, R, precision)
+    monkeypatch.setenv("KPM_BLOCK", "-1")
+    assert (got != _size(secs, R, precision)) == sliced
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,n_up,R,precision,kernel", [
+    (20, 15, 3, "fp64", None), (20, 13, 1, "fp64", 1), (20, 13, 2, "fp64", 5), (22, 16, 9, "fp64", 3), (18, 9, 5, "fp64", 5),
+    (18, 9, 6, "fp32", 5), (20, 13, 5, "fp32", 1), (26, 21, 2, "fp64", 1)])
+def test_moments(kpm, n, n_up, R, precision, kernel):
+    from oracle import hamiltonian, moments
+    sec = W.Sector(W.j1j2_chain(n, 1.0, 0.5), n_up, 0)
+    mu, ab = kpm.chebyshev_moments([sec], 16, R, "gaussian", precision, seed=4, bounds=[(-20.0, 20.0)])
+    if kernel is not None:
+        assert kpm.last_run_stats()["kernel"] == kernel
+    a, b = ab.cpu().numpy()[0]
+    want = moments.sector_moments(sec, a, b, 16, R, "gaussian", 4, H=hamiltonian.sector_hamiltonian(sec.cluster, n_up))
+    assert np.abs(mu.cpu().numpy()[0] - want).max() <= (1e-10 if precision == "fp64" else 1e-5) * want[0]
