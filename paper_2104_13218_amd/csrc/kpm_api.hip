@@ -662,6 +662,17 @@ bool slice_pays(const kpm_problem* p, int n, const RunShape& s) {
   return true;
 }
 
+// Columns of the default slice plan's blocks, where they are not slice_tune's:
+// two float64 columns where blocks of four would hold two or three empty ones (5
+// columns of 24 sites, S^z = 0, 6.6 -> 5.4 ms for 30 steps; 28 sites, 9 columns,
+// 7.8 -> 6.6 GB), four float32 columns where one block does and waves are few (18
+// sites, 8 columns, 0.72 -> 0.61 ms).
+int slice_width(const kpm_problem* p, int n, const RunShape& s, int width) {
+  const int64_t c = most_columns(p, n, s);
+  if (s.precision == KPM_FP64) return c > 4 && (c % 4 == 1 || c % 4 == 2) ? 2 : width;
+  return c <= 8 && largest_sector(p, n) < (int64_t(1) << 18) ? 4 : width;
+}
+
 // Whether make_plan takes the slice kernel by itself.
 bool slice_by_default(const kpm_problem* p, int n, const RunShape& s) {
   return s.allow_slice && !s.adjoint && s.tune.kernel < 0 && s.tune.col_block == 0 && s.col_block == 0 &&
@@ -686,6 +697,7 @@ int make_plan(const kpm_problem* p, int n, const RunShape& s, const double* a_ar
     for (int L : {10, 9}) {
       RunShape t = s;
       t.tune = slice_tune(p, n, s.precision, L);
+      t.tune.col_block = slice_width(p, n, s, t.tune.col_block);
       t.slice_only = true;
       Planned Q;
       if (make_plan_shape(p, n, t, a_arr, b_arr, Q) == KPM_OK && Q.plan.block == 3) {

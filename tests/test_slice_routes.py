@@ -1,6 +1,6 @@
 """Which calls of 2^15 and more states take the slice kernel by default: not
 where its blocks have few members (high S^z) or its rows are narrow (the route is
-read off the workspace's size, CPU); the moments on both
+read off the workspace's size, CPU), and the plans' padding; the moments on both
 sides of the lines against the oracle (GPU)."""
 import numpy as np
 import pytest
@@ -26,6 +26,14 @@ def test_route(monkeypatch, n, n_up, R, precision, sliced):
     got = _size(secs, R, precision)
     monkeypatch.setenv("KPM_BLOCK", "-1")
     assert (got != _size(secs, R, precision)) == sliced
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 5, 6, 9, 10, 13, 17, 18, 20])
+def test_padding_of_float64_blocks(R):
+    """At most one empty column, as on the other kernels (two vectors of the real
+    columns are most of the workspace)."""
+    sec = W.Sector(W.ring(26), 13, 0)
+    assert _size([sec], R, "fp64") <= 16 * sec.dim * (R + 1) * 1.08
 
 
 @pytest.mark.gpu
