@@ -1670,28 +1670,32 @@ double columns_worth(const kpm_problem* p, int n, const RunShape& s) {
 // Whether the moments of a call that can run resident are faster so.  A compute
 // unit takes a step of one column in the same time however many columns there
 // are, the step kernels take longer with each.  Measured, us per step, resident
-// and stepped with 1, 4 and 8 columns (9 to 32 bonds): 12870 states 8.1-14.0,
-// 8.7-14.4, 10.2-17.8, 11.4-19.9; 15504 states 9.9-17.0, 8.4-13.6, 10.2-16.3,
-// 11.2-18.1; 19448 states 11.8-20.4, 8.3-14.5, 10.0-17.7, 11.3-19.6; from nine
-// columns on stepped takes 1.5 times as long as resident at any size.  A stepped
+// and stepped with 1, 4 and 8 columns (9 to 32 bonds): 12870 states 8.4-14.2,
+// 8.7-14.4, 10.2-17.8, 11.4-19.9; 15504 states 10.5-17.3, 8.4-13.6, 10.2-16.3,
+// 11.2-18.1; 19448 states 12.5-20.8, 8.3-14.5, 10.0-17.7, 11.3-19.6; from nine
+// columns on stepped takes 1.4 times as long as resident at any size.  A stepped
 // call costs about 65 us more before its first step, which few steps do not win
 // back.
 bool resident_moments_pay(const kpm_problem* p, int n, const RunShape& s, int64_t K) {
   const int64_t d = largest_sector(p, n);
-  return d <= 13312 || K < 24 || columns_worth(p, n, s) >= (d <= 16384 ? 3.0 : 6.0);
+  return d <= 13312 || K < 24 || columns_worth(p, n, s) >= (d <= 16384 ? 3.0 : 9.0);
 }
 
-// The same for the gradient, whose workgroups have half the threads: us per
-// step, resident and stepped with 1, 8 and 16 columns: 8855 states 1.1-1.5 times
-// as fast with one; 12870 states 40-64, 35-54, 40-69, 73-141; 15504 states
-// 50-75, 35-49, 40-63, 79-132; 19448 states 60-91, 35-53, 40-68, 69-139.
+// The same for the gradient, whose workgroups have half the threads: stepped
+// over resident, one column, 400 moments: 6435 states 1.3-1.45, 8855 states
+// 0.95-1.1, 12870 states 0.75-0.85; 16 columns: 12870 states 1.2-1.85, 19448
+// states 0.78-0.94 with 9 bonds and 1.03-1.35 with 16 and more.
 bool resident_gradient_pays(const kpm_problem* p, int n, const RunShape& s, int64_t K) {
   const int64_t d = largest_sector(p, n);
-  return d <= 10240 || K < 12 || columns_worth(p, n, s) >= (d <= 13312 ? 9.0 : 16.0);
+  if (d <= 8192 || K < 12) return true;
+  int least = INT32_MAX;
+  for (int i = 0; i < n; ++i) least = std::min(least, p[i].n_bonds);
+  if (d <= 13312) return columns_worth(p, n, s) >= (d <= 10240 ? 3.0 : 9.0);
+  return least >= 16 && columns_worth(p, n, s) >= 16.0;
 }
 
 struct ResLayout {
-  size_t probs, info, jobs, lz, binom, mask, coef, units, pu0, scale, flag, unstable, rows, up, idx, lohi, alpha, beta,
+  size_t probs, info, jobs, lz, binom, mask, coef, units, pu0, scale, flag, unstable, rows, up, idx, diag, off, lohi, alpha, beta,
       seg, ckpt, wsave, bonds, total;
   int n_ckpt;   // checkpoints of a gradient call, 0: the whole trajectory
 };
@@ -1708,11 +1712,12 @@ ResLayout res_layout(const kpm_problem* p, int n, int64_t cols, int64_t K, int n
     o = align_up(o + bytes);
     return r;
   };
-  size_t entries = 0, elems = 0;
+  size_t entries = 0, elems = 0, all_rows = 0;
   for (int i = 0; i < n; ++i) {
     const size_t d = (size_t)prob_dim(p[i]);
     elems += d * (basis ? d : (size_t)(cols / n));
     entries += d * (size_t)std::max(1, (p[i].n_bonds + 7) / 8);
+    all_rows += d;
   }
   L.probs = put((size_t)n * sizeof(ProbDev));
   L.info = put((size_t)n * sizeof(ResInfo));
@@ -1729,6 +1734,8 @@ ResLayout res_layout(const kpm_problem* p, int n, int64_t cols, int64_t K, int n
   L.rows = put(ckpt_every ? (size_t)cols * 8 : 0);
   L.up = o;
   L.idx = put(entries * 16);
+  L.diag = put(all_rows * 8);
+  L.off = put(all_rows * 4);
   L.lohi = put((size_t)n * 16);
   L.alpha = put((size_t)(cols ? K + 1 : 0) * cols * 8);
   L.beta = put((size_t)K * cols * 8);
@@ -1792,7 +1799,7 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
   RunShape s;
   s.vec_kind = q.vec_kind;
   s.R = q.R;
-  int64_t entries = 0, rows = 0, col = 0;
+  int64_t entries = 0, all_rows = 0, rows = 0, col = 0;
   int32_t bonds = 0;
   int64_t* row0 = reinterpret_cast<int64_t*>(h + L.rows);   // gradient: rows of the columns before each
   std::vector<int> order(n);
@@ -1811,7 +1818,9 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
     f.nch = std::max(1, (p[i].n_bonds + 7) / 8);
     f.coef_off = i * kResMaxBonds;
     f.idx_off = entries;
+    f.row_off = all_rows;
     entries += (int64_t)f.nch * d.dim;
+    all_rows += d.dim;
     for (int b = 0; b < p[i].n_bonds; ++b) {
       mask[f.coef_off + b] = (1u << p[i].bond_i[b]) | (1u << p[i].bond_j[b]);
       coef[f.coef_off + b] = 0.5 * p[i].J[b];
@@ -1849,6 +1858,8 @@ int res_start(const kpm_problem* p, int n, const kpm_params& q, int64_t cols, in
   a.mask = reinterpret_cast<uint32_t*>(work + L.mask);
   a.coef = reinterpret_cast<double*>(work + L.coef);
   a.idx = reinterpret_cast<uint4*>(work + L.idx);
+  a.diag = reinterpret_cast<double*>(work + L.diag);
+  a.off = reinterpret_cast<uint32_t*>(work + L.off);
   a.scale = reinterpret_cast<double*>(work + L.scale);
   a.lohi = reinterpret_cast<double*>(work + L.lohi);
   a.alpha = reinterpret_cast<double*>(work + L.alpha);

@@ -415,6 +415,7 @@ constexpr int kResAdjThreads = 512;   // threads of the gradient's workgroups
 constexpr int kResMom = 0, kResLz = 1, kResAdj = 2;   // launch_resident: moments, bounds, reverse sweep
 struct ResInfo {
   int64_t idx_off;     // first 16-byte index entry of the problem ([nch][dim])
+  int64_t row_off;     // rows of the problems before it
   int32_t nch;         // index entries (8 bonds each) per row
   int32_t coef_off;    // first of its nch * 8 masks and coefficients (zeros past the last bond)
 };
@@ -430,6 +431,8 @@ struct ResArgs {
   const uint32_t* mask;    // per bond (1 << i) | (1 << j)
   const double* coef;      // per bond J_b / 2
   uint4* idx;
+  double* diag;            // per row
+  uint32_t* off;           // per row: bit b, bond b does not act
   double* scale;           // [n_probs][2]: (a, b)
   double* lohi;            // [n_probs][2]: the window
   double* alpha;           // [K + 1][total_cols]

@@ -8,9 +8,16 @@
 // neighbour indices is read from memory per step, and those only where they
 // do not fit registers.
 //
-// H = sum_b J_b (P_b / 2 - 1/4), P_b the exchange of the bond's two sites, so
-// a row is sum_b (J_b / 2) v[P_b r] - (sum_b J_b / 4) v[r]: one index per bond
-// and no diagonal of its own.
+// A row of H v is its diagonal (a table, +-J_b / 4 summed once) times v[r] plus
+// sum_b (J_b / 2) v[P_b r] over the bonds that act, P_b the exchange of the
+// bond's two sites: one index per bond, that of an element held at zero where the
+// bond does not act.  (H = sum_b J_b (P_b / 2 - 1/4) over all bonds needs no
+// table, but adds the bonds that do not act at full weight and takes them off
+// again.  Error against 80-bit sums, as a multiple of the step kernels': 126 sets
+// of 64 to 1000 moments 2.06, sawtooth chains up to 7, and 0.88 with the table; 60
+// gradients 2.09 and 0.74, differences P_b v - v instead 2.08.  The table costs 2
+// to 7 % of a step of the moments, the choice of every dot's operand 10 to 20 % of
+// the gradient's.)
 //
 // What bounds it: the LDS gathers.  A row needs one 8-byte LDS read per bond,
 // 64 lanes to scattered addresses; with one row per thread the two barriers
@@ -36,8 +43,9 @@ namespace kpm {
 // ------------------------------------------------------------------ tables
 
 // Per row: the rank of the state each bond's exchange maps it to (16 bits; the
-// row itself where the two sites agree), eight bonds per 16-byte entry,
-// entries of one chunk consecutive in the row.
+// number of rows, where a zero is kept, if the two sites agree), eight bonds per
+// 16-byte entry, entries of one chunk consecutive in the row; its diagonal, and
+// a bit per bond that does not act.
 __global__ __launch_bounds__(kThreads) void res_tables_kernel(const ResArgs a) {
   __shared__ uint32_t bn[kBinomN * kBinomN];
   for (int e = threadIdx.x; e < kBinomN * kBinomN; e += kThreads) bn[e] = a.binom[e];
@@ -49,7 +57,10 @@ __global__ __launch_bounds__(kThreads) void res_tables_kernel(const ResArgs a) {
   if (r >= dim) return;
   const uint32_t s = unrank(r, P.n_sites, P.n_up, bn);
   const uint32_t* mask = a.mask + I.coef_off;
+  const double* cf = a.coef + I.coef_off;
   uint4* out = a.idx + I.idx_off;
+  double dg = 0.0;
+  uint32_t off = 0u;
   for (int ch = 0; ch < I.nch; ++ch) {
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -57,18 +68,23 @@ __global__ __launch_bounds__(kThreads) void res_tables_kernel(const ResArgs a) {
       const uint32_t m = mask[ch * 8 + t];    // 0 past the last bond
       const uint32_t v = s & m;
       const bool act = v != 0u && v != m;
-      uint32_t n = r;
-      if (act) {
+      dg = fma(act ? -0.5 : 0.5, cf[ch * 8 + t], dg);   // coefficient 0 past the last bond
+      uint32_t n = dim;
+      if (!act) {
+        off |= 1u << (ch * 8 + t);
+      } else {
         n = word_rank(s ^ m, bn);
         if (n >= dim) {
           atomicOr(a.flag, 2);
-          n = r;
+          n = dim;
         }
       }
       w[t >> 1] |= n << ((t & 1) * 16);
     }
     out[(size_t)ch * dim + r] = make_uint4(w[0], w[1], w[2], w[3]);
   }
+  a.diag[I.row_off + r] = dg;
+  a.off[I.row_off + r] = off;
 }
 
 // ------------------------------------------------------------------ helpers
@@ -120,13 +136,6 @@ __device__ __forceinline__ double at(const double* base, uint32_t r) {
   return *reinterpret_cast<const double*>(reinterpret_cast<const unsigned char*>(base) + r * 8u);
 }
 
-// sum_b J_b / 4 (coefficients past the last bond are 0)
-__device__ __forceinline__ double half_sum(cptr<double> cf) {
-  double s = 0.0;
-  for (int b = 0; b < kResMaxBonds; ++b) s += cf[b];
-  return 0.5 * s;
-}
-
 // sum_b (J_b / 2) x[exchanged row] of one row from its NCH index entries
 template <int NCH>
 __device__ __forceinline__ double gather_row(const uint4 (&q)[NCH], cptr<double> cf, const double* x) {
@@ -143,7 +152,7 @@ __device__ __forceinline__ double gather_row(const uint4 (&q)[NCH], cptr<double>
   return acc;
 }
 
-// The index entries of a workgroup's rows: kept in registers for the whole
+// The index entries and diagonals of a workgroup's rows: kept in registers for the whole
 // recursion where they fit (at most 8 entries per thread), else read from
 // L2 each step, the next row's while the current one is summed.  NCH is the
 // number of entries per row (rows with fewer read repeats with coefficient 0).
@@ -151,7 +160,11 @@ template <int RPT, int NCH>
 struct Rows {
   static constexpr bool kKeep = RPT * NCH <= 8;
   uint4 q[kKeep ? RPT : 1][NCH];
+  double d[kKeep ? RPT : 1];
+  uint32_t off[kKeep ? RPT : 1];
   const uint4* src;
+  const double* dsrc;
+  const uint32_t* osrc;
   uint32_t dim;
   int nch;
   __device__ __forceinline__ void load(int k, uint32_t r, uint4 (&o)[NCH]) const {
@@ -162,8 +175,8 @@ struct Rows {
   }
 };
 
-// One product: h[k] = sum_b (J_b/2) x[nb] for the thread's rows, passed to
-// use(k, row, on, h).
+// One product: h = sum_b (J_b/2) x[nb] and the diagonal d of each of the
+// thread's rows, passed to use(k, row, on, h, d).
 template <int RPT, int NCH, typename F>
 __device__ __forceinline__ void product(const Rows<RPT, NCH>& R, cptr<double> cf, const double* x, int tid, int T,
                                         F&& use) {
@@ -178,33 +191,39 @@ __device__ __forceinline__ void product(const Rows<RPT, NCH>& R, cptr<double> cf
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch)
           q[ch] = make_uint4(fresh(R.q[k][ch].x), fresh(R.q[k][ch].y), fresh(R.q[k][ch].z), fresh(R.q[k][ch].w));
-        use(k, min(r, R.dim - 1u), r < R.dim, gather_row<NCH>(q, cf, x));
+        use(k, min(r, R.dim - 1u), r < R.dim, gather_row<NCH>(q, cf, x), R.d[k]);
       }
     }
   } else {
     uint4 cur[NCH], nxt[NCH];
     tid = (int)fresh((uint32_t)tid);
     R.load(0, min((uint32_t)tid, R.dim - 1u), nxt);
+    double dn = at(R.dsrc, min((uint32_t)tid, R.dim - 1u));
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
       const uint32_t r0 = (uint32_t)(k * T);
       if (r0 < R.dim) {
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) cur[ch] = nxt[ch];
+        const double d = dn;
         const uint32_t r = r0 + (uint32_t)tid;
-        if (k + 1 < RPT && r0 + (uint32_t)T < R.dim) R.load(k + 1, min(r + (uint32_t)T, R.dim - 1u), nxt);
-        use(k, min(r, R.dim - 1u), r < R.dim, gather_row<NCH>(cur, cf, x));
+        if (k + 1 < RPT && r0 + (uint32_t)T < R.dim) {
+          R.load(k + 1, min(r + (uint32_t)T, R.dim - 1u), nxt);
+          dn = at(R.dsrc, min(r + (uint32_t)T, R.dim - 1u));
+        }
+        use(k, min(r, R.dim - 1u), r < R.dim, gather_row<NCH>(cur, cf, x), d);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
 }
 
-// The product with its bond dots: D[b] += v x[P_b r] over the thread's rows,
-// v = of(row, on).
+// The product with its bond dots: D[b] += v x[P_b r] over the thread's rows
+// (x[r] = xr where the bond does not act: its bit of `off`; testing the index
+// itself holds it, and 254 registers spilled at 38 rows of 32 bonds), v = of(row, on).
 template <int NCH>
-__device__ __forceinline__ double gather_dots(const uint4 (&q)[NCH], cptr<double> cf, const double* x, double v,
-                                              double (&D)[NCH * 8]) {
+__device__ __forceinline__ double gather_dots(const uint4 (&q)[NCH], cptr<double> cf, const double* x, double v, double xr,
+                                              uint32_t off, double (&D)[NCH * 8]) {
   double acc = 0.0;
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
@@ -215,7 +234,7 @@ __device__ __forceinline__ double gather_dots(const uint4 (&q)[NCH], cptr<double
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       acc = fma(cf[ch * 8 + t], g[t], acc);
-      D[ch * 8 + t] = fma(v, g[t], D[ch * 8 + t]);
+      D[ch * 8 + t] = fma(v, off >> (ch * 8 + t) & 1u ? xr : g[t], D[ch * 8 + t]);
     }
   }
   return acc;
@@ -224,8 +243,14 @@ template <int RPT, int NCH, typename V, typename F>
 __device__ __forceinline__ void product_dots(const Rows<RPT, NCH>& R, cptr<double> cf, const double* x, int tid, int T,
                                              double (&D)[NCH * 8], V&& of, F&& use) {
   uint4 nxt[NCH];
+  double dn = 0.0;
+  uint32_t offn = 0u;
   tid = (int)fresh((uint32_t)tid);
-  if constexpr (!Rows<RPT, NCH>::kKeep) R.load(0, min((uint32_t)tid, R.dim - 1u), nxt);
+  if constexpr (!Rows<RPT, NCH>::kKeep) {
+    R.load(0, min((uint32_t)tid, R.dim - 1u), nxt);
+    dn = at(R.dsrc, min((uint32_t)tid, R.dim - 1u));
+    offn = R.osrc[min((uint32_t)tid, R.dim - 1u)];
+  }
 #pragma unroll
   for (int k = 0; k < RPT; ++k) {
     const uint32_t r0 = (uint32_t)(k * T);
@@ -241,10 +266,20 @@ __device__ __forceinline__ void product_dots(const Rows<RPT, NCH>& R, cptr<doubl
         else
           cur[ch] = nxt[ch];
       }
+      double d = dn;
+      uint32_t off = offn;
+      if constexpr (Rows<RPT, NCH>::kKeep) {
+        d = R.d[k];
+        off = R.off[k];
+      }
       if constexpr (!Rows<RPT, NCH>::kKeep)
-        if (k + 1 < RPT && r0 + (uint32_t)T < R.dim) R.load(k + 1, min(r + (uint32_t)T, R.dim - 1u), nxt);
-      const double h = gather_dots<NCH>(cur, cf, x, v, D);
-      use(k, rc, r < R.dim, h, v);
+        if (k + 1 < RPT && r0 + (uint32_t)T < R.dim) {
+          R.load(k + 1, min(r + (uint32_t)T, R.dim - 1u), nxt);
+          dn = at(R.dsrc, min(r + (uint32_t)T, R.dim - 1u));
+          offn = R.osrc[min(r + (uint32_t)T, R.dim - 1u)];
+        }
+      const double h = gather_dots<NCH>(cur, cf, x, v, x[rc], off, D);
+      use(k, rc, r < R.dim, h, d, v);
       if constexpr (!Rows<RPT, NCH>::kKeep) __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -254,6 +289,8 @@ template <int RPT, int NCH>
 __device__ __forceinline__ void rows_init(Rows<RPT, NCH>& R, const ResArgs& a, const ResInfo& I, uint32_t dim, int tid,
                                           int T) {
   R.src = a.idx + I.idx_off;
+  R.dsrc = a.diag + I.row_off;
+  R.osrc = a.off + I.row_off;
   R.dim = dim;
   R.nch = I.nch;
   if constexpr (Rows<RPT, NCH>::kKeep) {
@@ -261,18 +298,21 @@ __device__ __forceinline__ void rows_init(Rows<RPT, NCH>& R, const ResArgs& a, c
     for (int k = 0; k < RPT; ++k) {
       const uint32_t r = min((uint32_t)(tid + k * T), dim - 1u);
       R.load(k, r, R.q[k]);
+      R.d[k] = at(R.dsrc, r);
+      R.off[k] = R.osrc[r];
     }
   }
 }
 
 // Start column of the job into x[0..dim), normalised as init_kernel does
 // (mode 1: <r|r> = dim over the vector's columns; mode 2: unit norm); each
-// thread writes and scales its own rows.  Returns the squared norm of the
+// thread writes and scales its own rows, and x[dim] = 0.  Returns the squared norm of the
 // unscaled column.
 __device__ __forceinline__ double start_rows(const ResArgs& a, const ProbDev& P, int kind, int col, int mode, int tid,
                                              int T, int lane, int wid, int nw, double* slot, double* x) {
   const int64_t dim = P.dim;
   double own = 0.0, pair = 0.0;
+  if (tid == 0) x[dim] = 0.0;
 #pragma unroll 1
   for (int64_t r = tid; r < dim; r += T) {
     const double v = start_value(kind, a.seed, P, col, r);
@@ -316,11 +356,10 @@ __global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
   const ResInfo I = a.info[J.prob];
   const uint32_t dim = (uint32_t)P.dim;
   double* red = sm;                       // [kResRing][16][2]
-  double* x = sm + kResRing * 32;         // [dim]
+  double* x = sm + kResRing * 32;         // [dim + 1]
   const double sa = a.scale[2 * J.prob], sb = a.scale[2 * J.prob + 1];
   const double inva = 1.0 / sa;
   const cptr<double> cf = cview(a.coef) + I.coef_off;
-  const double dg = -(half_sum(cf) + sb) * inva;
   Rows<RPT, NCH> R;
   rows_init(R, a, I, dim, tid, T);
   double y[RPT];
@@ -350,9 +389,9 @@ __global__ __launch_bounds__(1024) void res_moments_kernel(const ResArgs a) {
   }
   for (int n = 0; n < a.K; ++n) {
     double s2 = 0.0, s1 = 0.0;
-    product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
+    product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h, double d) {
       const double xr = x[r];
-      const double hx = fma(h, inva, dg * xr);
+      const double hx = fma(d - sb, xr, h) * inva;
       const double v = on ? (n == 0 ? hx : fma(2.0, hx, -y[k])) : 0.0;
       s2 = fma(v, v, s2);
       s1 = fma(v, xr, s1);
@@ -420,12 +459,11 @@ __global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResAr
   const ResInfo I = a.info[J.prob];
   const uint32_t dim = (uint32_t)P.dim;
   double* red = sm;                       // [2][16]
-  double* x = sm + 32;                    // [dim]
+  double* x = sm + 32;                    // [dim + 1]
   const double sa = a.scale[2 * J.prob], sb = a.scale[2 * J.prob + 1];
   if (tid == 0 && (!(sa > 0.0) || !isfinite(sa) || !isfinite(sb))) atomicOr(a.flag, 8);
   const double inva = 1.0 / sa;
   const cptr<double> cf = cview(a.coef) + I.coef_off;
-  const double dg = -(half_sum(cf) + sb) * inva;
   // dL/d<v_n, v_n> and dL/d<v_{n+1}, v_n> from dL/dmu through the estimator
   // and the doubling identities
   const double* lam = a.lambda + (int64_t)J.prob * a.M;
@@ -451,6 +489,7 @@ __global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResAr
     y[k] = 0.0;
     if (r < dim) x[r] = 0.0;
   }
+  if (tid == 0) x[dim] = 0.0;
   const int64_t ce = a.col_elems[J.ocol];                    // rows of the columns before this one
   const bool full = a.ckpt == nullptr;
   const int C = a.ckpt_every, K = a.K;
@@ -501,8 +540,8 @@ __global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResAr
       const int top = min(j1 + 1, K);                        // highest v index needed
       for (int t = 1; j0 + t + 1 <= top; ++t) {
         double* vt = seg + (int64_t)(t + 1) * dim;
-        product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
-          const double v = on ? fma(2.0, fma(h, inva, dg * x[r]), -y[k]) : 0.0;
+        product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h, double d) {
+          const double v = on ? fma(2.0, fma(d - sb, x[r], h) * inva, -y[k]) : 0.0;
           if (on) at(vt, r) = v;
           y[k] = v;
         });
@@ -526,18 +565,18 @@ __global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResAr
       const double* vm = v0 - dim;
       const double* vp = n + 1 <= K ? v0 + dim : v0;         // bbar_K = 0
       product_dots<RPT, NCH>(R, cf, x, tid, T, D, [&](uint32_t r, bool on) { return on ? 2.0 * at(v0, r) : 0.0; },
-                             [&](int k, uint32_t r, bool on, double h, double v2) {
+                             [&](int k, uint32_t r, bool on, double h, double d, double v2) {
                                const double wr = x[r];
                                s0 = fma(v2, wr, s0);
                                const double g = fma(gbm, at(vm, r), fma(gb, at(vp, r), ga * v2));
-                               y[k] = on ? g + fma(2.0, fma(h, inva, dg * wr), -y[k]) : 0.0;
+                               y[k] = on ? g + fma(2.0, fma(d - sb, wr, h) * inva, -y[k]) : 0.0;
                              });
       swap_in();
     }
   }
   // <w_1, h_b v_0> with weight 1 (slot 0 of segment 0 is v_0)
   product_dots<RPT, NCH>(R, cf, x, tid, T, D, [&](uint32_t r, bool on) { return on ? at(static_cast<const double*>(seg), r) : 0.0; },
-                         [&](int, uint32_t r, bool, double, double v) { s0 = fma(v, x[r], s0); });
+                         [&](int, uint32_t r, bool, double, double, double v) { s0 = fma(v, x[r], s0); });
   const double sq = group_sum(s0, red, lane, wid, nw);
 #pragma unroll
   for (int b = 0; b < NCH * 8; ++b) {
@@ -593,11 +632,10 @@ __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
   double* red = sm;                       // [2][16]
   double* al = sm + 32;                   // [kResLanczos]
   double* be = al + kResLanczos;          // [kResLanczos]: beta_{j+1}^2
-  double* x = be + kResLanczos;           // [dim]
+  double* x = be + kResLanczos;           // [dim + 1]
   const cptr<double> cf = cview(a.coef) + I.coef_off;
   Rows<RPT, NCH> R;
   rows_init(R, a, I, dim, tid, T);
-  const double hs = half_sum(cf);
   double y[RPT];
   start_rows(a, P, KPM_RES_GAUSSIAN, J.col, 2, tid, T, lane, wid, nw, red, x);
 #pragma unroll
@@ -608,9 +646,9 @@ __global__ __launch_bounds__(1024) void res_lanczos_kernel(const ResArgs a) {
   int L = steps;
   for (int j = 0; j < steps; ++j) {
     double s = 0.0;
-    product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h) {
+    product<RPT, NCH>(R, cf, x, tid, T, [&](int k, uint32_t r, bool on, double h, double d) {
       const double xr = x[r];
-      const double w = on ? fma(-hs, xr, h) - b * y[k] : 0.0;
+      const double w = on ? fma(d, xr, h) - b * y[k] : 0.0;
       s = fma(w, xr, s);
       y[k] = w;
     });
@@ -786,8 +824,9 @@ static hipError_t launch_res_n(const ResArgs& a, int what, int nch, int grid, in
 static hipError_t launch_res_any(const ResArgs& a, int what, int nch, int grid, uint32_t max_dim, hipStream_t st) {
   if (max_dim > (uint32_t)kResMaxDim || nch > kResMaxBonds / 8 || grid < 1) return hipErrorInvalidValue;
   // the bounds end on three rows of omega in the vector's place
-  const size_t lds = what == kResLz ? (std::max<size_t>(max_dim, 3 * (kResLanczos + 2)) + 32 + 2 * kResLanczos) * 8
-                                    : ((size_t)max_dim + (what == kResMom ? kResRing * 32 : 32)) * 8;
+  const size_t rows = (size_t)max_dim + 1;
+  const size_t lds = what == kResLz ? (std::max<size_t>(rows, 3 * (kResLanczos + 2)) + 32 + 2 * kResLanczos) * 8
+                                    : (rows + (what == kResMom ? kResRing * 32 : 32)) * 8;
   const uint32_t most = what == kResAdj ? (uint32_t)kResAdjThreads : 1024u;
   const int threads = (int)std::min<uint32_t>(most, std::max(64u, (max_dim + 63u) / 64u * 64u));
   const int rpt = (int)((max_dim + threads - 1) / threads);

@@ -33,7 +33,7 @@ def _sizes(monkeypatch, secs, M, R, kind):
 @pytest.mark.parametrize("n,n_up,M,R,resident", [
     (16, 8, 400, 1, True),                              # 12870 states
     (20, 15, 400, 2, False), (20, 15, 400, 3, True),    # 15504
-    (17, 10, 400, 5, False), (17, 10, 400, 6, True),    # 19448
+    (17, 10, 400, 8, False), (17, 10, 400, 9, True),    # 19448
     (17, 10, 47, 1, True), (17, 10, 48, 1, False),      # 23 and 24 steps
 ])
 def test_moments_by_columns(monkeypatch, n, n_up, M, R, resident):
@@ -42,7 +42,8 @@ def test_moments_by_columns(monkeypatch, n, n_up, M, R, resident):
 
 
 @pytest.mark.parametrize("n,n_up,M,R,resident", [
-    (23, 19, 400, 1, True),                             # 8855
+    (16, 10, 400, 1, True),                             # 8008
+    (23, 19, 400, 2, False), (23, 19, 400, 3, True),    # 8855
     (16, 8, 400, 8, False), (16, 8, 400, 9, True),      # 12870
     (17, 10, 400, 15, False), (17, 10, 400, 16, True),  # 19448
     (17, 10, 23, 1, True), (17, 10, 24, 1, False),      # 11 and 12 steps
@@ -50,6 +51,12 @@ def test_moments_by_columns(monkeypatch, n, n_up, M, R, resident):
 def test_gradient_by_columns(monkeypatch, n, n_up, M, R, resident):
     got, stepped = _sizes(monkeypatch, [W.Sector(_graph(n, 24), n_up, 0)], M, R, "gradient")
     assert (got != stepped) == resident
+
+
+def test_gradient_of_few_bonds_keeps_the_step_kernels(monkeypatch):
+    for n_bonds, resident in ((15, False), (16, True)):
+        got, stepped = _sizes(monkeypatch, [W.Sector(_graph(17, n_bonds), 10, 0)], 400, 16, "gradient")
+        assert (got != stepped) == resident
 
 
 def test_smaller_sectors_count_by_their_rows(monkeypatch):
@@ -61,12 +68,12 @@ def test_smaller_sectors_count_by_their_rows(monkeypatch):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("R", [2, 5, 6])
+@pytest.mark.parametrize("R", [2, 8, 9])
 def test_moments_on_either_side(kpm, R):
     from oracle import hamiltonian, moments
     sec = W.Sector(_graph(17, 24), 10, 0)
     mu, ab = kpm.chebyshev_moments([sec], 60, R, "rademacher", "fp64", seed=3, bounds=[(-40.0, 40.0)])
-    assert (kpm.last_run_stats()["kernel"] == 6) == (R == 6)
+    assert (kpm.last_run_stats()["kernel"] == 6) == (R == 9)
     ab = ab.cpu().numpy()[0]
     want = moments.sector_moments(sec, ab[0], ab[1], 60, R, "rademacher", 3, H=hamiltonian.sector_hamiltonian(sec.cluster, 10))
     assert np.abs(mu.cpu().numpy()[0] - want).max() <= 1e-10 * want[0]
