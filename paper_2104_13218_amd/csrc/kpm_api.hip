@@ -2964,6 +2964,13 @@ int thermo_meta(const kpm_problem* p, int n, std::vector<ThermoProb>& tp,
   return KPM_OK;
 }
 
+// Sectors of the largest cluster of thermo_meta's list.
+int most_sectors(const std::vector<int32_t>& start) {
+  int m = 0;
+  for (size_t c = 0; c + 1 < start.size(); ++c) m = std::max(m, start[c + 1] - start[c]);
+  return m;
+}
+
 struct ThermoDev {
   DevBuf buf;
   double* g = nullptr;
@@ -2987,7 +2994,7 @@ int thermo_forward(const double* d_mu, const double* d_ab, const kpm_problem* p,
   int r = thermo_meta(p, n, tp, start, list, n_clusters);
   if (r != KPM_OK) return r;
   const int Nt = n_nodes ? n_nodes : M;
-  const int chunk = thermo_chunk(n, n_T);
+  const int sectors = most_sectors(start), chunk = thermo_chunk(n, n_T, Nt, sectors, d_h != nullptr);
   size_t o = 0;
   auto put = [&](size_t bytes) {
     const size_t rr = o;
@@ -3036,6 +3043,8 @@ int thermo_forward(const double* d_mu, const double* d_ab, const kpm_problem* p,
   ta.n_probs = n;
   ta.h = d_h;
   ta.mag = d_mag;
+  ta.chunk = chunk;
+  ta.max_sectors = sectors;
   KPM_HIP(launch_thermo(ta, st));
   // the host staging vectors die with the caller's frame: finish the copies now
   KPM_HIP(hipStreamSynchronize(st));
@@ -4061,7 +4070,9 @@ int kpm_thermo_hybrid(const double* d_mu, const double* d_ab, const kpm_problem*
     hipStream_t st = static_cast<hipStream_t>(stream);
     StreamSync guard{st};
     const int Nt = n_nodes ? n_nodes : M;
-    const int chunk = thermo_chunk(n, n_pts);
+    const int sectors = most_sectors(start),
+              chunk = thermo_chunk(n, n_pts, std::max(Nt, *std::max_element(cnt.begin(), cnt.end())),
+                                   sectors, d_h != nullptr);
     size_t o = 0;
     auto put = [&](size_t bytes) {
       const size_t rr = o;
@@ -4109,6 +4120,8 @@ int kpm_thermo_hybrid(const double* d_mu, const double* d_ab, const kpm_problem*
     ta.ed_count = reinterpret_cast<const int32_t*>(w + ocnt);
     ta.evals = d_evals;
     ta.evals_ld = evals_ld;
+    ta.chunk = chunk;
+    ta.max_sectors = sectors;
     KPM_HIP(launch_thermo(ta, st));
     KPM_HIP(hipStreamSynchronize(st));
     return KPM_OK;

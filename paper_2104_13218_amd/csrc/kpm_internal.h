@@ -325,6 +325,7 @@ struct ThermoArgs {
   uint8_t* znonpos;
   double* stats;             // [n_clusters][n_T][6]: S0, Ebar, Var, <m^2>, Eref, beta
   int32_t n_nodes, n_T, n_clusters, n_probs;
+  int32_t chunk, max_sectors;   // points per chunk (0: one pass), sectors of the largest cluster
   int32_t t0, t1;            // the chunk's points
   SectorSums* sums;          // [n_probs][t1 - t0]
   int32_t* same;             // [t1 - t0] (with h only)
@@ -591,7 +592,7 @@ hipError_t launch_lz_fix(const DevicePlan& p, double* vec, int y_hi, const doubl
 hipError_t launch_kernel_coef(int M, int kernel, double* g, hipStream_t st);
 hipError_t launch_gamma(int n_probs, int M, int n_nodes, const double* g, const double* mu,
                         const double* ab, double* gamma, double* enode, hipStream_t st);
-int thermo_chunk(int n_probs, int n_T);
+int thermo_chunk(int n_probs, int n_T, int n_nodes, int max_sectors, bool field);
 hipError_t launch_thermo(ThermoArgs a, hipStream_t st);
 hipError_t launch_thermo_vjp(const ThermoVjpArgs& a, hipStream_t st);
 

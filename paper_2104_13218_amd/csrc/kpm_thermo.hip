@@ -60,6 +60,15 @@ __device__ __forceinline__ double node_x(int64_t k, int64_t Nt) {
 // a cosine costs several times what one problem's term does, and four
 // problems' sums still fit the registers of a fully occupied compute unit.
 constexpr int kCosShare = 4;
+constexpr int kOnePassSectors = 256;   // their sums in LDS, 10 kB
+
+
+// Up to here each wave takes one problem: three workgroups a compute unit are in
+// flight anyway, and the shared cosine would cost a chain of four problems' sums.
+// T-only calls, four problems a wave against one: 75 us to 70 at 315 workgroups
+// (5 problems, 500 moments), 69 to 68 at 572, 93 to 92 at 750; 85 to 87 at 800,
+// 115 to 125 at 1250 and 128 to 179 at 3250.
+constexpr int kGammaGroups = 768;
 
 }  // namespace
 
@@ -81,13 +90,13 @@ hipError_t launch_kernel_coef(int M, int kernel, double* g, hipStream_t st) {
 }
 
 // gamma[p][k-1] and E[p][k-1], one wave per pair of nodes k, Nt + 1 - k and
-// kCosShare problems: cos(n theta) at the second node is (-1)^n that at the
+// kShare problems: cos(n theta) at the second node is (-1)^n that at the
 // first, and n has the parity of its lane, so the second node costs a sign in
 // the last sum.  k runs over the lower half of the spectrum, whose small
-// weights keep the cosines of their own arguments.  Bound by float64 arithmetic, most of it the cosines': 13
-// sectors with 2000 moments took 200 us with a wave per node and problem.
-// Without damping the weights of the
-// lowest nodes are small differences of large terms, so the sum is compensated
+// weights keep the cosines of their own arguments.  Bound by float64 arithmetic,
+// most of it the cosines': 13 sectors with 2000 moments took 200 us with a wave
+// per node and problem.  Without damping the weights of the lowest nodes are
+// small differences of large terms, so the sum is compensated
 // (the Dot2 scheme of Ogita, Rump and Oishi, "Accurate sum and dot product",
 // SIAM J. Sci. Comput. 26 (2005)): each product's rounding error from an fma,
 // each addition's from TwoSum, carried in a second sum; lane l takes the terms
@@ -102,26 +111,27 @@ __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e
   e = (a - (s - bb)) + (b - bb);
 }
 
+template <int kShare>
 __global__ __launch_bounds__(kThreads) void gamma_kernel(int n_probs, int M, int Nt,
                                                          const double* g, const double* mu,
                                                          const double* ab, double* gamma,
                                                          double* enode) {
 #pragma clang fp contract(off)
-  const int p0 = blockIdx.y * kCosShare;
+  const int p0 = blockIdx.y * kShare;
   const int lane = threadIdx.x & 63;
   const int k = Nt - (blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
   if (2 * k < Nt + 1) return;   // k is the same across the wave
-  const int np = min(kCosShare, n_probs - p0);
+  const int np = min(kShare, n_probs - p0);
   const double* mp = mu + (int64_t)p0 * M;
   const int64_t period = 4 * (int64_t)Nt;
   const int64_t stride = (64 * (2 * (int64_t)k - 1)) % period;
   int64_t m = ((int64_t)lane * (2 * (int64_t)k - 1)) % period;
-  double sum[kCosShare] = {}, err[kCosShare] = {};
+  double sum[kShare] = {}, err[kShare] = {};
   for (int n = lane; n < M; n += 64) {
     const double gn = g[n];
     const double cv = reduced_cos(m, Nt);
 #pragma unroll
-    for (int j = 0; j < kCosShare; ++j) {
+    for (int j = 0; j < kShare; ++j) {
       if (j >= np) break;
       const double cn = gn * mp[(int64_t)j * M + n] * (n == 0 ? 1.0 : 2.0);
       const double x = cn * cv;
@@ -134,7 +144,7 @@ __global__ __launch_bounds__(kThreads) void gamma_kernel(int n_probs, int M, int
     if (m >= period) m -= period;
   }
 #pragma unroll
-  for (int j = 0; j < kCosShare; ++j) {
+  for (int j = 0; j < kShare; ++j) {
     if (j >= np) break;
     double v = sum[j], r = err[j];
     double vo = lane & 1 ? -v : v, ro = lane & 1 ? -r : r;
@@ -165,10 +175,13 @@ __global__ __launch_bounds__(kThreads) void gamma_kernel(int n_probs, int M, int
 hipError_t launch_gamma(int n_probs, int M, int n_nodes, const double* g, const double* mu,
                         const double* ab, double* gamma, double* enode, hipStream_t st) {
   constexpr int kPairsPerGroup = kThreads / 64;
-  dim3 grid(((n_nodes + 1) / 2 + kPairsPerGroup - 1) / kPairsPerGroup,
-            (n_probs + kCosShare - 1) / kCosShare);
-  hipLaunchKernelGGL(gamma_kernel, grid, dim3(kThreads), 0, st, n_probs, M, n_nodes, g, mu, ab,
-                     gamma, enode);
+  const unsigned groups = ((n_nodes + 1) / 2 + kPairsPerGroup - 1) / kPairsPerGroup;
+  if ((int64_t)groups * n_probs <= kGammaGroups)
+    hipLaunchKernelGGL(gamma_kernel<1>, dim3(groups, n_probs), dim3(kThreads), 0, st, n_probs, M,
+                       n_nodes, g, mu, ab, gamma, enode);
+  else
+    hipLaunchKernelGGL(gamma_kernel<kCosShare>, dim3(groups, (n_probs + kCosShare - 1) / kCosShare),
+                       dim3(kThreads), 0, st, n_probs, M, n_nodes, g, mu, ab, gamma, enode);
   return hipGetLastError();
 }
 
@@ -191,19 +204,12 @@ __global__ __launch_bounds__(kThreads) void same_T_kernel(const ThermoArgs a) {
   if (lane == 0) a.same[t - a.t0] = first;
 }
 
-// Sums over the nodes (or exact levels) of one sector at one temperature, in a
-// wave: four temperatures of a sector share the cached node energies and
-// weights.  One exponential a node and pass; every shift of the whole sector
-// (its lowest energy against the cluster's, the field's h S^z and its mirror)
-// is one factor in points_kernel.  The second pass takes the energies about
-// the sector's mean, as the variance needs them.  200 temperatures of 13
-// sectors with 2000 nodes, each at 40 fields: the sums of all 8000 points took
-// 3.35 ms with the nodes' cosine and four exponentials in each point.
-__global__ __launch_bounds__(kThreads) void sector_sums_kernel(const ThermoArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int t = a.t0 + blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  const int p = blockIdx.y;
-  if (t >= a.t1 || (a.h && a.same[t - a.t0] != t)) return;   // the same across the wave
+// Sums over the nodes (or exact levels) of sector p at point t's temperature, in
+// a wave.  One exponential a node and pass; every shift of the whole sector (its
+// lowest energy against the cluster's, the field's h S^z and its mirror) is one
+// factor in point_sums.  The second pass takes the energies about the sector's
+// mean, as the variance needs them.
+__device__ __forceinline__ SectorSums sector_sums(const ThermoArgs& a, int p, int t, int lane) {
   const int ned = a.ed_count ? a.ed_count[p] : 0;
   const int items = ned > 0 ? ned : a.n_nodes;
   const double* en = ned > 0 ? a.evals + (int64_t)p * a.evals_ld : a.enode + (int64_t)p * a.n_nodes;
@@ -242,37 +248,26 @@ __global__ __launch_bounds__(kThreads) void sector_sums_kernel(const ThermoArgs 
   }
   r1 = lanes_sum<64>(r1);
   v = lanes_sum<64>(v);
-  if (lane == 0) {
-    SectorSums* o = a.sums + (int64_t)p * (a.t1 - a.t0) + (t - a.t0);
-    o->lo = lo;
-    o->s0 = s0;
-    o->c = c;
-    o->s1 = r1;
-    o->v = v;
-  }
+  return SectorSums{lo, s0, c, r1, v};
 }
 
-// One point (T, h) of a cluster per 16 lanes, its sectors over the lanes.  The
-// sector S^z = m keeps its zero-field DOS and every energy moves by h m (h = g
-// mu_B B); a sector with S^z > 0 stands for m = +S^z and its mirror m = -S^z.
-// With d = E - c and D = c + h m - <E> the centred sum of squares is
-// sum w (d + D)^2 = v + D (2 s1 + D s0) in each sector, with no cancellation.
-__global__ __launch_bounds__(kThreads) void points_kernel(const ThermoArgs a) {
-  const int sub = threadIdx.x & 15;
-  const int t = a.t0 + blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
-  const int cl = blockIdx.y;
-  if (t >= a.t1) return;   // the same across the 16 lanes
+// One point (T, h) of a cluster in 16 lanes, its sectors over the lanes, their
+// sums from of(list position, sector).  The sector S^z = m keeps its zero-field
+// DOS and every energy moves by h m (h = g mu_B B); a sector with S^z > 0 stands
+// for m = +S^z and its mirror m = -S^z.  With d = E - c and D = c + h m - <E> the
+// centred sum of squares is sum w (d + D)^2 = v + D (2 s1 + D s0) in each sector,
+// with no cancellation.
+template <typename F>
+__device__ __forceinline__ void point_sums(const ThermoArgs& a, int t, int cl, int sub, F&& of) {
   const int q0 = a.cl_start[cl], q1 = a.cl_start[cl + 1];
   const double beta = 1.0 / a.T[t];
   const double hf = a.h ? a.h[t] : 0.0;
-  const SectorSums* sums = a.sums + ((a.h ? a.same[t - a.t0] : t) - a.t0);
-  const int64_t ld = a.t1 - a.t0;
 
   double emin = INFINITY;
   for (int q = q0 + sub; q < q1; q += 16) {
     const int p = a.cl_list[q];
     const ThermoProb P = a.tp[p];
-    const double lo = sums[p * ld].lo;
+    const double lo = of(q, p).lo;
     emin = fmin(emin, fma(hf, P.sz, lo));
     if (P.weight > 1.0) emin = fmin(emin, fma(-hf, P.sz, lo));
   }
@@ -282,7 +277,7 @@ __global__ __launch_bounds__(kThreads) void points_kernel(const ThermoArgs a) {
   for (int q = q0 + sub; q < q1; q += 16) {
     const int p = a.cl_list[q];
     const ThermoProb P = a.tp[p];
-    const SectorSums s = sums[p * ld];
+    const SectorSums s = of(q, p);
     const double hm = hf * P.sz;
     const double fu = exp(-beta * ((s.lo + hm) - eref));
     const double fd = P.weight > 1.0 ? exp(-beta * ((s.lo - hm) - eref)) : 0.0;
@@ -299,7 +294,7 @@ __global__ __launch_bounds__(kThreads) void points_kernel(const ThermoArgs a) {
   for (int q = q0 + sub; q < q1; q += 16) {
     const int p = a.cl_list[q];
     const ThermoProb P = a.tp[p];
-    const SectorSums s = sums[p * ld];
+    const SectorSums s = of(q, p);
     const int nm = P.weight > 1.0 ? 2 : 1;
     for (int j = 0; j < nm; ++j) {
       const double m = j == 0 ? P.sz : -P.sz;
@@ -333,17 +328,67 @@ __global__ __launch_bounds__(kThreads) void points_kernel(const ThermoArgs a) {
   }
 }
 
+// Sector by temperature, in a wave: four temperatures of a sector share the
+// cached node energies and weights.  200 temperatures of 13 sectors with 2000
+// nodes, each at 40 fields: the sums of all 8000 points took 3.35 ms with the
+// nodes' cosine and four exponentials in each point.
+__global__ __launch_bounds__(kThreads) void sector_sums_kernel(const ThermoArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int t = a.t0 + blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const int p = blockIdx.y;
+  if (t >= a.t1 || (a.h && a.same[t - a.t0] != t)) return;   // the same across the wave
+  const SectorSums s = sector_sums(a, p, t, lane);
+  if (lane == 0) a.sums[(int64_t)p * (a.t1 - a.t0) + (t - a.t0)] = s;
+}
+
+__global__ __launch_bounds__(kThreads) void points_kernel(const ThermoArgs a) {
+  const int t = a.t0 + blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
+  if (t >= a.t1) return;   // the same across the 16 lanes
+  const SectorSums* sums = a.sums + ((a.h ? a.same[t - a.t0] : t) - a.t0);
+  const int64_t ld = a.t1 - a.t0;
+  point_sums(a, t, blockIdx.y, threadIdx.x & 15, [&](int, int p) { return sums[p * ld]; });
+}
+
+// A point of a cluster per workgroup, its sectors' sums over the waves and then
+// in LDS: the same sums in the same order, in one launch and without the look for
+// equal temperatures.  Small calls are bound by launches: 16 temperatures by 8
+// fields of 8 sites with 64 nodes 72 us, with the three kernels 100.
+__global__ __launch_bounds__(1024) void one_pass_kernel(const ThermoArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  SectorSums* sums = reinterpret_cast<SectorSums*>(smem);
+  const int t = blockIdx.x, cl = blockIdx.y, lane = threadIdx.x & 63;
+  const int q0 = a.cl_start[cl], q1 = a.cl_start[cl + 1];
+  for (int q = q0 + (threadIdx.x >> 6); q < q1; q += blockDim.x >> 6) {
+    const SectorSums s = sector_sums(a, a.cl_list[q], t, lane);
+    if (lane == 0) sums[q - q0] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < 16) point_sums(a, t, cl, threadIdx.x, [&](int q, int) { return sums[q - q0]; });
+}
+
 // Points per chunk: the sums of a chunk stay under 64 MB wherever 64 points do
-// (a point's temperature is looked for within its chunk only).
-int thermo_chunk(int n_probs, int n_T) {
+// (a point's temperature is looked for within its chunk only).  0: the one-pass
+// kernel, which evaluates the nodes at every point.  With fields, up to 2e6 of
+// them: 0.7e6 91 us to 85, 1.2e6 118 to 100, 2.0e6 152 to 128 and 94 to 93; above,
+// 89 to 96 at 2.1e6 and 92 to 123 at 2.6e6, where temperatures repeat 8 and 40
+// times.  Without, where it saves one launch of 2 us and nothing repeats, up to
+// 250,000: 62 to 59 at 6e4 and 1e5, 71 to 68 at 2.3e5; 126 to 132 at 4.2e5.
+int thermo_chunk(int n_probs, int n_T, int n_nodes, int max_sectors, bool field) {
+  const double nodes = (double)n_probs * n_T * n_nodes;
+  if (max_sectors <= kOnePassSectors && nodes <= (field ? 2000000 : 250000)) return 0;
   const int64_t fit = (int64_t)(64 << 20) / ((int64_t)n_probs * sizeof(SectorSums));
   return (int)std::min<int64_t>(n_T, std::min<int64_t>(std::max<int64_t>(fit, 64), 16384));
 }
 
 hipError_t launch_thermo(ThermoArgs a, hipStream_t st) {
-  const int chunk = thermo_chunk(a.n_probs, a.n_T);
+  if (a.chunk == 0) {
+    const int waves = std::max(1, std::min(a.max_sectors, 16));
+    hipLaunchKernelGGL(one_pass_kernel, dim3(a.n_T, a.n_clusters), dim3(64 * waves),
+                       a.max_sectors * sizeof(SectorSums), st, a);
+    return hipGetLastError();
+  }
   for (a.t0 = 0; a.t0 < a.n_T; a.t0 = a.t1) {
-    a.t1 = a.t0 + std::min(chunk, a.n_T - a.t0);
+    a.t1 = a.t0 + std::min(a.chunk, a.n_T - a.t0);
     const int n = a.t1 - a.t0, waves = kThreads / 64, points = kThreads / 16;
     const dim3 gw((n + waves - 1) / waves), gs(gw.x, a.n_probs), gp((n + points - 1) / points, a.n_clusters);
     if (a.h) {
