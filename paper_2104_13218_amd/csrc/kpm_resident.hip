@@ -611,7 +611,7 @@ __device__ __forceinline__ int sturm_below(const double* al, const double* be2, 
     r = fma(fma(-q, r, 1.0), r, r);
     r = fma(fma(-q, r, 1.0), r, r);
     q = al[i] - x - (i ? be2[i - 1] * r : 0.0);
-    if (fabs(q) < 1e-290) q = -1e-290;
+    if (fabs(q) < 1e-140) q = -1e-140;   // its reciprocal times be2 stays finite up to 1e168
     cnt += q < 0.0;
   }
   return cnt;
