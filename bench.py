@@ -65,7 +65,7 @@ METRIC = "Chebyshev steps·dim/s + HBM GB/s at N=24 S^z=0; speedup vs FP64 at C(
 HBM_PEAK_GBS = 8000.0
 # step kernel families as reported by kpm_last_run_stats()["kernel"]
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X, dense float64 vector arithmetic
-KERNEL_FAMILY = {0: "step_kernel", 1: "row_kernel", 2: "block_kernel", 3: "tab_kernel", 4: "spin_split_kernel",
+KERNEL_FAMILY = {0: "step_kernel", 1: "row_kernel", 2: "block_kernel", 3: "tab_kernel", 4: "spin_kernel",
                  5: "slice_kernel", 6: "res_moments_kernel"}
 PROFILES = os.path.join(ROOT, "profiles")
 
@@ -261,10 +261,19 @@ def _line(args, workload, value, unit, dt, config, roofline=None, extra=None):
     return line
 
 
-def _roofline(st, tag=None):
+def _spin_family(st, sectors, element_bytes, columns):
+    """Which of the two spin-s kernels ran, from the bytes of a launch: beside
+    the vectors the list kernel reads 8 + 8 bonds bytes a row and column block."""
+    vectors = 3.0 * element_bytes * st["state_col_steps"] / st["step_launches"]
+    blocks = -(-columns // st["col_block"])
+    lists = blocks * sum(s.dim * (8.0 + 8.0 * len(s.cluster.J)) for s in sectors)
+    return "spin_kernel" if abs(st["bytes_per_launch"] - vectors - lists) < 1e-6 * lists else "spin_split_kernel"
+
+
+def _roofline(st, tag=None, family=None):
     t = st["recursion_ms"] / 1e3 / st["step_launches"]
     ach = st["bytes_per_launch"] / t / 1e9
-    family = KERNEL_FAMILY.get(st["kernel"], "step_kernel")
+    family = family or KERNEL_FAMILY.get(st["kernel"], "step_kernel")
     traffic = _traffic(family, tag, st) if tag else None
     return {"bound": "hbm", "kernel": family, "achieved": ach,
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
@@ -334,9 +343,9 @@ def other_workload(args, kpm, W, np, torch, dev):
                "max_dim": int(max(dims)), "M": wl.M, "vectors": f"{wl.R} {wl.vec_kind}", "storage": "f32",
                "col_block": st["col_block"], "bounds": "lanczos50+1% (outside the timing)", "device": dev}
         extra = {"fp64": {"value": st64["state_col_steps"] / dt64, "ms": dt64 * 1e3,
-                          "roofline": _roofline(st64, "fe10_fp64")}}
+                          "roofline": _roofline(st64, "fe10_fp64", _spin_family(st64, wl.problems, 8, wl.R))}}
         return _line(args, name, st["state_col_steps"] / dt, "state-column-steps/s", dt, cfg,
-                     _roofline(st, "fe10_fp32"), extra)
+                     _roofline(st, "fe10_fp32", _spin_family(st, wl.problems, 4, wl.R)), extra)
     if name == "ed_batched":
         # exact spectra of the small sectors of the 64 random clusters (the
         # hybrid form: sectors of dimension <= 1024 diagonalised completely)
