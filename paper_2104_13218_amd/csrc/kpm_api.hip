@@ -1225,14 +1225,18 @@ int make_plan_shape(const kpm_problem* p, int n, const RunShape& s, const double
       }
       size_t len = 0;
       for (auto& q : queue) len = std::max(len, q.size());
-      // its rows are then fetched into one L2 instead of eight; taken where
-      // no XCD gets over 5 % more than the mean and a slot is of the size it
-      // was measured at (20-site sawtooth chain, 55 blocks: 129 against 137
-      // us; eight random clusters, 228 blocks of up to 23 MB: 958 against
-      // 978; with 22 blocks, unevenly, 61 against 59)
+      // its rows are then fetched into one L2 instead of eight, but a large
+      // block's far rows no longer come from the memory-side cache while the
+      // other XCDs use them.  Taken where no XCD gets over 5 % more than the mean
+      // (else 0.2 to 0.9 times the speed) and slots are of up to 4 MB on average:
+      // 20-site sawtooth chain, 55 blocks, 2 MB on average, 129 against 137 us;
+      // eight random clusters, 228 blocks, 2 MB, 958 against 978.  460 pairs, rings,
+      // sawtooth chains and random clusters, by average slot: up to 1 MB 0.98-1.22
+      // times as fast, 2 MB 0.94-1.1, 6 MB 0.93-1.01, 11 MB 0.90-1.02, 22 MB
+      // 0.86-0.99, 83 MB 0.87-0.95.
       if (D.xcd_remap < 0)
         D.xcd_remap = (double)len * 8 <= 1.05 * tiles &&
-                              largest_sector(p, n) * D.ld_max * elt <= (int64_t(24) << 20)
+                              vec_elems * elt <= (int64_t)P.units.size() << 22
                           ? 3
                           : 2;
       if (D.xcd_remap == 3)
