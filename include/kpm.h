@@ -301,7 +301,7 @@ size_t kpm_sector_eigenvalues_workspace_size(const kpm_problem* p, int32_t n, in
  *  max_dim   1..1024
  *  d_evals   device double [n][max_dim]
  *  d_work    device workspace of kpm_sector_eigenvalues_workspace_size bytes
- *            (8 D^2 + 32 max(D, 4) per diagonalised sector + small tables), or
+ *            (8 D^2 + 48 max(D, 4) per diagonalised sector + small tables), or
  *            NULL: allocated and freed inside the call
  * Errors: KPM_EINVAL, KPM_EWORKSPACE, KPM_EDEVICE (HIP error, or a neighbour
  * rank outside its sector). */
@@ -422,7 +422,8 @@ typedef struct {
                               6 resident (every step of a column in one launch,
                               its vectors on one compute unit: float64 calls
                               whose sectors all have at most 19456 states and
-                              32 bonds; step_launches still counts the steps) */
+                              32 bonds, where that is the faster way;
+                              step_launches still counts the steps) */
   double recursion_ms;     /* hipEvent time on the call's stream from the first
                               to the last recursion-step launch, inclusive */
   int32_t relabelled;      /* problems whose sites the block kernels relabel (fewer

@@ -542,7 +542,11 @@ void apply_scale(const kpm_problem* p, int n, const double* a_arr, const double*
 
 // Sectors from kSliceRows on have tiles enough to give every wave several
 // slices (two sub-tiles per workgroup: 24-site ring, 20 float32 columns, 281
-// against 290 us); below, one sub-tile.
+// against 290 us); below, one sub-tile.  Speed of large sectors' shape over that of
+// small ones (rings and random clusters, one sector and six, 4 and 20 columns):
+// float64 48620 to 705432 states 0.96-1.08, 1144066 and more 1.03-1.07; float32
+// 48620 0.71-0.95, 184756 0.78-1.04, 705432 0.94-1.07, 1352078 0.97-1.10, 2704156
+// and more 1.02-1.10.
 constexpr int64_t kSliceRows = int64_t(1) << 21;
 // Below this the recursion is bound by the chain of loads inside one step
 // (13-15 us either way) and keeps the row and block-table kernels.
@@ -3066,8 +3070,12 @@ struct FtlmLayout {
 // width 1 splits a complex vector's Re and Im into separate blocks).
 // FTLM runs float64 vectors.  Without a requested block width, spin-1/2
 // problems take the slice kernel on blocks of 4 columns (ring N=24, 20
-// columns, 200 steps: 195 ms per call, 201 ms on blocks of 2, 301 ms with the
-// block-table kernel); the planner falls back where no slice plan exists.
+// columns, 200 steps: 170 ms per call; on the kernel's first form 195 ms, 201 on
+// blocks of 2, 301 with the block-table kernel); the planner falls back where no
+// slice plan exists.  slice_tune's shape, four blocks a sub-tile instead of up to
+// 64, also in small sectors: 176 calls of 252 to 184756 states, 9 to 40 bonds and 1
+// to 40 columns 1.36 times as fast (1.00 at 252 states, 4.9 at 184756 states and
+// one column), 170 of high S^z 2.8 times (1.13 to 7.9).
 RunShape ftlm_shape(const kpm_params& q, const kpm_problem* p, int n) {
   RunShape s = shape_of(q);
   s.precision = KPM_FP64;

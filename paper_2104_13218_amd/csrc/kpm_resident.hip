@@ -27,9 +27,9 @@
 // states they had (a chain of dependent loads through L2, then the next
 // launch), and five launches per Lanczos step.  Measured: the 12-site ring
 // (7 sectors, 20 columns, 128 steps) 30 -> 1.0 us per step, a whole call with
-// bounds and thermodynamics 5.82 -> 0.46 ms; the 16-site ladder (9 sectors up
+// bounds and thermodynamics 5.87 -> 0.47 ms; the 16-site ladder (9 sectors up
 // to 12870 states, 200 columns, 50 steps) 111 -> 45 us per step and 117 ->
-// 14 us per Lanczos step, the call 13.0 -> 3.2 ms.
+// 14 us per Lanczos step, the call 13.0 -> 3.0 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

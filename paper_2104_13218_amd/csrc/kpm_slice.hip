@@ -34,8 +34,9 @@
 // Which mixed bonds act is one exclusive-or: the word row holds the low sites'
 // bits, the block record the high sites' bits.  Their coefficients are in LDS
 // and the loops' conditions are kept inside the slice loop (fresh_uniform):
-// held in scalar registers across it, they spilled 166 of them to vector
-// lanes (64-byte word rows; now 43) and cost more than the mixed rows' loads.
+// held in scalar registers across it, they spilled 80 of them to vector lanes
+// (4 float32 columns, 32-byte word rows; now 40) or 168 (64-byte; now 48) and cost
+// more than the mixed rows' loads.
 // Measured before and after, us per step: 24-site ring, 20 float32 columns 287
 // and 280; 20-site sawtooth chain, all sectors, 20 float64 columns, one
 // sub-tile of 4 waves, 232 and 174; eight random clusters, 32 float32 columns
