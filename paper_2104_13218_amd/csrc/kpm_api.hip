@@ -639,6 +639,17 @@ int64_t most_columns(const kpm_problem* p, int n, const RunShape& s) {
   return c;
 }
 
+// States of the largest sector per block of low words.
+double slice_members(const kpm_problem* p, int n) {
+  int at = 0;
+  for (int i = 1; i < n; ++i)
+    if (prob_dim(p[i]) > prob_dim(p[at])) at = i;
+  const int L = std::min(10, p[at].n_sites);
+  double blocks = 0.0;
+  for (int k = 0; k <= L; ++k) blocks += (double)binom64(p[at].n_sites - L, p[at].n_up - k);
+  return (double)prob_dim(p[at]) / blocks;
+}
+
 // Whether the slice kernel is the faster one for the call's largest sector.  A
 // wave works on one block of low words at a time, so blocks of few members (high
 // S^z) leave its lanes idle, and rows under 16 bytes (one float64, one or two
@@ -651,14 +662,8 @@ int64_t most_columns(const kpm_problem* p, int n, const RunShape& s) {
 //   narrow rows: 80 members 0.84-0.96, 190 1.0, from 2^19 states on 1.2-3.3
 //   5-8 float32 columns: 30-80 members 0.86-1.06, from 2^18 states on 1.07-1.3
 bool slice_pays(const kpm_problem* p, int n, const RunShape& s) {
-  int at = 0;
-  for (int i = 1; i < n; ++i)
-    if (prob_dim(p[i]) > prob_dim(p[at])) at = i;
-  const int64_t d = (int64_t)prob_dim(p[at]), c = most_columns(p, n, s);
-  const int L = std::min(10, p[at].n_sites);
-  double blocks = 0.0;
-  for (int k = 0; k <= L; ++k) blocks += (double)binom64(p[at].n_sites - L, p[at].n_up - k);
-  const double members = (double)d / blocks;
+  const int64_t d = largest_sector(p, n), c = most_columns(p, n, s);
+  const double members = slice_members(p, n);
   const bool fp32 = s.precision == KPM_FP32_STORE;
   if (members < (c > 8 && d >= (int64_t(1) << 20) ? 48.0 : 32.0)) return false;
   if (c <= (fp32 ? 2 : 1)) return members >= 100.0 || d >= (int64_t(1) << 19);
@@ -667,14 +672,23 @@ bool slice_pays(const kpm_problem* p, int n, const RunShape& s) {
 }
 
 // Columns of the default slice plan's blocks, where they are not slice_tune's:
-// two float64 columns where blocks of four would hold two or three empty ones (5
-// columns of 24 sites, S^z = 0, 6.6 -> 5.4 ms for 30 steps; 28 sites, 9 columns,
-// 7.8 -> 6.6 GB), four float32 columns where one block does and waves are few (18
-// sites, 8 columns, 0.72 -> 0.61 ms).
+// two float64 columns instead of four where those would leave two or three of a
+// block empty and that costs more than narrow rows do.  Time on blocks of four
+// over that on two: 5 and 6 columns 1.00-1.30; 9 and 10 0.95-1.4; 13 to 18 one
+// sector of S^z near 0 0.90-1.15 below 2^21 states, 1.00-1.07 to 2^23 and 1.04-1.12
+// above, where 21 to 34 are 0.99-1.08; several sectors or high S^z 0.87-0.95, many
+// columns 0.65-0.9.  From 2^26 states on a column is 1 GB and always worth it (28
+// sites, 9 columns 7.8 -> 6.6 GB).  Four float32 columns where one block does and
+// waves are few (18 sites, 8 columns, 0.72 -> 0.61 ms).
 int slice_width(const kpm_problem* p, int n, const RunShape& s, int width) {
-  const int64_t c = most_columns(p, n, s);
-  if (s.precision == KPM_FP64) return c > 4 && (c % 4 == 1 || c % 4 == 2) ? 2 : width;
-  return c <= 8 && largest_sector(p, n) < (int64_t(1) << 18) ? 4 : width;
+  const int64_t c = most_columns(p, n, s), d = largest_sector(p, n);
+  if (s.precision != KPM_FP64) return c <= 8 && d < (int64_t(1) << 18) ? 4 : width;
+  if (c <= 4 || c % 4 == 0 || c % 4 == 3) return width;
+  if (c <= 10 || d >= (int64_t(1) << 26)) return 2;
+  double rows = 0.0;
+  for (int i = 0; i < n; ++i) rows += (double)prob_dim(p[i]);
+  const bool one = rows < 1.5 * (double)d && slice_members(p, n) >= 100.0;
+  return one && d >= (int64_t(1) << 21) && c <= (d >= (int64_t(1) << 23) ? 34 : 18) ? 2 : width;
 }
 
 // Whether make_plan takes the slice kernel by itself.

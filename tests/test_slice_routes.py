@@ -36,6 +36,20 @@ def test_padding_of_float64_blocks(R):
     assert _size([sec], R, "fp64") <= 16 * sec.dim * (R + 1) * 1.08
 
 
+@pytest.mark.parametrize("secs,R,two", [
+    (W.sectors(W.ring(20)), 6, True), (W.sectors(W.ring(20)), 10, True), (W.sectors(W.ring(20)), 13, False),
+    (W.sectors(W.ladder(22)), 121, False), ([W.Sector(W.ring(22), 11, 0)], 14, False),
+    ([W.Sector(W.ring(24), 12, 0)], 18, True), ([W.Sector(W.ring(24), 12, 0)], 21, False),
+    ([W.Sector(W.ring(26), 17, 0)], 13, False), ([W.Sector(W.ring(30), 15, 0)], 121, True)])
+def test_width_of_float64_blocks(secs, R, two):
+    """Two columns, at most one of them empty, or four: few columns, one large
+    sector, or memory, but not many columns of many sectors."""
+    rows = 16 * sum(s.dim for s in secs)
+    got = _size(secs, R, "fp64")
+    narrow = rows * (R + R % 2)
+    assert narrow <= got < 1.09 * narrow if two else got >= rows * ((R + 3) // 4 * 4)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,n_up,R,precision,kernel", [
     (20, 15, 3, "fp64", None), (20, 13, 1, "fp64", 1), (20, 13, 2, "fp64", 5), (22, 16, 9, "fp64", 3), (18, 9, 5, "fp64", 5),
