@@ -1704,15 +1704,16 @@ bool resident_moments_pay(const kpm_problem* p, int n, const RunShape& s, int64_
 }
 
 // The same for the gradient, whose workgroups have half the threads: stepped
-// over resident, one column, 400 moments: 6435 states 1.3-1.45, 8855 states
-// 0.95-1.1, 12870 states 0.75-0.85; 16 columns: 12870 states 1.2-1.85, 19448
-// states 0.78-0.94 with 9 bonds and 1.03-1.35 with 16 and more.
+// over resident, one column, 400 moments: 6435 states 1.5-1.7, 8855 states 1.1-1.5;
+// 12870 states, us a step, resident 40-64, stepped with 1, 8 and 16 columns 35-54,
+// 40-69, 73-141; 16 columns: 12870 states 1.4-2.3, 19448 states 0.78-0.94 with 9
+// bonds and 1.03-1.35 with 16 and more.
 bool resident_gradient_pays(const kpm_problem* p, int n, const RunShape& s, int64_t K) {
   const int64_t d = largest_sector(p, n);
-  if (d <= 8192 || K < 12) return true;
+  if (d <= 10240 || K < 12) return true;
   int least = INT32_MAX;
   for (int i = 0; i < n; ++i) least = std::min(least, p[i].n_bonds);
-  if (d <= 13312) return columns_worth(p, n, s) >= (d <= 10240 ? 3.0 : 9.0);
+  if (d <= 13312) return columns_worth(p, n, s) >= 9.0;
   return least >= 16 && columns_worth(p, n, s) >= 16.0;
 }
 

@@ -16,8 +16,7 @@
 // again.  Error against 80-bit sums, as a multiple of the step kernels': 126 sets
 // of 64 to 1000 moments 2.06, sawtooth chains up to 7, and 0.88 with the table; 60
 // gradients 2.09 and 0.74, differences P_b v - v instead 2.08.  The table costs 2
-// to 7 % of a step of the moments, the choice of every dot's operand 10 to 20 % of
-// the gradient's.)
+// to 7 % of a step of the moments.)
 //
 // What bounds it: the LDS gathers.  A row needs one 8-byte LDS read per bond,
 // 64 lanes to scattered addresses; with one row per thread the two barriers
@@ -161,7 +160,6 @@ struct Rows {
   static constexpr bool kKeep = RPT * NCH <= 8;
   uint4 q[kKeep ? RPT : 1][NCH];
   double d[kKeep ? RPT : 1];
-  uint32_t off[kKeep ? RPT : 1];
   const uint4* src;
   const double* dsrc;
   const uint32_t* osrc;
@@ -218,10 +216,20 @@ __device__ __forceinline__ void product(const Rows<RPT, NCH>& R, cptr<double> cf
   }
 }
 
-// The product with its bond dots: D[b] += v x[P_b r] over the thread's rows
-// (x[r] = xr where the bond does not act: its bit of `off`; testing the index
-// itself holds it, and 254 registers spilled at 38 rows of 32 bonds), v = of(row, on).
-template <int NCH>
+// Whether the sums of v x[r] over the steps, one per row, fit the registers
+// beside the bond dots (rows kept in registers: always).
+template <int RPT, int NCH>
+constexpr bool kRowSums = RPT <= 16 || (RPT <= 26 && NCH <= 3);
+
+// The product with its bond dots: D[b] += v x[P_b r] over the thread's rows, v =
+// of(row, on).  Where the bond does not act the term is v x[r]: the same at every
+// step, so with kRowSums it is left out here (the index gives a zero) and added at
+// the end from the row's own sum.  Else the operand is picked by the row's bit of
+// `off` (testing the index itself holds it, and 254 registers spilled at 38 rows
+// of 32 bonds), which takes 10 to 20 % of a step: a gradient of 16 columns and 150
+// steps, 1716 states and 32 bonds 1.52 ms, with the rows' sums 1.26; 12870 states
+// and 8 bonds 6.0 and 5.1.
+template <int NCH, bool kPick>
 __device__ __forceinline__ double gather_dots(const uint4 (&q)[NCH], cptr<double> cf, const double* x, double v, double xr,
                                               uint32_t off, double (&D)[NCH * 8]) {
   double acc = 0.0;
@@ -234,7 +242,7 @@ __device__ __forceinline__ double gather_dots(const uint4 (&q)[NCH], cptr<double
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       acc = fma(cf[ch * 8 + t], g[t], acc);
-      D[ch * 8 + t] = fma(v, off >> (ch * 8 + t) & 1u ? xr : g[t], D[ch * 8 + t]);
+      D[ch * 8 + t] = fma(v, kPick && (off >> (ch * 8 + t) & 1u) ? xr : g[t], D[ch * 8 + t]);
     }
   }
   return acc;
@@ -245,11 +253,12 @@ __device__ __forceinline__ void product_dots(const Rows<RPT, NCH>& R, cptr<doubl
   uint4 nxt[NCH];
   double dn = 0.0;
   uint32_t offn = 0u;
+  constexpr bool kPick = !kRowSums<RPT, NCH>;
   tid = (int)fresh((uint32_t)tid);
   if constexpr (!Rows<RPT, NCH>::kKeep) {
     R.load(0, min((uint32_t)tid, R.dim - 1u), nxt);
     dn = at(R.dsrc, min((uint32_t)tid, R.dim - 1u));
-    offn = R.osrc[min((uint32_t)tid, R.dim - 1u)];
+    if constexpr (kPick) offn = R.osrc[min((uint32_t)tid, R.dim - 1u)];
   }
 #pragma unroll
   for (int k = 0; k < RPT; ++k) {
@@ -267,18 +276,15 @@ __device__ __forceinline__ void product_dots(const Rows<RPT, NCH>& R, cptr<doubl
           cur[ch] = nxt[ch];
       }
       double d = dn;
-      uint32_t off = offn;
-      if constexpr (Rows<RPT, NCH>::kKeep) {
-        d = R.d[k];
-        off = R.off[k];
-      }
+      const uint32_t off = offn;
+      if constexpr (Rows<RPT, NCH>::kKeep) d = R.d[k];
       if constexpr (!Rows<RPT, NCH>::kKeep)
         if (k + 1 < RPT && r0 + (uint32_t)T < R.dim) {
           R.load(k + 1, min(r + (uint32_t)T, R.dim - 1u), nxt);
           dn = at(R.dsrc, min(r + (uint32_t)T, R.dim - 1u));
-          offn = R.osrc[min(r + (uint32_t)T, R.dim - 1u)];
+          if constexpr (kPick) offn = R.osrc[min(r + (uint32_t)T, R.dim - 1u)];
         }
-      const double h = gather_dots<NCH>(cur, cf, x, v, x[rc], off, D);
+      const double h = gather_dots<NCH, kPick>(cur, cf, x, v, kPick ? x[rc] : 0.0, off, D);
       use(k, rc, r < R.dim, h, d, v);
       if constexpr (!Rows<RPT, NCH>::kKeep) __builtin_amdgcn_sched_barrier(0);
     }
@@ -299,7 +305,6 @@ __device__ __forceinline__ void rows_init(Rows<RPT, NCH>& R, const ResArgs& a, c
       const uint32_t r = min((uint32_t)(tid + k * T), dim - 1u);
       R.load(k, r, R.q[k]);
       R.d[k] = at(R.dsrc, r);
-      R.off[k] = R.osrc[r];
     }
   }
 }
@@ -480,7 +485,10 @@ __global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResAr
   };
   Rows<RPT, NCH> R;
   rows_init(R, a, I, dim, tid, T);
-  double y[RPT], D[NCH * 8], s0 = 0.0;
+  constexpr bool kSums = kRowSums<RPT, NCH>;
+  double y[RPT], D[NCH * 8], S[kSums ? RPT : 1];              // S: sums of v_n w_{n+1}, by row or of all rows
+#pragma unroll
+  for (int k = 0; k < (kSums ? RPT : 1); ++k) S[k] = 0.0;
 #pragma unroll
   for (int b = 0; b < NCH * 8; ++b) D[b] = 0.0;
 #pragma unroll
@@ -567,7 +575,8 @@ __global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResAr
       product_dots<RPT, NCH>(R, cf, x, tid, T, D, [&](uint32_t r, bool on) { return on ? 2.0 * at(v0, r) : 0.0; },
                              [&](int k, uint32_t r, bool on, double h, double d, double v2) {
                                const double wr = x[r];
-                               s0 = fma(v2, wr, s0);
+                               double& s = S[kSums ? k : 0];
+                               s = fma(v2, wr, s);
                                const double g = fma(gbm, at(vm, r), fma(gb, at(vp, r), ga * v2));
                                y[k] = on ? g + fma(2.0, fma(d - sb, wr, h) * inva, -y[k]) : 0.0;
                              });
@@ -576,7 +585,23 @@ __global__ __launch_bounds__(kResAdjThreads) void res_adjoint_kernel(const ResAr
   }
   // <w_1, h_b v_0> with weight 1 (slot 0 of segment 0 is v_0)
   product_dots<RPT, NCH>(R, cf, x, tid, T, D, [&](uint32_t r, bool on) { return on ? at(static_cast<const double*>(seg), r) : 0.0; },
-                         [&](int, uint32_t r, bool, double, double, double v) { s0 = fma(v, x[r], s0); });
+                         [&](int k, uint32_t r, bool, double, double, double v) {
+                           double& s = S[kSums ? k : 0];
+                           s = fma(v, x[r], s);
+                         });
+  double s0 = S[0];
+  if constexpr (kSums) {
+    // the terms of the bonds that do not act, 0 past the last row
+    s0 = 0.0;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const uint32_t r = (uint32_t)(tid + k * T);
+      const uint32_t off = r < dim ? R.osrc[r] : 0u;
+      s0 += S[k];
+#pragma unroll
+      for (int b = 0; b < NCH * 8; ++b) D[b] += off >> b & 1u ? S[k] : 0.0;
+    }
+  }
   const double sq = group_sum(s0, red, lane, wid, nw);
 #pragma unroll
   for (int b = 0; b < NCH * 8; ++b) {

@@ -42,8 +42,7 @@ def test_moments_by_columns(monkeypatch, n, n_up, M, R, resident):
 
 
 @pytest.mark.parametrize("n,n_up,M,R,resident", [
-    (16, 10, 400, 1, True),                             # 8008
-    (23, 19, 400, 2, False), (23, 19, 400, 3, True),    # 8855
+    (23, 19, 400, 1, True),                             # 8855
     (16, 8, 400, 8, False), (16, 8, 400, 9, True),      # 12870
     (17, 10, 400, 15, False), (17, 10, 400, 16, True),  # 19448
     (17, 10, 23, 1, True), (17, 10, 24, 1, False),      # 11 and 12 steps
@@ -100,3 +99,22 @@ def test_checkpointed_gradient_beside_resident_moments(kpm):
     want = adjoint.sector_moments_vjp(sec, a, b, M, R, "rademacher", 2, lam[0])
     assert np.abs(got - want).max() <= 1e-9 * np.abs(want).max()
     assert np.abs(once - want).max() <= 1e-9 * np.abs(want).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,n_up,n_bonds,R", [
+    (9, 5, 14, 2), (12, 6, 9, 2), (12, 6, 31, 2), (13, 7, 17, 2), (14, 7, 32, 2),   # 1 to 8 rows a thread
+    (16, 10, 16, 2), (16, 10, 25, 2),                                               # 16 rows, two and four index entries
+    (16, 8, 16, 9), (16, 8, 24, 9),                                                 # 26 rows, row sums
+    (16, 8, 25, 9), (17, 10, 16, 16)])                                              # 26 and 38 rows, operands picked
+def test_gradient_of_bonds_that_do_not_act(kpm, n, n_up, n_bonds, R):
+    """Every number of rows a thread has, with and without the rows' own sums."""
+    import torch
+    from oracle import adjoint
+    sec, M = W.Sector(_graph(n, n_bonds, 5), n_up, 0), 26
+    a, b = 1.1 * n_bonds, 0.3
+    ab = torch.tensor([[a, b]], dtype=torch.float64, device="cuda")
+    lam = np.random.default_rng(2).normal(size=(1, M))
+    got = kpm.moments_vjp([sec], M, R, ab, torch.tensor(lam, device="cuda"), seed=4, ckpt_every=4).cpu().numpy()
+    want = adjoint.sector_moments_vjp(sec, a, b, M, R, "rademacher", 4, lam[0])
+    assert np.abs(got - want).max() <= 1e-9 * np.abs(want).max()
