@@ -1703,17 +1703,25 @@ bool resident_moments_pay(const kpm_problem* p, int n, const RunShape& s, int64_
   return d <= 13312 || K < 24 || columns_worth(p, n, s) >= (d <= 16384 ? 3.0 : 9.0);
 }
 
-// The same for the gradient, whose workgroups have half the threads: stepped
-// over resident, one column, 400 moments: 6435 states 1.5-1.7, 8855 states 1.1-1.5;
-// 12870 states, us a step, resident 40-64, stepped with 1, 8 and 16 columns 35-54,
-// 40-69, 73-141; 16 columns: 12870 states 1.4-2.3, 19448 states 0.78-0.94 with 9
-// bonds and 1.03-1.35 with 16 and more.
+// The same for the gradient, whose workgroups have half the threads and, from 26
+// rows a thread on, pick the operands of the dots of more than 24 bonds.  Time of
+// 400 moments stepped over resident, 1, 2, 3 to 8, 9 and more columns:
+//   6435 states             1.5-1.7  1.7-1.8  1.7-2.1   2.5 and more
+//   8855, up to 24 bonds    1.2-1.3  1.2-1.35 1.3-1.6   1.5-1.8
+//     25 and 32             0.85-0.95 0.9-1.0 0.97-1.15 1.3-1.4
+//   12870, up to 24 bonds   0.83-0.94 0.88-1.0 0.94-1.2 1.03-1.5  (60 moments 0.96-1.1 with one)
+//     25 and 32             0.63-0.75 0.63-0.8 0.7-0.98 0.89-1.2
+//   19448, 16 columns       0.78-0.94 with 9 bonds, 1.03-1.35 with 16 and more
 bool resident_gradient_pays(const kpm_problem* p, int n, const RunShape& s, int64_t K) {
-  const int64_t d = largest_sector(p, n);
-  if (d <= 10240 || K < 12) return true;
-  int least = INT32_MAX;
-  for (int i = 0; i < n; ++i) least = std::min(least, p[i].n_bonds);
-  if (d <= 13312) return columns_worth(p, n, s) >= 9.0;
+  const int64_t d = largest_sector(p, n), c = most_columns(p, n, s);
+  if (d <= 8192 || K < 12) return true;
+  int least = INT32_MAX, most = 0;
+  for (int i = 0; i < n; ++i) {
+    least = std::min(least, p[i].n_bonds);
+    most = std::max(most, p[i].n_bonds);
+  }
+  if (d <= 10240) return most <= 24 || c >= 3;
+  if (d <= 13312) return most <= 24 ? c >= 3 || K <= 32 : c >= 9;
   return least >= 16 && columns_worth(p, n, s) >= 16.0;
 }
 

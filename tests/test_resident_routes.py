@@ -43,7 +43,8 @@ def test_moments_by_columns(monkeypatch, n, n_up, M, R, resident):
 
 @pytest.mark.parametrize("n,n_up,M,R,resident", [
     (23, 19, 400, 1, True),                             # 8855
-    (16, 8, 400, 8, False), (16, 8, 400, 9, True),      # 12870
+    (16, 8, 400, 2, False), (16, 8, 400, 3, True),      # 12870
+    (16, 8, 64, 1, True), (16, 8, 66, 1, False),        # 32 and 33 steps
     (17, 10, 400, 15, False), (17, 10, 400, 16, True),  # 19448
     (17, 10, 23, 1, True), (17, 10, 24, 1, False),      # 11 and 12 steps
 ])
@@ -58,12 +59,25 @@ def test_gradient_of_few_bonds_keeps_the_step_kernels(monkeypatch):
         assert (got != stepped) == resident
 
 
+@pytest.mark.parametrize("n,n_up,R,resident", [
+    (23, 19, 2, False), (23, 19, 3, True),              # 8855
+    (16, 8, 8, False), (16, 8, 9, True),                # 12870
+])
+def test_gradient_of_many_bonds(monkeypatch, n, n_up, R, resident):
+    got, stepped = _sizes(monkeypatch, [W.Sector(_graph(n, 25), n_up, 0)], 400, R, "gradient")
+    assert (got != stepped) == resident
+
+
 def test_smaller_sectors_count_by_their_rows(monkeypatch):
-    """All sectors of 16 sites: 39203 rows, three times the largest's."""
-    secs = W.sectors(_graph(16, 24))
-    for R, resident in ((2, False), (3, True)):
-        got, stepped = _sizes(monkeypatch, secs, 400, R, "gradient")
-        assert (got != stepped) == resident
+    """The sectors of 17 sites that can be resident: the largest has 19448 of
+    their 41226 rows."""
+    secs = [s for s in W.sectors(_graph(17, 24)) if s.dim < 20000]
+    rows = sum(s.dim for s in secs) / max(s.dim for s in secs)
+    for kind, line in (("moments", 9), ("gradient", 16)):
+        at = int(-(-line // rows))
+        for R, resident in ((at - 1, False), (at, True)):
+            got, stepped = _sizes(monkeypatch, secs, 400, R, kind)
+            assert (got != stepped) == resident, (kind, R)
 
 
 @pytest.mark.gpu
@@ -80,11 +94,11 @@ def test_moments_on_either_side(kpm, R):
 
 @pytest.mark.gpu
 def test_checkpointed_gradient_beside_resident_moments(kpm):
-    """16 sites, four columns: the moments run resident, the gradient on the
+    """16 sites, 28 bonds, four columns: the moments run resident, the gradient on the
     step kernels; forward, resumed and single call against the oracle."""
     import torch
     from oracle import adjoint
-    sec, M, R = W.Sector(_graph(16, 20), 8, 0), 30, 4
+    sec, M, R = W.Sector(_graph(16, 28), 8, 0), 30, 4
     ps = kpm.ProblemSet([sec])
     mu, ab, ws = kpm.moments_ckpt(None, M, R, seed=2, ckpt_every=4, problems=ps)
     mu0, ab0 = kpm.chebyshev_moments([sec], M, R, seed=2)
